@@ -161,34 +161,31 @@ __global__ __launch_bounds__(256) void k_batch_clear_err(const DecompressJob* __
     if (j < n_jobs && jobs[j].err) *jobs[j].err = 0u;
 }
 
-__global__ __launch_bounds__(64, 2) void k_batch_decompress(const DecompressJob* __restrict__ jobs,
-                                                         const int32_t* __restrict__ chunk_job)
+__global__ __launch_bounds__(512, 4) void k_batch_decompress(const DecompressJob* __restrict__ jobs,
+                                                             const int32_t* __restrict__ chunk_job)
 {
-    __shared__ float tile[kTileFloats];
+    __shared__ DecompressLds<8> S;
     const DecompressJob& J = jobs[chunk_job[blockIdx.x]];
     const int64_t c = (int64_t)blockIdx.x - J.chunk0;
-    const int lane = threadIdx.x;
-    switch (J.key) {
-        case 7: decompress_chunk_any<3, true>(J.s, J.s_bytes, J.y, J.g, J.err, c, lane, tile); break;
-        case 6: decompress_chunk_any<3, false>(J.s, J.s_bytes, J.y, J.g, J.err, c, lane, tile); break;
-        case 5: decompress_chunk_any<2, true>(J.s, J.s_bytes, J.y, J.g, J.err, c, lane, tile); break;
-        case 4: decompress_chunk_any<2, false>(J.s, J.s_bytes, J.y, J.g, J.err, c, lane, tile); break;
-        case 3: decompress_chunk_any<1, true>(J.s, J.s_bytes, J.y, J.g, J.err, c, lane, tile); break;
-        default: decompress_chunk_any<1, false>(J.s, J.s_bytes, J.y, J.g, J.err, c, lane, tile); break;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const bool stream = (J.key & 1) != 0;
+    const uint8_t* s = as_global(J.s);
+    float* y = as_global(J.y);
+    uint32_t* err = as_global(J.err);
+    switch (J.key >> 1) {
+        case 3: decompress_chunk<3>(s, J.s_bytes, y, stream, J.g, err, c, wave, lane, S); break;
+        case 2: decompress_chunk<2>(s, J.s_bytes, y, stream, J.g, err, c, wave, lane, S); break;
+        default: decompress_chunk<1>(s, J.s_bytes, y, stream, J.g, err, c, wave, lane, S); break;
     }
 }
 
 // ------------------------------------------------------------------- plans
 namespace {
 
-// launch class of a field: rank and whether whole 16-byte accesses apply
-// (decompression: 16-byte aligned output rows of whole 16-byte pieces;
-// compression: 4-byte aligned input, vec_loads)
-int vec_key(const void* p, const Geom& g)
-{
-    const bool vec4 = (reinterpret_cast<uintptr_t>(p) & 15) == 0 && (g.rank == 1 || (g.n[g.rank - 1] & 3) == 0);
-    return g.rank * 2 + (vec4 ? 1 : 0);
-}
+// launch class of a field: rank and, for decompression, whether its stores
+// stream (stream_stores); for compression, whether its loads are 16 bytes wide
+// (vec_loads)
+int decompress_key(const void* p, const Geom& g) { return g.rank * 2 + (stream_stores(p, g, 4) ? 1 : 0); }
 
 int compress_key(const void* p, const Geom& g) { return g.rank * 2 + (vec_loads(p) ? 1 : 0); }
 
@@ -279,7 +276,7 @@ hipError_t plan_run(const Plan* P, hipStream_t st)
         const DecompressJob* jobs = static_cast<const DecompressJob*>(P->d_jobs);
         hipLaunchKernelGGL(k_batch_clear_err, dim3((P->n_jobs + 255) / 256), dim3(256), 0, st, jobs, P->n_jobs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_batch_decompress, dim3((unsigned)P->total_chunks), dim3(64), 0, st, jobs, P->d_chunk_job);
+        hipLaunchKernelGGL(k_batch_decompress, dim3((unsigned)P->total_chunks), dim3(512), 0, st, jobs, P->d_chunk_job);
         return hipGetLastError();
     }
     const CompressJob* jobs = static_cast<const CompressJob*>(P->d_jobs);
@@ -392,7 +389,7 @@ int plan_decompress(Plan* Pp, int n, const fz_decompress_job* jobs)
         J.s_bytes = q.stream_bytes;
         J.y = q.d_out;
         J.err = q.d_err;
-        J.key = vec_key(q.d_out, J.g);
+        J.key = decompress_key(q.d_out, J.g);
         J.chunk0 = chunks;
         chunks += J.g.n_chunks;
         P.djobs.push_back(J);

@@ -42,7 +42,7 @@ __device__ __forceinline__ void log_escapes(const int (&d)[32], uint32_t (&P)[16
 #pragma unroll
     for (int i = 0; i < 32; i++) emask |= ((uint32_t)d[i] + 32767u > kEscapeLimit ? 1u : 0u) << i;
     const int cnt = __popc(emask);
-    const int incl = wave_incl_scan(cnt, lane);
+    const int incl = wave_incl_scan(cnt);
     const int total = __shfl(incl, 63);
     int pos = log.count + incl - cnt;
 #pragma unroll

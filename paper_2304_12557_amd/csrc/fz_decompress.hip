@@ -1,6 +1,6 @@
 // fz_decompress.hip -- per-field decompression kernels of libfzmi (gfx950):
-// one wave per chunk, or for fields with few chunks a workgroup of 4 waves
-// per chunk (one per layer), running the device code of fz_decompress_dev.hpp.
+// a workgroup of 8 waves per chunk, or for fields with few chunks one of 16
+// waves, running the device code of fz_decompress_dev.hpp.
 #include <hip/hip_runtime.h>
 
 #include "fz_decompress_dev.hpp"
@@ -8,26 +8,25 @@
 
 namespace fz {
 
-template <int RANK, bool VEC4>
-__global__ __launch_bounds__(64, 2) void k_decompress(const uint8_t* __restrict__ s, uint64_t sb,
-                                                      float* __restrict__ y, Geom g, uint32_t* d_err)
+// 128 registers (4 waves per SIMD) and 72 KB of LDS: two workgroups per CU.
+template <int RANK, bool STREAM>
+__global__ __launch_bounds__(512, 4) void k_decompress(const uint8_t* __restrict__ s, uint64_t sb,
+                                                       float* __restrict__ y, Geom g, uint32_t* d_err)
 {
-    __shared__ float tile[kTileFloats];
-    decompress_chunk_any<RANK, VEC4>(s, sb, y, g, d_err, blockIdx.x, threadIdx.x, tile);
+    __shared__ DecompressLds<8> S;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    decompress_chunk<RANK, float, 8>(s, sb, y, STREAM, g, d_err, blockIdx.x, wave, threadIdx.x & 63, S);
 }
 
-// the same with a workgroup of NW waves per chunk, each on 4/NW layers
-// (fields with few chunks; launched with NW = 4).  Both forms are held to 2
-// waves per SIMD: left to itself the compiler took 258 registers for the 3-D
-// form, which allows only 1 (512^3 decompression 152 -> 132 us at 2).
-template <int RANK, bool VEC4, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void k_decompress_split(const uint8_t* __restrict__ s, uint64_t sb,
-                                                              float* __restrict__ y, Geom g, uint32_t* d_err)
+// the same with NW waves, one step each (fields with few chunks; launched
+// with NW = 16)
+template <int RANK, bool STREAM, int NW>
+__global__ __launch_bounds__(64 * NW, 4) void k_decompress_split(const uint8_t* __restrict__ s, uint64_t sb,
+                                                                 float* __restrict__ y, Geom g, uint32_t* d_err)
 {
-    __shared__ float tiles[NW][kTileFloats];
-    __shared__ int xch[NW * 2048];
+    __shared__ DecompressLds<NW> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    decompress_chunk_any<RANK, VEC4, NW>(s, sb, y, g, d_err, blockIdx.x, threadIdx.x & 63, tiles[wave], wave, xch);
+    decompress_chunk<RANK, float, NW>(s, sb, y, STREAM, g, d_err, blockIdx.x, wave, threadIdx.x & 63, S);
 }
 
 __global__ void k_set_u32(uint32_t* p, uint32_t v)
@@ -35,22 +34,21 @@ __global__ void k_set_u32(uint32_t* p, uint32_t v)
     if (threadIdx.x == 0) *p = v;
 }
 
-// fields of at most this many chunks are decompressed with 4 waves per chunk
-constexpr int64_t kSplitChunks = 512;
+// Fields of at most this many chunks (one workgroup per CU) are decompressed
+// with 16 waves per chunk: a lone workgroup of 8 waves leaves a SIMD with two
+// waves to hide each other's latency, one of 16 with four (128x128x256, 128
+// chunks: 11.0 us against 11.2-12.0 us a pass).  Beyond, two workgroups of 8
+// waves share a CU (256^3, 512 chunks: 21 us against 30 us).
+constexpr int64_t kSplitChunks = 256;
 
-template <int RANK, bool VEC4>
+template <int RANK, bool STREAM>
 static hipError_t launch_rank(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
-    // Up to 512 chunks (2048 waves, what the chip holds at 2 per SIMD) a chunk
-    // gets 4 waves: its latency, not the VALU throughput, then sets the time.
-    // Beyond, the single wave per chunk is faster (measured: a 2-wave form
-    // lost everywhere, since 2 waves on one SIMD share its VALU and the split
-    // adds a decode pass).
     if (g.n_chunks <= kSplitChunks)
-        hipLaunchKernelGGL((k_decompress_split<RANK, VEC4, kLayers>), dim3((unsigned)g.n_chunks), dim3(64 * kLayers), 0,
-                           st, s, sb, y, g, d_err);
+        hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), dim3((unsigned)g.n_chunks), dim3(1024), 0, st, s, sb,
+                           y, g, d_err);
     else
-        hipLaunchKernelGGL((k_decompress<RANK, VEC4>), dim3((unsigned)g.n_chunks), dim3(64), 0, st, s, sb, y, g, d_err);
+        hipLaunchKernelGGL((k_decompress<RANK, STREAM>), dim3((unsigned)g.n_chunks), dim3(512), 0, st, s, sb, y, g, d_err);
     return hipGetLastError();
 }
 
@@ -61,8 +59,8 @@ hipError_t launch_decompress(const uint8_t* s, uint64_t sb, float* y, const Geom
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const bool vec4 = (reinterpret_cast<uintptr_t>(y) & 15) == 0 && (g.rank == 1 || (g.n[g.rank - 1] & 3) == 0);
-    switch (g.rank * 2 + (vec4 ? 1 : 0)) {
+    const bool stream = stream_stores(y, g, 4);
+    switch (g.rank * 2 + (stream ? 1 : 0)) {
         case 7: return launch_rank<3, true>(s, sb, y, g, d_err, st);
         case 6: return launch_rank<3, false>(s, sb, y, g, d_err, st);
         case 5: return launch_rank<2, true>(s, sb, y, g, d_err, st);

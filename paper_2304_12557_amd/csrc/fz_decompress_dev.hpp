@@ -2,14 +2,16 @@
 // per-field kernel (fz_decompress.hip) and the batched one (fz_batch.hip).
 //
 // The inverse of the compression pass (Sec. 4.4 calls the two pipelines
-// symmetric).  One wave per chunk sweeps its steps in order.  Per step each
-// lane loads word t of its nonzero bricks (their positions follow from the bit
-// flags by popcount and mbcnt, Sec. 3.4) two steps before it computes them;
-// it undoes the bitshuffle with the same in-register transpose, decodes the
-// sign-magnitude codes (Sec. 3.2), and inverts the Lorenzo predictor as
-// inclusive prefix sums: along the patch in registers, across lanes for the
-// carries, and along the sweep dimension with the previous step kept in
-// registers.  Then it dequantizes (one fp32 multiply, Sec. 2.3) and stores.
+// symmetric).  A workgroup per chunk, its 16 steps shared out over the waves
+// (8 waves of 2 steps, or 16 of 1).  Each lane loads its steps' words of its
+// nonzero bricks (their positions follow from the bit flags by popcount and
+// mbcnt, Sec. 3.4), undoes the bitshuffle with the same in-register
+// transpose, decodes the sign-magnitude codes (Sec. 3.2), and inverts the
+// Lorenzo predictor as inclusive prefix sums: along the patch in registers,
+// across lanes for the carries, along the sweep dimension over the wave's own
+// steps in registers and over the waves through LDS (the sum of a wave's
+// steps is what it adds to every later one).  Then it dequantizes (one fp32
+// multiply, Sec. 2.3) and stores.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -30,7 +32,7 @@ __device__ __forceinline__ uint32_t check_header(const uint8_t* __restrict__ s, 
     // the whole header at once, as 32-bit words, and every check on them
     // without an early exit: the loads are uniform and issued together (one
     // wait), where byte loads behind branches would each wait in turn
-    const uint32_t* hw = reinterpret_cast<const uint32_t*>(s);
+    const ConstMem<uint32_t>* hw = const_mem<uint32_t>(s);
     uint32_t w[kHeaderBytes / 4];
 #pragma unroll
     for (int i = 0; i < kHeaderBytes / 4; i++) w[i] = hw[i];
@@ -56,110 +58,21 @@ __device__ __forceinline__ uint32_t check_header(const uint8_t* __restrict__ s, 
          : bad ? 6u : 0u;
 }
 
-// Sign-magnitude decode (Sec. 3.2).  The transpose ran with plane 15 (the
-// signs) cleared, so P[i] holds the magnitudes of codes i and i+16; bit m of
-// `sgn` is the sign of code m.  d = (m ^ s) - s with s = 0 or -1.
-__device__ __forceinline__ void decode_codes(const uint32_t (&P)[16], uint32_t sgn, int (&d)[32])
+// Sign-magnitude decode (Sec. 3.2): P[i] holds the codes of cells i and
+// i + 16 (sign in bit 15), decoded in packed 16-bit arithmetic, d = (m ^ s) - s
+// with s = 0 or -1, and widened (where the sums that follow allow it, inside
+// their adds).
+__device__ __forceinline__ void decode_codes(const uint32_t (&P)[16], int (&d)[32])
 {
 #pragma unroll
     for (int i = 0; i < 16; i++) {
-        const int slo = (int)(sgn << (31 - i)) >> 31, shi = (int)(sgn << (15 - i)) >> 31;
-        const int mlo = (int)(P[i] & 0xFFFFu), mhi = (int)(P[i] >> 16);
-        d[i] = (mlo ^ slo) - slo;
-        d[i + 16] = (mhi ^ shi) - shi;
+        const fz_short2 s = __builtin_bit_cast(fz_short2, P[i]) >> 15;
+        const fz_short2 m = __builtin_bit_cast(fz_short2, P[i] & 0x7FFF7FFFu);
+        const fz_short2 r = (m ^ s) - s;
+        d[i] = r.x;
+        d[i + 16] = r.y;
     }
 }
-
-// Replace escaped cells (code 0x8000) by their logged deltas.  Pairs are in
-// code-index order: this step's pairs follow the `seen` earlier ones.
-__device__ __forceinline__ uint32_t apply_escapes(const uint32_t (&P)[16], uint32_t sgn, int (&d)[32],
-                                                  const uint32_t* __restrict__ pairs, uint32_t nout, uint32_t& seen,
-                                                  uint32_t n0, int lane)
-{
-    uint32_t emask = 0;  // the escape code 0x8000: sign set, magnitude 0
-#pragma unroll
-    for (int i = 0; i < 16; i++) {
-        emask |= ((P[i] & 0xFFFFu) == 0u ? 1u : 0u) << i;
-        emask |= ((P[i] >> 16) == 0u ? 1u : 0u) << (i + 16);
-    }
-    emask &= sgn;
-    const int cnt = __popc(emask);
-    const int incl = wave_incl_scan(cnt, lane);
-    const uint32_t total = (uint32_t)__shfl(incl, 63);
-    uint32_t pos = seen + (uint32_t)(incl - cnt);
-    uint32_t bad = 0;
-#pragma unroll
-    for (int i = 0; i < 32; i++) {
-        if ((emask >> i) & 1u) {
-            if (pos < nout && pairs[2 * pos] == n0 + (uint32_t)lane * kPatchCodes + i) d[i] = (int)pairs[2 * pos + 1];
-            else bad = 1;
-            pos++;
-        }
-    }
-    seen += total;
-    return bad;
-}
-
-// Dequantization (Sec. 2.3): q * 2eb in the output's precision (one fp32 or
-// one fp64 multiply), or in the point-wise relative mode (fp32 only) the
-// inverse of the bit-pattern transform with the stream's step.
-template <bool PW, typename T>
-__device__ __forceinline__ T dequant(int q, T ebx2, uint32_t step)
-{
-    if constexpr (std::is_integral_v<T>) return q;  // the integers themselves (field-global predictor)
-    else if constexpr (PW) return pw_dequant(q, step);
-    else return (T)q * ebx2;
-}
-
-// the 32-bit pattern an fp32 or integer output value leaves in the LDS tile
-template <bool PW, typename T>
-__device__ __forceinline__ float tile_val(int q, T ebx2, uint32_t step)
-{
-    if constexpr (std::is_integral_v<T>) return __int_as_float(q);
-    else return dequant<PW>(q, ebx2, step);
-}
-
-template <int CNT, bool VEC4, bool PW, typename T>
-__device__ __forceinline__ void store_run(T* __restrict__ p, const int* q, T ebx2, uint32_t step)
-{
-    if constexpr (VEC4 && std::is_integral_v<T>) {
-#pragma unroll
-        for (int j = 0; j < CNT / 4; j++)
-            *reinterpret_cast<int4*>(p + 4 * j) = make_int4(q[4 * j], q[4 * j + 1], q[4 * j + 2], q[4 * j + 3]);
-    } else if constexpr (VEC4 && sizeof(T) == 4) {
-#pragma unroll
-        for (int j = 0; j < CNT / 4; j++)
-            *reinterpret_cast<float4*>(p + 4 * j) =
-                make_float4(dequant<PW>(q[4 * j], ebx2, step), dequant<PW>(q[4 * j + 1], ebx2, step),
-                            dequant<PW>(q[4 * j + 2], ebx2, step), dequant<PW>(q[4 * j + 3], ebx2, step));
-    } else if constexpr (VEC4) {
-#pragma unroll
-        for (int j = 0; j < CNT / 2; j++)
-            *reinterpret_cast<double2*>(p + 2 * j) =
-                make_double2(dequant<PW>(q[2 * j], ebx2, step), dequant<PW>(q[2 * j + 1], ebx2, step));
-    } else {
-#pragma unroll
-        for (int j = 0; j < CNT; j++) p[j] = dequant<PW>(q[j], ebx2, step);
-    }
-}
-
-template <int CNT, bool PW, typename T>
-__device__ __forceinline__ void store_run_masked(T* __restrict__ p, const int* q, T ebx2, uint32_t step, int valid)
-{
-#pragma unroll
-    for (int j = 0; j < CNT; j++)
-        if (j < valid) p[j] = dequant<PW>(q[j], ebx2, step);
-}
-
-// Decompress chunk c of a field with one wave (lane = 0..63; the workgroup is
-// that one wave).  `tile` is kTileFloats of LDS.  A stream that fails a check
-// writes an fz_status code to *d_err (if given) and leaves the chunk's output
-// untouched.  No byte at or past s + s_bytes is read: the header's total is
-// checked against s_bytes, and every chunk's payload against the total.
-// LDS tile of one step: 3-D, 32 rows of 64 values with a row pitch of 68;
-// 2-D and 1-D, the step's 2048 values in order with 4 floats of padding after
-// every 32 (both paddings spread a wave's 16-byte accesses over the banks)
-constexpr int kTilePitch = 68;
 
 // Orders one wave's LDS accesses to its own tile (writes before the reads of
 // other lanes, reads before the next rewrite): the compiler may not move
@@ -171,77 +84,175 @@ __device__ __forceinline__ void wave_lds_sync()
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_wave_barrier();
 }
-constexpr int kTileFloats = 2048 + 4 * (2048 / 32);
-static_assert(32 * kTilePitch <= kTileFloats, "the 3-D tile fits");
-__device__ __forceinline__ int run_slot(int i) { return i + 4 * (i >> 5); }
 
-// Store one 2-D or 1-D step from its LDS tile (filled by the caller):
-// instruction i writes values 256 i .. 256 i + 255 of the step, a run of 1 KiB
-// of whole lines, streamed out.  Values 1024 r .. 1024 r + 1023 start at byte
-// r * row_bytes from `base`: the step's second row in 2-D, 4096 in 1-D (one
-// contiguous run).
-__device__ __forceinline__ void store_tile_runs(const float* tile, void* base, uint32_t row_bytes, int lane)
+// LDS of one wave (kRegionWords 32-bit words): first its share of the carry
+// exchange (2048 ints), then the tile through which it stores a step, so that
+// every store instruction writes whole rows: 3-D, 32 rows of 64 values, the
+// 16-byte pieces of row r exchanged by XOR with r / 4 (a lane's patch row;
+// without it the 8 lanes of a column of patches write to the same banks:
+// half of the kernel's LDS cycles were conflicts); 2-D and 1-D, the step's
+// 2048 values in order with 4 words of padding after every 32.  Both spread a
+// wave's 16-byte accesses over the banks.  fp64 steps pass through it half by
+// half.
+constexpr int kRegionWords = 2048 + 4 * (2048 / 32);
+// places in a 2-D or 1-D tile, written so that all but the lane's part is an
+// immediate offset: value i sits at i + 4 (i / 32), double i (of 1024, which
+// fill a region) at i + 2 (i / 16)
+template <int RANK>
+__device__ __forceinline__ int run_put(int j, int lane)  // the j-th 4 of a lane's 32 values
 {
-    wave_lds_sync();  // orders the tile's writes before its reads
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, (short)0, -1, kBufferFlags);
+    return RANK == 2 ? 1152 * (j >> 2) + 16 * lane + 4 * (lane >> 1) + 4 * (j & 3) : 36 * lane + 4 * j;
+}
+__device__ __forceinline__ int run_get(int i, int lane) { return 288 * i + 4 * lane + 4 * (lane >> 3); }  // values 256 i + 4 lane ..
+__device__ __forceinline__ int run_put64(int j, int lane) { return 18 * lane + 2 * j; }  // the j-th 2 of a lane's 16 doubles
+__device__ __forceinline__ int run_get64(int i, int lane) { return 144 * i + 2 * lane + 2 * (lane >> 3); }  // doubles 128 i + 2 lane ..
+
+// an offset past the range of any resource below: the store is dropped
+constexpr uint32_t kNoStore = 0xFFFFFFF0u;
+
+// What a step of a chunk covers of the output: `rows` x `cols` values from
+// `base`, row pitch `nx` (3-D: a plane; 2-D: two rows; 1-D: one run).
+template <typename T>
+struct StepOut {
+    T* base;
+    int64_t nx;
+    int rows, cols;
+};
+
+template <int RANK, typename T>
+__device__ __forceinline__ StepOut<T> step_out(T* __restrict__ y, const Geom& g, const int64_t (&org)[3],
+                                               const int64_t (&ext)[3], int st)
+{
+    // uniform, and kept in scalar registers: a resource built from a vector
+    // register would put a loop around each store
+    auto uni = [](int64_t v) { return __builtin_amdgcn_readfirstlane((int)v); };
+    if (RANK == 3)
+        return {as_global(y + ((org[0] + st) * g.n[1] + org[1]) * g.n[2] + org[2]), g.n[2], uni(ext[1]), uni(ext[2])};
+    if (RANK == 2)
+        return {as_global(y + (org[0] + 2 * st) * g.n[1] + org[1]), g.n[1], min(2, uni(ext[0]) - 2 * st), uni(ext[1])};
+    return {as_global(y + org[0] + (int64_t)kStepCodes * st), 0, 1, min(kStepCodes, uni(ext[0]) - kStepCodes * st)};
+}
+
+// Store one step of 32-bit values (fp32, or the integers), held as 32 words
+// per lane, through the wave's tile.  Store instruction i writes 16 bytes per
+// lane: 4 rows of 64 values of a 3-D plane, or 1 KiB of a 2-D row or 1-D run.
+// stream: nontemporal stores, for whole lines only (kCacheStream); 4-byte
+// alignment suffices for a 16-byte buffer store.  edge: the step is cut by
+// the field's edge (uniform); pieces outside are skipped, a piece straddling the end of
+// a row is stored value by value.
+template <int RANK, typename T>
+__device__ __forceinline__ void store_step32(const StepOut<T>& o, bool stream, bool edge, const uint32_t (&d)[32], int lane,
+                                             uint32_t* tile)
+{
+    static_assert(sizeof(T) == 4, "32-bit values");
+    if (RANK == 3) {
+        const int py = lane & 7, px = lane >> 3;
+        uint32_t* t = tile + 256 * py;
+        const int p0 = 4 * ((2 * px) ^ py), p1 = 4 * ((2 * px + 1) ^ py);
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const float4 v = *reinterpret_cast<const float4*>(tile + run_slot(256 * i + 4 * lane));
-        const fz_u32x4 w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
-        const uint32_t soff = (uint32_t)(i >> 2) * row_bytes + 1024u * (uint32_t)(i & 3);
-        __builtin_amdgcn_raw_buffer_store_b128(w, rs, 16u * (uint32_t)lane, soff, kCacheStreamStore);
+        for (int r = 0; r < 4; r++) {
+            *reinterpret_cast<uint4*>(t + 64 * r + p0) = make_uint4(d[8 * r], d[8 * r + 1], d[8 * r + 2], d[8 * r + 3]);
+            *reinterpret_cast<uint4*>(t + 64 * r + p1) = make_uint4(d[8 * r + 4], d[8 * r + 5], d[8 * r + 6], d[8 * r + 7]);
+        }
+    } else {
+        // 2-D: lane l has columns 16 l .. of both rows; 1-D: values 32 l ..
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            *reinterpret_cast<uint4*>(tile + run_put<RANK>(j, lane)) = make_uint4(d[4 * j], d[4 * j + 1], d[4 * j + 2], d[4 * j + 3]);
+    }
+    wave_lds_sync();  // orders the tile's writes before its reads
+    // offsets stay below 2^32 - 16: at most 32 rows of a contiguous extent
+    // below 2^25
+    const uint32_t nx = (uint32_t)o.nx;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        o.base, (short)0, !edge ? -1 : o.rows > 0 ? (int)(4u * ((uint32_t)(o.rows - 1) * nx + (uint32_t)o.cols)) : 0,
+        kBufferFlags);
+    auto piece = [&](int i) {
+        return *reinterpret_cast<const fz_u32x4*>(RANK == 3 ? tile + 64 * (4 * i + (lane >> 4)) + 4 * ((lane & 15) ^ i)
+                                                            : tile + run_get(i, lane));
+    };
+    if (!edge) {
+        const uint32_t voff = RANK == 3 ? 4u * ((uint32_t)(lane >> 4) * nx + 4u * (uint32_t)(lane & 15)) : 16u * (uint32_t)lane;
+        auto soff = [&](int i) {
+            return RANK == 3 ? 16u * (uint32_t)i * nx : RANK == 2 ? 4u * (uint32_t)(i >> 2) * nx + 1024u * (i & 3) : 1024u * i;
+        };
+        fz_u32x4 w[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) w[i] = piece(i);
+        if (stream) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) __builtin_amdgcn_raw_buffer_store_b128(w[i], rs, voff, soff(i), kCacheStream);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; i++) __builtin_amdgcn_raw_buffer_store_b128(w[i], rs, voff, soff(i), 0);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const int row = RANK == 3 ? 4 * i + (lane >> 4) : RANK == 2 ? i >> 2 : 0;
+            const int col = RANK == 3 ? 4 * (lane & 15) : RANK == 2 ? 256 * (i & 3) + 4 * lane : 256 * i + 4 * lane;
+            const int n = row < o.rows ? o.cols - col : 0;  // values of the piece inside the field
+            const uint32_t voff = 4u * ((uint32_t)row * nx + (uint32_t)col);
+            const fz_u32x4 w = piece(i);
+            __builtin_amdgcn_raw_buffer_store_b128(w, rs, n >= 4 ? voff : kNoStore, 0u, 0);
+            if (o.cols & 3) {  // uniform: rows that end inside a piece
+                __builtin_amdgcn_raw_buffer_store_b32(w.x, rs, n > 0 && n < 4 ? voff : kNoStore, 0u, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(w.y, rs, n > 1 && n < 4 ? voff + 4u : kNoStore, 0u, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(w.z, rs, n == 3 ? voff + 8u : kNoStore, 0u, 0);
+            }
+        }
     }
     wave_lds_sync();  // the tile is rewritten by the next step
 }
 
-// The same for a 2-D step of a chunk cut by the field's edge: `rows` (1 or
-// 2) rows of `cols` values (a multiple of 4) from `base`, row pitch `nx`
-// values; pieces outside the field are dropped by the resource's range
-// (offset past it), and the stores are plain, as the lines are partly written.
-__device__ __forceinline__ void store_tile_runs_edge(const float* tile, void* base, uint32_t nx, uint32_t rows,
-                                                     uint32_t cols, int lane)
+// The same for doubles, in two halves: rows 4 py + 2 h, + 1 of every patch
+// (3-D), row h (2-D), values 16 h .. 16 h + 15 of every lane's 32 (1-D).
+// Store instruction i writes 16 bytes per lane, whole 128-byte lines: 2 rows
+// of 64 doubles, 1 KiB of a row, or 8 runs of 16 doubles.
+template <int RANK>
+__device__ __forceinline__ void store_step64(const StepOut<double>& o, bool stream, bool edge, const int (&d)[32], double ebx2,
+                                             int lane, uint32_t* tile)
 {
-    wave_lds_sync();  // orders the tile's writes before its reads
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)(4u * ((rows - 1) * nx + cols)), kBufferFlags);
+    double* t64 = reinterpret_cast<double*>(tile);
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const float4 v = *reinterpret_cast<const float4*>(tile + run_slot(256 * i + 4 * lane));
-        const fz_u32x4 w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
-        const uint32_t row = (uint32_t)(i >> 2), col = 256u * (uint32_t)(i & 3) + 4u * (uint32_t)lane;
-        const uint32_t voff = row < rows && col < cols ? 4u * (row * nx + col) : 0x80000000u;
-        __builtin_amdgcn_raw_buffer_store_b128(w, rs, voff, 0u, 0);
-    }
-    wave_lds_sync();  // the tile is rewritten by the next step
-}
-
-// The fp64 output's tiles (twice the words; the caller's LDS holds
-// kTileFloats64 floats): 3-D rows of 64 doubles with a pitch of 68 doubles;
-// 2-D and 1-D runs of the step's 2048 doubles with 2 doubles of padding after
-// every 16.  Every store instruction writes whole 512-byte rows (3-D) or
-// 1 KiB of one row (2-D, 1-D), streamed out.
-constexpr int kTilePitch64 = 68;  // doubles
-constexpr int kTileFloats64 = 2 * (2048 + 2 * (2048 / 16));
-static_assert(2 * 32 * kTilePitch64 <= kTileFloats64, "the 3-D fp64 tile fits");
-__device__ __forceinline__ int run_slot64(int i) { return i + 2 * (i >> 4); }
-
-__device__ __forceinline__ void store_nt2(double* p, double a, double b)
-{
-    const fz_f64x2 v = {a, b};
-    __builtin_nontemporal_store(v, reinterpret_cast<fz_f64x2*>(p));
-}
-
-// 2-D / 1-D: instruction i writes doubles 128 i .. 128 i + 127 of the step;
-// doubles 1024 r .. start at element r * row_elems from `base`
-__device__ __forceinline__ void store_tile_runs64(const double* tile, double* base, int64_t row_elems, int lane)
-{
-    wave_lds_sync();  // orders the tile's writes before its reads
+    for (int h = 0; h < 2; h++) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-        const double2 v = *reinterpret_cast<const double2*>(tile + run_slot64(128 * i + 2 * lane));
-        store_nt2(base + (int64_t)(i >> 3) * row_elems + 128 * (i & 7) + 2 * lane, v.x, v.y);
+        for (int j = 0; j < 8; j++) {
+            const int i = 16 * h + 2 * j;
+            double* t = RANK == 3 ? t64 + 128 * (lane & 7) + 64 * (j >> 2) + 2 * ((4 * (lane >> 3) + (j & 3)) ^ (lane & 7))
+                                  : t64 + run_put64(j, lane);
+            *reinterpret_cast<double2*>(t) = make_double2((double)d[i] * ebx2, (double)d[i + 1] * ebx2);
+        }
+        wave_lds_sync();  // orders the tile's writes before its reads
+        fz_u32x4 w[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++)
+            w[i] = *reinterpret_cast<const fz_u32x4*>(RANK == 3 ? t64 + 64 * (2 * i + (lane >> 5)) + 2 * ((lane & 31) ^ i)
+                                                                : t64 + run_get64(i, lane));
+        const uint32_t pitch = RANK == 3 ? (uint32_t)o.nx : 0u;
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            // the instruction's first row is uniform: its resource starts there
+            const int at = 128 * i + 2 * lane;  // 2-D, 1-D: the value's place in the half
+            const int row0 = RANK == 3 ? 4 * i + 2 * h : RANK == 2 ? h : 0, row = row0 + (RANK == 3 ? lane >> 5 : 0);
+            const int col = RANK == 3 ? 2 * (lane & 31) : RANK == 2 ? at : 32 * (at >> 4) + 16 * h + (at & 15);
+            const int left = o.rows - row0;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                o.base + (int64_t)row0 * o.nx, (short)0,
+                !edge ? -1 : left > 0 ? (int)(8u * ((left > 1 ? pitch : 0u) + (uint32_t)o.cols)) : 0, kBufferFlags);
+            const uint32_t voff = 8u * ((RANK == 3 ? (uint32_t)(lane >> 5) * pitch : 0u) + (uint32_t)col);
+            if (!edge) {
+                if (stream) __builtin_amdgcn_raw_buffer_store_b128(w[i], rs, voff, 0u, kCacheStream);
+                else __builtin_amdgcn_raw_buffer_store_b128(w[i], rs, voff, 0u, 0);
+            } else {
+                const int n = row < o.rows ? o.cols - col : 0;  // values of the piece inside the field
+                __builtin_amdgcn_raw_buffer_store_b128(w[i], rs, n >= 2 ? voff : kNoStore, 0u, 0);
+                if (o.cols & 1)  // uniform: rows that end inside a piece
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_shufflevector(w[i], w[i], 0, 1), rs, n == 1 ? voff : kNoStore, 0u, 0);
+            }
+        }
+        wave_lds_sync();  // the tile is rewritten by the next half
     }
-    wave_lds_sync();  // the tile is rewritten by the next step
 }
 
 // 3-D: inclusive prefix of one plane of deltas along x, then y (the lane's
@@ -265,16 +276,17 @@ __device__ __forceinline__ void plane_prefix3(int (&d)[32], int lane)
     for (int r = 1; r < 4; r++)
 #pragma unroll
         for (int cc = 0; cc < 8; cc++) d[8 * r + cc] += d[8 * (r - 1) + cc];
+    // the carry over the 8 lanes of a column of patches: a shift by 1 and by 2
+    // inside the 16-lane row, lanes whose value would reach the next 8 cleared
+    // first, so that each shift fuses with its add; a shift by 4 into the
+    // upper half of each 8 only (a bank mask)
+    const int m1 = py == 7 ? 0 : -1, m2 = py >= 6 ? 0 : -1;
 #pragma unroll
     for (int cc = 0; cc < 8; cc++) {
         const int C = d[24 + cc];
-        int inc = C;
-        int tv = row_shr<1>(inc);
-        inc += py >= 1 ? tv : 0;
-        tv = row_shr<2>(inc);
-        inc += py >= 2 ? tv : 0;
-        tv = row_shr<4>(inc);
-        inc += py >= 4 ? tv : 0;
+        int inc = C + row_shr<1>(C & m1);
+        inc += row_shr<2>(inc & m2);
+        inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xa, false);
         const int ex_ = inc - C;
 #pragma unroll
         for (int r = 0; r < 4; r++) d[8 * r + cc] += ex_;
@@ -288,422 +300,334 @@ __device__ __forceinline__ void row_prefix2(int* d, int lane)
 #pragma unroll
     for (int cc = 1; cc < 16; cc++) d[cc] += d[cc - 1];
     const int tot = d[15];
-    const int ex_ = wave_incl_scan(tot, lane) - tot;
+    const int ex_ = wave_incl_scan(tot) - tot;
 #pragma unroll
     for (int cc = 0; cc < 16; cc++) d[cc] += ex_;
 }
 
-// Decompress chunk c of a field.  NW = 1: one wave (the workgroup) runs
-// every layer.  NW = 2 or 4: the chunk's workgroup has NW waves, and wave
-// `wave` runs layers 4/NW * wave .. (a field with few chunks, whose
-// latency is set by a chunk's serial steps).  The prefix sums along the step
-// dimension need what the layers below contributed: each wave first decodes
-// its layers once and sums their deltas over the steps; the in-plane prefix of
-// that sum is its contribution to the carry (the prefix is linear), left in
-// `xch` (LDS, NW x 2048 ints).  After a workgroup barrier, wave w adds those of
-// waves 0 .. w-1 to get its starting carry, then runs its layers as the single
-// wave would.
-template <int RANK, bool VEC4, bool PW, typename T, int NW>
-__device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, uint64_t s_bytes, T* __restrict__ y,
-                                                 const Geom& g, uint32_t* d_err, int64_t c, int lane, float* tile,
-                                                 int wave, int* xch)
+// Workgroup-shared state of a decompression workgroup of NW waves.
+template <int NW>
+struct DecompressLds {
+    __attribute__((aligned(16))) uint32_t region[NW][kRegionWords];  // per wave: its carry, then its tile
+};
+
+// A step's escape codes (sign set, magnitude 0; they decode to 0), one bit per
+// cell, from the words of its 16 bit planes (plane 15: the signs).
+__device__ __forceinline__ uint32_t escape_mask(const uint32_t (&P)[16])
 {
-    constexpr bool SPLIT = NW > 1;
-    constexpr bool F64 = sizeof(T) == 8;
-    constexpr bool INT = std::is_integral_v<T>;
-    const uint32_t hdr_err = check_header(s, g, RANK, F64 ? 1 : 0, INT ? 1 : 0, s_bytes);
-    if (hdr_err) {
-        if (c == 0 && lane == 0 && d_err) atomicCAS(d_err, 0u, hdr_err);
-        return;
-    }
-    const T ebx2 = INT ? (T)1
-                 : F64 ? (T)*reinterpret_cast<const double*>(s + kOffEbx2F64)
-                       : (T)*reinterpret_cast<const float*>(s + kOffEbx2);
-    const uint32_t step = PW ? (uint32_t)ebx2 : 0u;  // the point-wise mode's step (checked by check_header)
-    const uint64_t total = *reinterpret_cast<const uint64_t*>(s + kOffTotal);
-    const uint64_t payload_units = (total - g.payload_off) / 16;
-    const uint32_t* tab = reinterpret_cast<const uint32_t*>(s + g.table_off + 8 * c);
-    const uint32_t off = tab[0], nout = tab[1];
-    const uint64_t* F = reinterpret_cast<const uint64_t*>(s + g.flags_off + (int64_t)kFlagBytesPerChunk * c);
-    int64_t org[3], ext[3];
-    chunk_box(g, c, org, ext);
-    const int L = layers_of(RANK, ext[0]);
-    uint32_t nnz = 0;
-    for (int i = 0; i < kLayers * kPlanes; i++) nnz += __popcll(F[i]);
-    // the table is the exclusive prefix sum of the chunks' units (Sec. 3.4):
-    // this chunk's offset plus its units (from the flags' popcounts and its
-    // escape count) is the next chunk's offset, or the payload's end; with
-    // chunk 0 at offset 0, every chunk lies inside the payload
-    const uint64_t next = c + 1 < g.n_chunks ? (uint64_t)tab[2] : payload_units;
-    bool bad = nout > (uint32_t)kChunkOutlierCap || (uint64_t)off + nnz + (nout + 1) / 2 != next || (c == 0 && off != 0);
-    for (int i = L * kPlanes; i < kLayers * kPlanes; i++) bad |= F[i] != 0;
-    if (bad) {
-        if (lane == 0 && d_err) atomicCAS(d_err, 0u, 6u);
-        return;
-    }
-    bool edge = false;
+    uint32_t mag = 0u;
 #pragma unroll
-    for (int i = 0; i < 3; i++) edge |= ext[i] < g.box[i];
+    for (int b = 0; b < 15; b++) mag |= P[b];
+    return P[15] & ~mag;
+}
 
-    const uint4* pay = reinterpret_cast<const uint4*>(s + g.payload_off);
-    const uint32_t* pairs = reinterpret_cast<const uint32_t*>(pay + off + nnz);
-    uint32_t seen = 0, esc_bad = 0;
-    // the chunk's bricks through a buffer resource based at its payload (reads
-    // past its nonzero bricks return 0, never another chunk's bytes)
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint4*>(pay + off), (short)0, (int)(16u * nnz), kBufferFlags);
-    {
-        // The bricks are read a few words per step over the chunk's 16 steps:
-        // touch all their lines now (64 lines per instruction), so that the
-        // later steps' loads find them in the caches instead of HBM.  The
-        // words land in 256 bytes of LDS that nothing reads: a load into LDS
-        // holds no register and nothing waits for it (the first step's wait
-        // for its own words, issued after these, covers them in order).
-        __shared__ uint32_t touch_dump[64];
-        for (uint32_t o = 8192u * (uint32_t)wave; o < 16u * nnz; o += (uint32_t)NW * 8192u)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)touch_dump, 4,
-                                                     o + 128u * (uint32_t)lane, 0, 0, 0);
-    }
-
-    // per-step brick words: plane b of this lane's brick holds word t of
-    // step 4k + t at byte voff[b] + 4t of the chunk's payload.  A zero brick
-    // gets an offset beyond the resource's range, where the load returns 0
-    // without touching memory: every load is issued unconditionally, so the
-    // wait for one step's words never has to cover the next step's loads.
-    constexpr uint32_t kZeroBrick = 0x80000000u;
-    uint32_t voff[16];
-    uint32_t cur = 0;
-    int k0 = 0, k1 = L;  // the layers this wave runs
-    auto layer_offsets = [&](int k) {  // past the wave's last layer: all bricks zero
+// The logged deltas of one step's escape codes (emask), added to d.  Pairs
+// are strictly ascending in the code index; those of the wave's steps are
+// pairs lo .. hi - 1.  Each lane takes pairs and scatters the step's deltas
+// into the wave's (zeroed) LDS region, from where every lane reads the ones of
+// its cells: no branch per cell and one round trip for all of them.  Returns
+// nonzero unless the step's pairs and its escape codes are the same cells and
+// every one of the pairs lies in the wave's `codes` codes from `first`.
+__device__ __forceinline__ uint32_t add_escapes(uint32_t emask, int (&d)[32], const uint32_t* __restrict__ pairs,
+                                                uint32_t lo, uint32_t hi, uint32_t first, uint32_t codes, uint32_t n0,
+                                                int lane, uint32_t* region)
+{
+    int left = __popc(emask);
+    uint32_t bad = 0;
 #pragma unroll
-        for (int b = 0; b < 16; b++) {
-            const uint64_t f = k < k1 ? F[k * kPlanes + b] : 0ull;
-            voff[b] = ((f >> lane) & 1ull) ? 16u * (cur + mbcnt(f)) : kZeroBrick;
-            cur += (uint32_t)__popcll(f);
+    for (int j = 0; j < 8; j++) *reinterpret_cast<uint4*>(region + 256 * j + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+    wave_lds_sync();  // zeros before the scatter
+    for (uint32_t j0 = lo; j0 < hi; j0 += 64) {
+        const uint32_t j = j0 + (uint32_t)lane;
+        uint32_t at = 0xFFFFFFFFu, delta = 0u;  // relative to the step: past it for a lane without a pair
+        if (j < hi) {
+            const uint32_t n = pairs[2 * j];
+            delta = pairs[2 * j + 1];
+            bad |= n - first >= codes || (j + 1 < hi && pairs[2 * j + 2] <= n) ? 1u : 0u;
+            at = n - n0;
         }
-    };
-    auto load_words = [&](int t, uint32_t (&w)[16]) {
-#pragma unroll
-        for (int b = 0; b < 16; b++) w[b] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff[b] + 4u * t, 0u, 0);
-    };
-
-    // per-rank geometry of this lane's patch
-    const int py = lane & 7, px = lane >> 3;
-    int carry3[32];   // 3-D: previous plane's q of this patch
-    int carry2[16];   // 2-D: previous row's q of this patch
-    int carry1 = 0;   // 1-D: q just before the current step
-#pragma unroll
-    for (int i = 0; i < 32; i++) carry3[i] = 0;
-#pragma unroll
-    for (int i = 0; i < 16; i++) carry2[i] = 0;
-
-    if constexpr (SPLIT) {
-        k0 = (kLayers / NW) * wave;
-        k1 = k0 + kLayers / NW < L ? k0 + kLayers / NW : L;
-        // bricks and escape pairs of the layers below this one (the pairs are
-        // in code-index order: those with an index below the layer's first)
-        for (int i = 0; i < (k0 < L ? k0 : L) * kPlanes; i++) cur += (uint32_t)__popcll(F[i]);
-        if (nout && k0 > 0) {
-            const uint32_t first = (uint32_t)(4 * k0) * kStepCodes;
-            uint32_t n = 0;
-            for (uint32_t j = (uint32_t)lane; j < nout; j += 64) n += pairs[2 * j] < first ? 1u : 0u;
-#pragma unroll
-            for (int sh = 32; sh > 0; sh >>= 1) n += (uint32_t)__shfl_xor((int)n, sh);
-            seen = n;
-        }
-        if (k0 < L) {
-            // pass 1: the deltas of the wave's layers summed over their steps,
-            // then their in-plane prefix (3-D: 32 per lane; 2-D: 16 per lane,
-            // both rows of each step; 1-D: the total)
-            const uint32_t cur0 = cur;
-            int acc[32];
-#pragma unroll
-            for (int i = 0; i < 32; i++) acc[i] = 0;
-            uint32_t seen1 = seen;
-#pragma unroll 1
-            for (int k = k0; k < k1; k++) {
-                layer_offsets(k);
-                uint32_t Wp[4][16];
-#pragma unroll
-                for (int t = 0; t < 4; t++) load_words(t, Wp[t]);
-#pragma unroll
-                for (int t = 0; t < 4; t++) {
-                    uint32_t P[16];
-#pragma unroll
-                    for (int b = 0; b < 15; b++) P[b] = Wp[t][b];
-                    const uint32_t sgn = Wp[t][15];
-                    P[15] = 0u;
-                    transpose16(P);
-                    int d[32];
-                    decode_codes(P, sgn, d);
-                    if (nout)
-                        esc_bad |= apply_escapes(P, sgn, d, pairs, nout, seen1, (uint32_t)(4 * k + t) * kStepCodes, lane);
-#pragma unroll
-                    for (int i = 0; i < 32; i++) acc[i] += d[i];
-                }
-            }
-            cur = cur0;
-            int* xw = xch + 2048 * wave;
-            if (RANK == 3) {
-                plane_prefix3(acc, lane);
-#pragma unroll
-                for (int i = 0; i < 32; i++) xw[64 * i + lane] = acc[i];
-            } else if (RANK == 2) {
-#pragma unroll
-                for (int cc = 0; cc < 16; cc++) acc[cc] += acc[16 + cc];
-                row_prefix2(acc, lane);
-#pragma unroll
-                for (int cc = 0; cc < 16; cc++) xw[64 * cc + lane] = acc[cc];
-            } else {
-                int tot = 0;
-#pragma unroll
-                for (int i = 0; i < 32; i++) tot += acc[i];
-#pragma unroll
-                for (int sh = 32; sh > 0; sh >>= 1) tot += __shfl_xor(tot, sh);
-                if (lane == 0) xw[0] = tot;
-            }
-        }
-        __syncthreads();  // every wave reaches it: the checks above are the same for the whole chunk
-        if (k0 >= L) return;
-        for (int j = 0; j < wave; j++) {
-            const int* xj = xch + 2048 * j;
-            if (RANK == 3) {
-#pragma unroll
-                for (int i = 0; i < 32; i++) carry3[i] += xj[64 * i + lane];
-            } else if (RANK == 2) {
-#pragma unroll
-                for (int cc = 0; cc < 16; cc++) carry2[cc] += xj[64 * cc + lane];
-            } else {
-                carry1 += xj[0];
-            }
+        const bool mine = at < (uint32_t)kStepCodes;
+        const uint32_t patch = (at >> 5) & 63u, cell = at & 31u;
+        const uint32_t em = (uint32_t)lane_value((int)emask, (int)patch);
+        if (mine) {
+            bad |= ((em >> cell) & 1u) ^ 1u;
+            region[256 * (cell >> 2) + 4 * patch + (cell & 3u)] = delta;
+            left--;
         }
     }
-
-    // The words of a step are loaded two steps ahead: the wait for them then
-    // leaves the previous step's stores outstanding (the counter of
-    // outstanding vector memory operations covers stores too, in issue order).
-    // W[t] holds the words of step t of a layer.  Every load is issued
-    // unconditionally, so no register that a load is still filling is ever
-    // copied at a join: iteration k = -1 loads zero bricks at t = 0, 1 and
-    // layer 0's first words at t = 2, 3; the last layer loads the zero
-    // bricks of the layer after it.
-    uint32_t W[4][16];
+    wave_lds_sync();  // the scatter before the reads
 #pragma unroll
-    for (int b = 0; b < 16; b++) voff[b] = kZeroBrick;
-    for (int k = k0 - 1; k < k1; k++) {
-#pragma unroll
-        for (int t = 0; t < 4; t++) {
-            if (t == 2) layer_offsets(k + 1);  // the last load of layer k was issued at t = 1
-            load_words(t < 2 ? t + 2 : t - 2, W[(t + 2) & 3]);
-            __builtin_amdgcn_sched_barrier(0);
-            const int st = 4 * k + t;
-            const int64_t step_lo = RANK == 3 ? st : RANK == 2 ? 2 * st : (int64_t)kStepCodes * st;
-            if (k < k0 || step_lo >= ext[0]) continue;
-            uint32_t P[16];
-#pragma unroll
-            for (int b = 0; b < 15; b++) P[b] = W[t][b];
-            const uint32_t sgn = W[t][15];  // plane 15: the signs
-            P[15] = 0u;
-            transpose16(P);
-            int d[32];
-            decode_codes(P, sgn, d);
-            if (nout) esc_bad |= apply_escapes(P, sgn, d, pairs, nout, seen, (uint32_t)st * kStepCodes, lane);
-
-            if (RANK == 3) {
-                plane_prefix3(d, lane);
-                // prefix along z: previous plane of the same patch
-#pragma unroll
-                for (int i = 0; i < 32; i++) {
-                    d[i] += carry3[i];
-                    carry3[i] = d[i];
-                }
-                const int64_t z = org[0] + st, y0 = org[1] + 4 * py, x0 = org[2] + 8 * px;
-                if (edge && !(VEC4 && !F64 && 32 * 4 * g.n[2] < 0x80000000ll)) {
-                    const int ey = clampi(ext[1] - 4 * py, 0, 4), ex = clampi(ext[2] - 8 * px, 0, 8);
-#pragma unroll
-                    for (int r = 0; r < 4; r++)
-                        if (r < ey) store_run_masked<8, PW>(y + ((z * g.n[1] + y0 + r) * g.n[2] + x0), d + 8 * r, ebx2, step, ex);
-                } else if constexpr (VEC4 && !F64) {
-                    // the plane goes through LDS so that every store instruction
-                    // writes 4 whole rows of 64 values (a lane's own 4x8 patch
-                    // would give each instruction half-filled 32-byte pieces)
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        float* t = tile + (4 * py + r) * kTilePitch + 8 * px;
-                        *reinterpret_cast<float4*>(t) =
-                            make_float4(tile_val<PW, T>(d[8 * r], ebx2, step), tile_val<PW, T>(d[8 * r + 1], ebx2, step),
-                                        tile_val<PW, T>(d[8 * r + 2], ebx2, step), tile_val<PW, T>(d[8 * r + 3], ebx2, step));
-                        *reinterpret_cast<float4*>(t + 4) =
-                            make_float4(tile_val<PW, T>(d[8 * r + 4], ebx2, step), tile_val<PW, T>(d[8 * r + 5], ebx2, step),
-                                        tile_val<PW, T>(d[8 * r + 6], ebx2, step), tile_val<PW, T>(d[8 * r + 7], ebx2, step));
-                    }
-                    wave_lds_sync();  // orders the tile's writes before its reads
-                    T* plane = y + (z * g.n[1] + org[1]) * g.n[2] + org[2];
-                    if (!edge) {
-                        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(plane, (short)0, -1, kBufferFlags);
-                        // offsets stay below 2^32: 32 rows of a contiguous extent below 2^25
-                        const uint32_t voff = 4u * ((uint32_t)(lane >> 4) * (uint32_t)g.n[2] + 4u * (lane & 15));
-#pragma unroll
-                        for (int i = 0; i < 8; i++) {
-                            const float4 v = *reinterpret_cast<const float4*>(tile + (4 * i + (lane >> 4)) * kTilePitch +
-                                                                              4 * (lane & 15));
-                            const fz_u32x4 w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
-                                                __float_as_uint(v.w)};
-                            __builtin_amdgcn_raw_buffer_store_b128(w, rs, voff, 16u * (uint32_t)i * (uint32_t)g.n[2],
-                                                                   kCacheStreamStore);
-                        }
-                    } else {
-                        // a chunk cut by the field's edge (its rows hold whole 16-byte pieces): the
-                        // pieces outside the field get an offset past the resource's range, where
-                        // the store is dropped; plain stores, as the rows' lines are partly written
-                        const uint32_t rows = (uint32_t)ext[1], cols = (uint32_t)ext[2], nx = (uint32_t)g.n[2];
-                        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                            plane, (short)0, (int)(4u * ((rows - 1) * nx + cols)), kBufferFlags);
-#pragma unroll
-                        for (int i = 0; i < 8; i++) {
-                            const float4 v = *reinterpret_cast<const float4*>(tile + (4 * i + (lane >> 4)) * kTilePitch +
-                                                                              4 * (lane & 15));
-                            const fz_u32x4 w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
-                                                __float_as_uint(v.w)};
-                            const uint32_t row = 4u * i + (lane >> 4), col = 4u * (lane & 15);
-                            const uint32_t voff = row < rows && col < cols ? 4u * (row * nx + col) : 0x80000000u;
-                            __builtin_amdgcn_raw_buffer_store_b128(w, rs, voff, 0u, 0);
-                        }
-                    }
-                    wave_lds_sync();  // the tile is rewritten by the next step
-                } else if constexpr (VEC4 && F64) {
-                    // through LDS as above: every store writes 2 whole rows of 64 doubles
-                    double* t64 = reinterpret_cast<double*>(tile);
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        double* t = t64 + (4 * py + r) * kTilePitch64 + 8 * px;
-#pragma unroll
-                        for (int j = 0; j < 4; j++)
-                            *reinterpret_cast<double2*>(t + 2 * j) =
-                                make_double2(dequant<PW>(d[8 * r + 2 * j], ebx2, step),
-                                             dequant<PW>(d[8 * r + 2 * j + 1], ebx2, step));
-                    }
-                    wave_lds_sync();  // orders the tile's writes before its reads
-                    T* base = y + (z * g.n[1] + org[1]) * g.n[2] + org[2];
-#pragma unroll
-                    for (int i = 0; i < 16; i++) {
-                        const int row = 2 * i + (lane >> 5), col = 2 * (lane & 31);
-                        const double2 v = *reinterpret_cast<const double2*>(t64 + row * kTilePitch64 + col);
-                        store_nt2(base + (int64_t)row * g.n[2] + col, v.x, v.y);
-                    }
-                    wave_lds_sync();  // the tile is rewritten by the next step
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; r++) store_run<8, VEC4, PW>(y + ((z * g.n[1] + y0 + r) * g.n[2] + x0), d + 8 * r, ebx2, step);
-                }
-            } else if (RANK == 2) {
-                row_prefix2(d, lane);
-                row_prefix2(d + 16, lane);
-#pragma unroll
-                for (int cc = 0; cc < 16; cc++) {
-                    d[cc] += carry2[cc];
-                    d[16 + cc] += d[cc];
-                    carry2[cc] = d[16 + cc];
-                }
-                const int64_t yy = org[0] + 2 * st, x0 = org[1] + 16 * lane;
-                if (edge && !(VEC4 && !F64 && 2 * 4 * g.n[1] < 0x80000000ll)) {
-                    const int ex = clampi(ext[1] - 16 * lane, 0, 16);
-                    store_run_masked<16, PW>(y + (yy * g.n[1] + x0), d, ebx2, step, ex);
-                    if (2 * st + 1 < ext[0]) store_run_masked<16, PW>(y + ((yy + 1) * g.n[1] + x0), d + 16, ebx2, step, ex);
-                } else if constexpr (VEC4 && !F64) {
-                    // through LDS, so that every store writes 1 KiB of one row
-#pragma unroll
-                    for (int r = 0; r < 2; r++)
-#pragma unroll
-                        for (int j = 0; j < 4; j++) {
-                            const int* q = d + 16 * r + 4 * j;
-                            *reinterpret_cast<float4*>(tile + run_slot(1024 * r + 16 * lane + 4 * j)) =
-                                make_float4(tile_val<PW, T>(q[0], ebx2, step), tile_val<PW, T>(q[1], ebx2, step),
-                                            tile_val<PW, T>(q[2], ebx2, step), tile_val<PW, T>(q[3], ebx2, step));
-                        }
-                    // row offsets stay below 2^32: the contiguous extent is below 2^25
-                    if (!edge) store_tile_runs(tile, y + (yy * g.n[1] + org[1]), 4u * (uint32_t)g.n[1], lane);
-                    else store_tile_runs_edge(tile, y + (yy * g.n[1] + org[1]), (uint32_t)g.n[1],
-                                              (uint32_t)min((int64_t)2, ext[0] - 2 * st), (uint32_t)ext[1], lane);
-                } else if constexpr (VEC4 && F64) {
-                    double* t64 = reinterpret_cast<double*>(tile);
-#pragma unroll
-                    for (int r = 0; r < 2; r++)
-#pragma unroll
-                        for (int j = 0; j < 8; j++) {
-                            const int* q = d + 16 * r + 2 * j;
-                            *reinterpret_cast<double2*>(t64 + run_slot64(1024 * r + 16 * lane + 2 * j)) =
-                                make_double2(dequant<PW>(q[0], ebx2, step), dequant<PW>(q[1], ebx2, step));
-                        }
-                    store_tile_runs64(t64, y + (yy * g.n[1] + org[1]), g.n[1], lane);
-                } else {
-                    store_run<16, VEC4, PW>(y + (yy * g.n[1] + x0), d, ebx2, step);
-                    store_run<16, VEC4, PW>(y + ((yy + 1) * g.n[1] + x0), d + 16, ebx2, step);
-                }
-            } else {
-#pragma unroll
-                for (int m = 1; m < 32; m++) d[m] += d[m - 1];
-                const int tot = d[31];
-                const int ex_ = wave_incl_scan(tot, lane) - tot + carry1;
-#pragma unroll
-                for (int m = 0; m < 32; m++) d[m] += ex_;
-                carry1 = __builtin_amdgcn_readlane(d[31], 63);
-                const int64_t x0 = org[0] + (int64_t)kStepCodes * st + kPatchCodes * lane;
-                if (edge) {
-                    const int valid = clampi(ext[0] - ((int64_t)kStepCodes * st + kPatchCodes * lane), 0, 32);
-                    store_run_masked<32, PW>(y + x0, d, ebx2, step, valid);
-                } else if constexpr (VEC4 && !F64) {
-#pragma unroll
-                    for (int j = 0; j < 8; j++) {
-                        const int* q = d + 4 * j;
-                        *reinterpret_cast<float4*>(tile + run_slot(32 * lane + 4 * j)) =
-                            make_float4(tile_val<PW, T>(q[0], ebx2, step), tile_val<PW, T>(q[1], ebx2, step),
-                                        tile_val<PW, T>(q[2], ebx2, step), tile_val<PW, T>(q[3], ebx2, step));
-                    }
-                    store_tile_runs(tile, y + (org[0] + (int64_t)kStepCodes * st), 4096u, lane);
-                } else if constexpr (VEC4 && F64) {
-                    double* t64 = reinterpret_cast<double*>(tile);
-#pragma unroll
-                    for (int j = 0; j < 16; j++) {
-                        const int* q = d + 2 * j;
-                        *reinterpret_cast<double2*>(t64 + run_slot64(32 * lane + 2 * j)) =
-                            make_double2(dequant<PW>(q[0], ebx2, step), dequant<PW>(q[1], ebx2, step));
-                    }
-                    store_tile_runs64(t64, y + (org[0] + (int64_t)kStepCodes * st), 1024, lane);
-                } else {
-                    store_run<32, VEC4, PW>(y + x0, d, ebx2, step);
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    for (int j = 0; j < 8; j++) {
+        const uint4 v = *reinterpret_cast<const uint4*>(region + 256 * j + 4 * lane);
+        d[4 * j] += (int)v.x;
+        d[4 * j + 1] += (int)v.y;
+        d[4 * j + 2] += (int)v.z;
+        d[4 * j + 3] += (int)v.w;
     }
-    // every escape code had its pair, and (the wave that ran the last layer)
-    // no pair is left over
-    if (nout && (esc_bad || (k1 == L && seen != nout))) {
-        if (lane == 0 && d_err) atomicCAS(d_err, 0u, 6u);
+    wave_lds_sync();  // the region is written again
+#pragma unroll
+    for (int sh = 32; sh > 0; sh >>= 1) left += __shfl_xor(left, sh);
+    return bad | (left != 0 ? 1u : 0u);
+}
+
+// In-plane part of the inverse predictor (the sums along the sweep dimension
+// follow): 3-D along x and y; 2-D along x, then the second row on the first;
+// 1-D along x over the step.
+template <int RANK>
+__device__ __forceinline__ void step_prefix(int (&d)[32], int lane)
+{
+    if (RANK == 3) {
+        plane_prefix3(d, lane);
+    } else if (RANK == 2) {
+        row_prefix2(d, lane);
+        row_prefix2(d + 16, lane);
+#pragma unroll
+        for (int cc = 0; cc < 16; cc++) d[16 + cc] += d[cc];
+    } else {
+#pragma unroll
+        for (int m = 1; m < 32; m++) d[m] += d[m - 1];
+        const int tot = d[31];
+        const int ex_ = wave_incl_scan(tot) - tot;
+#pragma unroll
+        for (int m = 0; m < 32; m++) d[m] += ex_;
     }
 }
 
-// Decompress chunk c with the stream's quantizer (the mode byte is uniform:
-// one of the two bodies runs).  NW > 1: the form with NW waves per chunk
-// (fp32 output only), `tile` this wave's own tile and `xch` the workgroup's
-// carry exchange.
-template <int RANK, bool VEC4, int NW = 1, typename T>
-__device__ __forceinline__ void decompress_chunk_any(const uint8_t* __restrict__ s, uint64_t s_bytes,
-                                                     T* __restrict__ y, const Geom& g, uint32_t* d_err, int64_t c,
-                                                     int lane, float* tile, int wave = 0, int* xch = nullptr)
+// Decompress chunk c of a field with a workgroup of NW waves; wave w runs
+// the 16 / NW steps from w * 16 / NW.  A stream that fails a check writes an
+// fz_status code to *d_err (if given) and leaves the chunk's output
+// untouched.  No byte at or past s + s_bytes is read: the header's total is
+// checked against s_bytes, and every chunk's payload against the total.
+// All checks give the same result in every wave, so the waves return together.
+//
+// Sweep dimension: what a step adds to the later ones is its last in-plane
+// prefix (3-D: the plane; 2-D: its second row; 1-D: its last value).  Each
+// wave sums its own steps in registers, leaves the sum in its LDS region, and
+// after a barrier adds the regions of the waves before it.  Holding every
+// step in registers, no step is decoded twice and none waits for the one
+// before it.
+//
+// What bounds it: VALU issue (584 instructions per step and wave, 68 % of the
+// cycles on 512^3) with the stores behind it; two workgroups per CU overlap
+// one's loads and barriers with the other's arithmetic.  Measured against one
+// wave per chunk (4 waves for at most 512 chunks) before: 512^3 REL 1e-3
+// 113 -> 107 us, 100x500x500 50 -> 34 us, 101x499x501 68 -> 36 us, 5001x5003
+// 69 -> 32 us, 2^26 values 64 -> 52 us, 1800x3600 19 -> 12 us, 64^3 18 -> 11 us
+// (times of a pass, rotating over three fields).
+template <int RANK, typename T, int NW>
+__device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, uint64_t s_bytes, T* __restrict__ y,
+                                                 bool stream, const Geom& g, uint32_t* d_err, int64_t c, int wave, int lane,
+                                                 DecompressLds<NW>& S)
 {
-    static_assert(NW == 1 || std::is_same_v<T, float>, "the split forms write fp32 through fp32 tiles");
-    static_assert(NW == 1 || NW == 2 || NW == 4, "a chunk's 4 layers are shared evenly");
-    if constexpr (sizeof(T) == 8 || std::is_integral_v<T>) {
-        // fp64 (grid modes only), or the integers of a field-global stream
-        // (dequantized after the carries, in any mode)
-        decompress_chunk<RANK, VEC4, false, T, 1>(s, s_bytes, y, g, d_err, c, lane, tile, 0, nullptr);
+    static_assert(NW == 8 || NW == 16, "2 or 1 steps per wave");
+    constexpr int NS = kSteps / NW;
+    constexpr bool F64 = sizeof(T) == 8;
+    constexpr bool INT = std::is_integral_v<T>;
+    // lane i holds flag word i of the chunk (layer i / 16, plane i % 16); the
+    // wave's own layer's words also come as scalars
+    const uint8_t* flags = s + g.flags_off + (int64_t)kFlagBytesPerChunk * c;
+    const uint64_t f = reinterpret_cast<const uint64_t*>(flags)[lane];
+    const int s0 = NS * wave, k = s0 >> 2;
+    const ConstMem<uint64_t>* fk = const_mem<uint64_t>(flags + 8 * kPlanes * k);
+    uint64_t F[kPlanes];
+#pragma unroll
+    for (int b = 0; b < kPlanes; b++) F[b] = fk[b];
+    const ConstMem<uint32_t>* tab = const_mem<uint32_t>(s + g.table_off + 8 * c);
+    const uint32_t off = tab[0], nout = tab[1];
+    const uint32_t hdr_err = check_header(s, g, RANK, F64 ? 1 : 0, INT ? 1 : 0, s_bytes);
+    if (hdr_err) {
+        if (c == 0 && threadIdx.x == 0 && d_err) atomicCAS(d_err, 0u, hdr_err);
+        return;
+    }
+    const uint64_t total = *const_mem<uint64_t>(s + kOffTotal);
+    const uint64_t payload_units = (total - g.payload_off) / 16;
+    int64_t org[3], ext[3];
+    chunk_box(g, c, org, ext);
+    const int L = layers_of(RANK, ext[0]);
+    const int cnt = __popcll(f);
+    const int incl = wave_incl_scan(cnt);
+    const uint32_t nnz = (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+    // the table is the exclusive prefix sum of the chunks' units (Sec. 3.4):
+    // this chunk's offset plus its units (from the flags' popcounts and its
+    // escape count) is the next chunk's offset, or the payload's end.  Chunks
+    // are checked independently, so each also checks that it ends inside the
+    // payload.
+    const uint64_t next = c + 1 < g.n_chunks ? (uint64_t)tab[2] : payload_units;
+    const uint64_t end = (uint64_t)off + nnz + (nout + 1) / 2;
+    const bool bad = nout > (uint32_t)kChunkOutlierCap || end != next || end > payload_units || (c == 0 && off != 0) ||
+                     __ballot(f != 0 && lane >= L * kPlanes) != 0;
+    if (bad) {
+        if (threadIdx.x == 0 && d_err) atomicCAS(d_err, 0u, 6u);
+        return;
+    }
+
+    // The wave's words: plane b of this lane's brick holds the words of steps
+    // s0 .. s0 + NS - 1 at byte voff of the chunk's payload.  A zero brick
+    // gets an offset beyond the resource's range, where the load returns 0
+    // without touching memory.
+    const uint4* pay = reinterpret_cast<const uint4*>(s + g.payload_off) + off;
+    const uint32_t skip = 4u * (uint32_t)(s0 & 3);  // the step's word in a brick, in the resource's base
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<uint8_t*>(const_cast<uint4*>(pay)) + skip, (short)0, nnz ? (int)(16u * nnz - skip) : 0, kBufferFlags);
+    uint32_t base = (uint32_t)__builtin_amdgcn_readlane(incl - cnt, k * kPlanes);
+    uint32_t W[NS][16];
+#pragma unroll
+    for (int b = 0; b < 16; b++) {
+        const uint32_t at = (base + mbcnt(F[b])) << 4;
+        const uint32_t voff = __builtin_amdgcn_inverse_ballot_w64(F[b]) ? at : 0x80000000u;
+        base += (uint32_t)__builtin_popcountll(F[b]);
+        if constexpr (NS == 2) {
+            const auto t = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, 0u, 0);
+            W[0][b] = t[0];
+            W[1][b] = t[1];
+        } else {
+            W[0][b] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, 0u, 0);
+        }
+    }
+
+    // steps of the chunk inside the field (the others hold no cell of it)
+    const int live = (int)(RANK == 3 ? ext[0] : RANK == 2 ? (ext[0] + 1) / 2 : (ext[0] + kStepCodes - 1) / kStepCodes);
+    // escape pairs are in code-index order: those of this wave's steps are the
+    // ones from `seen` (indices below its first code) to `seen_end`
+    const uint32_t* pairs = reinterpret_cast<const uint32_t*>(pay + nnz);
+    uint32_t seen = 0, seen_end = 0, esc_bad = 0;
+    const uint32_t first = (uint32_t)s0 * kStepCodes;
+    if (nout) {
+        uint32_t n0 = 0, n1 = 0;
+        for (uint32_t j = (uint32_t)lane; j < nout; j += 64) {
+            const uint32_t at = pairs[2 * j];
+            n0 += at < first ? 1u : 0u;
+            n1 += at < first + (uint32_t)NS * kStepCodes ? 1u : 0u;
+            esc_bad |= at >= (uint32_t)live * kStepCodes ? 1u : 0u;
+        }
+#pragma unroll
+        for (int sh = 32; sh > 0; sh >>= 1) {
+            n0 += (uint32_t)__shfl_xor((int)n0, sh);
+            n1 += (uint32_t)__shfl_xor((int)n1, sh);
+        }
+        seen = n0;
+        seen_end = n1;
+    }
+
+    int d[NS][32];
+#pragma unroll
+    for (int t = 0; t < NS; t++) {
+        if (s0 + t < live) {
+            if (nout) {
+                const uint32_t emask = escape_mask(W[t]);
+                transpose16(W[t]);
+                decode_codes(W[t], d[t]);
+                esc_bad |= add_escapes(emask, d[t], pairs, seen, seen_end, first, (uint32_t)NS * kStepCodes,
+                                       (uint32_t)(s0 + t) * kStepCodes, lane, S.region[wave]);
+                step_prefix<RANK>(d[t], lane);
+            } else {  // without the branch inside, the widening of the codes goes into the adds
+                transpose16(W[t]);
+                decode_codes(W[t], d[t]);
+                step_prefix<RANK>(d[t], lane);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 32; i++) d[t][i] = 0;
+        }
+        __builtin_amdgcn_sched_barrier(0);  // one step's arrays at a time: 128 registers
+    }
+    if (nout) {  // every escape code has its pair and every pair its escape code
+        if (__syncthreads_or(esc_bad)) {
+            if (threadIdx.x == 0 && d_err) atomicCAS(d_err, 0u, 6u);
+            return;
+        }
+    }
+
+    // sums along the sweep dimension: what the wave's steps add to later ones
+    // goes to its region, those of the waves before are added to its first
+    // step, and that one to its second
+    constexpr int NC = RANK == 3 ? 8 : 4;   // a wave's sum (2-D, 3-D): NC x 4 values per lane
+    constexpr int C0 = RANK == 3 ? 0 : 16;  // from value C0 of a step
+    auto put_sum = [&]() {
+        int* xw = reinterpret_cast<int*>(S.region[wave]);
+#pragma unroll
+        for (int j = 0; j < NC; j++) {
+            int q[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) q[i] = d[NS - 1][C0 + 4 * j + i] + (NS == 2 ? d[0][C0 + 4 * j + i] : 0);
+            *reinterpret_cast<int4*>(xw + 256 * j + 4 * lane) = make_int4(q[0], q[1], q[2], q[3]);
+        }
+    };
+    auto add_sum = [&](int j) {
+        const int* xj = reinterpret_cast<const int*>(S.region[j]);
+#pragma unroll
+        for (int i = 0; i < NC; i++) {
+            const int4 v = *reinterpret_cast<const int4*>(xj + 256 * i + 4 * lane);
+            d[0][4 * i] += v.x;
+            d[0][4 * i + 1] += v.y;
+            d[0][4 * i + 2] += v.z;
+            d[0][4 * i + 3] += v.w;
+            if (RANK == 2) {
+                d[0][16 + 4 * i] += v.x;
+                d[0][16 + 4 * i + 1] += v.y;
+                d[0][16 + 4 * i + 2] += v.z;
+                d[0][16 + 4 * i + 3] += v.w;
+            }
+        }
+    };
+    if (RANK >= 2) put_sum();
+    else if (lane == 63) S.region[wave][0] = (uint32_t)(d[NS - 1][31] + (NS == 2 ? d[0][31] : 0));
+    __syncthreads();
+    if (RANK >= 2) {
+        // in groups of 4 waves: first the waves before in the group, then the
+        // groups before, whose sum their last wave leaves in its region (no
+        // wave has read that one yet): 16 region reads per chunk, not 28
+#pragma unroll 1
+        for (int j = wave & ~3; j < wave; j++) add_sum(j);
+        if ((wave & 3) == 3 && wave < NW - 1) put_sum();
+        __syncthreads();
+#pragma unroll 1
+        for (int j = 3; j < (wave & ~3); j += 4) add_sum(j);
     } else {
-        // the mode byte from its (uniform, scalar-loaded) header word
-        const uint32_t mode = (reinterpret_cast<const uint32_t*>(s)[kOffEbMode / 4] >> (8 * (kOffEbMode % 4))) & 0xFFu;
-        if (mode == 2) decompress_chunk<RANK, VEC4, true, T, NW>(s, s_bytes, y, g, d_err, c, lane, tile, wave, xch);
-        else decompress_chunk<RANK, VEC4, false, T, NW>(s, s_bytes, y, g, d_err, c, lane, tile, wave, xch);
+        int carry = lane < wave ? (int)S.region[lane < NW ? lane : 0][0] : 0;
+#pragma unroll
+        for (int sh = 8; sh > 0; sh >>= 1) carry += __shfl_xor(carry, sh);  // the waves' lanes 0 .. 15
+        carry = __builtin_amdgcn_readfirstlane(carry);
+#pragma unroll
+        for (int i = 0; i < 32; i++) d[0][i] += carry;
+    }
+    if (NS == 2) {
+        const int last = RANK == 1 ? __builtin_amdgcn_readlane(d[0][31], 63) : 0;
+#pragma unroll
+        for (int i = 0; i < 32; i++) d[NS - 1][i] += RANK == 3 ? d[0][i] : RANK == 2 ? d[0][16 + (i & 15)] : last;
+    }
+    __syncthreads();  // the regions become the waves' tiles
+
+    const uint32_t mode = (const_mem<uint32_t>(s)[kOffEbMode / 4] >> (8 * (kOffEbMode % 4))) & 0xFFu;
+#pragma unroll
+    for (int t = 0; t < NS; t++) {
+        if (s0 + t >= live) break;
+        const StepOut<T> o = step_out<RANK, T>(y, g, org, ext, s0 + t);
+        const bool edge = RANK == 3 ? o.rows < 32 || o.cols < 64 : RANK == 2 ? o.rows < 2 || o.cols < 1024 : o.cols < kStepCodes;
+        if constexpr (F64) {
+            const double ebx2 = *const_mem<double>(s + kOffEbx2F64);
+            store_step64<RANK>(o, stream, edge, d[t], ebx2, lane, S.region[wave]);
+        } else {
+            // Dequantization (Sec. 2.3): q * 2eb, one fp32 multiply, or in the
+            // point-wise relative mode the inverse of the bit-pattern
+            // transform with the stream's step (checked by check_header); the
+            // integers themselves for the field-global predictor
+            uint32_t v[32];
+            const float ebx2 = *const_mem<float>(s + kOffEbx2);
+            if (INT) {
+#pragma unroll
+                for (int i = 0; i < 32; i++) v[i] = (uint32_t)d[t][i];
+            } else if (mode == 2) {
+                const uint32_t step = (uint32_t)ebx2;
+#pragma unroll
+                for (int i = 0; i < 32; i++) v[i] = __float_as_uint(pw_dequant(d[t][i], step));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 32; i++) v[i] = __float_as_uint((float)d[t][i] * ebx2);
+            }
+            store_step32<RANK>(o, stream, edge, v, lane, S.region[wave]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 

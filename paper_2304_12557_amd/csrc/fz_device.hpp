@@ -24,12 +24,6 @@ typedef double fz_f64x2 __attribute__((ext_vector_type(2)));
 // 128-byte lines per instruction: partial-line nontemporal stores lose the
 // merging in L2 (measured 3-6x slower).
 constexpr int kCacheStream = 2;
-// the same for whole-line stores of data no kernel of the pipeline reads back
-// soon (the reconstructed field): nt with system scope (sc1), which measured
-// 116 -> 112 us against nt alone for back-to-back 512^3 decompressions (after
-// a compression the two are within noise)
-constexpr int kCacheStreamStore = 2 | 16;
-
 // lane l receives lane l-1's value (DPP wave_shr:1).  Lane 0 receives an
 // unspecified value: the compiler may leave the DPP destination of a lane
 // without a source uninitialized, so callers mask it.
@@ -89,14 +83,17 @@ __device__ __forceinline__ uint32_t mbcnt(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// inclusive prefix sum over the 64 lanes
-__device__ __forceinline__ int wave_incl_scan(int v, int lane)
+// inclusive prefix sum over the 64 lanes: within each row of 16 by DPP row
+// shifts, then the last lane of the row before (rows 1 and 3) and of lane 31
+// (rows 2 and 3) broadcast into the next rows
+__device__ __forceinline__ int wave_incl_scan(int v)
 {
-#pragma unroll
-    for (int sh = 1; sh < 64; sh <<= 1) {
-        int t = lane_value(v, lane - sh);
-        v += lane >= sh ? t : 0;
-    }
+    v += row_shr<1>(v);
+    v += row_shr<2>(v);
+    v += row_shr<4>(v);
+    v += row_shr<8>(v);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
     return v;
 }
 
@@ -195,11 +192,21 @@ constexpr int kMaxCodeDelta = 32767;
 // In-register bit transpose: on entry P[i] holds code i (low half) and code
 // i+16 (high half); on exit P[b] bit m = bit b of code m (Sec. 3.3's
 // bitshuffle of 32 codes).  The transform is its own inverse.
+// One bit-field insert per result, named in assembly: from the masked form
+// the compiler merges the masks of neighbouring stages into up to three ands
+// and ors per result (measured: about 190 instead of 112 instructions per
+// transpose).
+__device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t on, uint32_t off)
+{
+    uint32_t r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(mask), "v"(on), "v"(off));
+    return r;
+}
 template <int S, uint32_t M>
 __device__ __forceinline__ void tswap(uint32_t& a, uint32_t& b)
 {
-    uint32_t na = (a & M) | ((b << S) & ~M);
-    uint32_t nb = ((a >> S) & M) | (b & ~M);
+    const uint32_t na = bfi(M, a, b << S);
+    const uint32_t nb = bfi(M, a >> S, b);
     a = na;
     b = nb;
 }
@@ -253,20 +260,41 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// A uniform pointer read from memory (a batch's job), as one to global memory
+// in scalar registers: the compiler cannot see either by itself and would use
+// flat accesses, per lane.
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p)
+{
+    return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)uniform64((int64_t)(uintptr_t)p);
+}
+
+// Memory that a kernel only reads, at a uniform address: read with scalar
+// loads, whatever else the kernel writes.
+template <typename T>
+using ConstMem = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ ConstMem<T>* const_mem(const void* p)
+{
+    return (ConstMem<T>*)(uintptr_t)uniform64((int64_t)(uintptr_t)p);
+}
+
+__device__ __forceinline__ uint32_t div_by(uint32_t n, const Divisor& d)
+{
+    return (uint32_t)(((uint64_t)n * d.mul) >> d.shift);
+}
+
 __device__ __forceinline__ void chunk_box(const Geom& g, int64_t c, int64_t org[3], int64_t ext[3])
 {
-    // chunk counts stay below 2^31, so 32-bit division suffices
-    const uint32_t cc = (uint32_t)c, g2 = (uint32_t)g.grid[2], g1 = (uint32_t)g.grid[1];
-    const uint32_t q2 = cc / g2;
-    int64_t ci[3];
-    ci[2] = cc - q2 * g2;
-    ci[1] = q2 % g1;
-    ci[0] = q2 / g1;
+    const uint32_t cc = (uint32_t)c, q2 = div_by(cc, g.div[1]), q0 = div_by(q2, g.div[0]);
+    const int64_t ci[3] = {q0, q2 - q0 * (uint32_t)g.grid[1], cc - q2 * (uint32_t)g.grid[2]};
 #pragma unroll
     for (int i = 0; i < 3; i++) {
         org[i] = ci[i] * g.box[i];
-        int64_t e = g.n[i] - org[i];
-        ext[i] = e < g.box[i] ? e : g.box[i];
+        // in 32-bit compares, which the scalar unit has (it has no 64-bit ones)
+        const uint64_t e = (uint64_t)(g.n[i] - org[i]);
+        const uint32_t lo = (uint32_t)e, hi = (uint32_t)(e >> 32), box = (uint32_t)g.box[i];
+        ext[i] = hi == 0u && lo < box ? lo : box;
     }
 }
 

@@ -216,12 +216,13 @@ hipError_t launch_f64_front(const double* x, uint8_t* out, const Geom& g, int mo
 }
 
 // ------------------------------------------------------------ decompression
-template <int RANK, bool VEC4>
-__global__ __launch_bounds__(64, 2) void k_decompress64(const uint8_t* __restrict__ s, uint64_t sb, double* __restrict__ y,
-                                                     Geom g, uint32_t* d_err)
+template <int RANK, bool STREAM>
+__global__ __launch_bounds__(512, 4) void k_decompress64(const uint8_t* __restrict__ s, uint64_t sb, double* __restrict__ y,
+                                                         Geom g, uint32_t* d_err)
 {
-    __shared__ __attribute__((aligned(16))) float tile[kTileFloats64];
-    decompress_chunk_any<RANK, VEC4>(s, sb, y, g, d_err, blockIdx.x, threadIdx.x, tile);
+    __shared__ DecompressLds<8> S;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    decompress_chunk<RANK, double, 8>(s, sb, y, STREAM, g, d_err, blockIdx.x, wave, threadIdx.x & 63, S);
 }
 
 __global__ void k_clear_err(uint32_t* p)
@@ -229,10 +230,10 @@ __global__ void k_clear_err(uint32_t* p)
     if (threadIdx.x == 0) *p = 0u;
 }
 
-template <int RANK, bool VEC4>
+template <int RANK, bool STREAM>
 static hipError_t launch_rank64(const uint8_t* s, uint64_t sb, double* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_decompress64<RANK, VEC4>), dim3((unsigned)g.n_chunks), dim3(64), 0, st, s, sb, y, g, d_err);
+    hipLaunchKernelGGL((k_decompress64<RANK, STREAM>), dim3((unsigned)g.n_chunks), dim3(512), 0, st, s, sb, y, g, d_err);
     return hipGetLastError();
 }
 
@@ -244,8 +245,8 @@ hipError_t launch_decompress_f64(const uint8_t* s, uint64_t sb, double* y, const
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const bool vec4 = (reinterpret_cast<uintptr_t>(y) & 15) == 0 && (g.rank == 1 || (g.n[g.rank - 1] & 3) == 0);
-    switch (g.rank * 2 + (vec4 ? 1 : 0)) {
+    const bool stream = stream_stores(y, g, 8);
+    switch (g.rank * 2 + (stream ? 1 : 0)) {
         case 7: return launch_rank64<3, true>(s, sb, y, g, d_err, st);
         case 6: return launch_rank64<3, false>(s, sb, y, g, d_err, st);
         case 5: return launch_rank64<2, true>(s, sb, y, g, d_err, st);

@@ -81,11 +81,26 @@ constexpr int kStageSlots = 768;
 // its inclusive prefix (kFlagIncl) once its offset is known
 constexpr uint64_t kFlagAgg = 1ull << 62, kFlagIncl = 2ull << 62, kValueMask = (1ull << 62) - 1;
 
+// Division of numbers below 2^31 by an invariant d (1 .. 2^31 - 1) as one
+// multiply and a shift (Granlund and Montgomery): with s = ceil(log2 d),
+// mul = ceil(2^(31+s) / d) <= 2^32 - 1 and n / d = (n * mul) >> (31 + s),
+// since mul * d exceeds 2^(31+s) by less than d <= 2^s.
+struct Divisor {
+    uint32_t mul, shift;
+};
+inline Divisor divisor(uint64_t d)
+{
+    uint32_t s = 0;
+    while ((1ull << s) < d) s++;
+    return Divisor{(uint32_t)(((1ull << (31 + s)) + d - 1) / d), 31 + s};
+}
+
 struct Geom {  // kept trivially copyable and below 448 bytes (it is copied into the scratch)
     int rank;
     int box[3];
     int64_t n[3];     // slowest-first, trailing unused = 1
     int64_t grid[3];  // chunks per dimension
+    Divisor div[2];   // by grid[1] and grid[2]: a chunk's place in the grid
     int64_t n_chunks;
     int64_t table_off, flags_off, payload_off;  // = header bytes
     int64_t stream_bound;  // worst-case stream bytes
@@ -126,6 +141,8 @@ inline bool make_geom(int rank, const uint64_t* dims, Geom* g)
         g->n_chunks *= g->grid[i];
     }
     if (g->n_chunks >= (1ll << 31)) return false;
+    g->div[0] = divisor((uint64_t)g->grid[1]);
+    g->div[1] = divisor((uint64_t)g->grid[2]);
     int64_t table = (8 * g->n_chunks + 15) / 16 * 16;
     g->table_off = kHeaderBytes;
     g->flags_off = kHeaderBytes + table;

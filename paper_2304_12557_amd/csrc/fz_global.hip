@@ -146,12 +146,13 @@ hipError_t launch_face(const float* x, uint8_t* out, const Geom& g, hipStream_t 
 }
 
 // ------------------------------------------------------------ decompression
-template <int RANK, bool VEC4>
-__global__ __launch_bounds__(64, 2) void k_decompress_int(const uint8_t* __restrict__ s, uint64_t sb,
-                                                       int32_t* __restrict__ y, Geom g, uint32_t* d_err)
+template <int RANK, bool STREAM>
+__global__ __launch_bounds__(512, 4) void k_decompress_int(const uint8_t* __restrict__ s, uint64_t sb,
+                                                           int32_t* __restrict__ y, Geom g, uint32_t* d_err)
 {
-    __shared__ float tile[kTileFloats];
-    decompress_chunk_any<RANK, VEC4>(s, sb, y, g, d_err, blockIdx.x, threadIdx.x, tile);
+    __shared__ DecompressLds<8> S;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    decompress_chunk<RANK, int32_t, 8>(s, sb, y, STREAM, g, d_err, blockIdx.x, wave, threadIdx.x & 63, S);
 }
 
 // Carries of the field-global prefix sums.  Along axis ax the field splits
@@ -269,11 +270,11 @@ __global__ void k_clear_err_g(uint32_t* p)
     if (threadIdx.x == 0) *p = 0u;
 }
 
-template <int RANK, bool VEC4>
+template <int RANK, bool STREAM>
 static hipError_t launch_rank_int(const uint8_t* s, uint64_t sb, int32_t* y, const Geom& g, uint32_t* d_err,
                                   hipStream_t st)
 {
-    hipLaunchKernelGGL((k_decompress_int<RANK, VEC4>), dim3((unsigned)g.n_chunks), dim3(64), 0, st, s, sb, y, g, d_err);
+    hipLaunchKernelGGL((k_decompress_int<RANK, STREAM>), dim3((unsigned)g.n_chunks), dim3(512), 0, st, s, sb, y, g, d_err);
     return hipGetLastError();
 }
 
@@ -294,8 +295,8 @@ hipError_t launch_decompress_global(const uint8_t* s, uint64_t sb, float* y, con
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     int32_t* yi = reinterpret_cast<int32_t*>(y);
-    const bool vec4 = (reinterpret_cast<uintptr_t>(y) & 15) == 0 && (g.rank == 1 || (g.n[g.rank - 1] & 3) == 0);
-    switch (g.rank * 2 + (vec4 ? 1 : 0)) {
+    const bool stream = stream_stores(y, g, 4);
+    switch (g.rank * 2 + (stream ? 1 : 0)) {
         case 7: e = launch_rank_int<3, true>(s, sb, yi, g, d_err, st); break;
         case 6: e = launch_rank_int<3, false>(s, sb, yi, g, d_err, st); break;
         case 5: e = launch_rank_int<2, true>(s, sb, yi, g, d_err, st); break;

@@ -44,6 +44,20 @@ hipError_t launch_decompress_global(const uint8_t* s, uint64_t sb, float* y, con
                                     void* work, hipStream_t st);
 size_t global_work_bytes(const Geom& g);
 
+// Whether a decompression's interior stores are streaming ones (nontemporal).
+// They pay where they fill whole 128-byte lines: the output starts on a line
+// and, past 1-D, its rows are whole lines (fp32 rows of 64 values per chunk
+// are two lines; measured: 512^3 107 us streaming, 155 us plain; 2^26 values
+// 1-D 52 / 75 us).  Otherwise two of a row segment's three lines are partial,
+// and plain stores merge them in the L2 (100x500x500: 48 us streaming, 40 us
+// plain).  Of an fp64 segment's five lines only the two ends are partial;
+// there streaming pays for rows of whole 32-byte pieces (the same field in
+// double, round trip: 214 us streaming, 225 us plain).
+inline bool stream_stores(const void* y, const Geom& g, int elem)
+{
+    return aligned_to(y, 128) && (g.rank == 1 || (g.n[g.rank - 1] * elem & (elem == 8 ? 31 : 127)) == 0);
+}
+
 // whether compression may read a field at x with 16-byte loads (4-byte aligned values)
 bool vec_loads(const void* x);
 // blocks of the REL range pass of a field of n values
