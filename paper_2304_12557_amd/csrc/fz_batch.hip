@@ -72,18 +72,19 @@ __global__ __launch_bounds__(256) void k_batch_params(const CompressJob* __restr
 // failed are skipped.  (One instantiation per launch keeps the register
 // budget of the per-field kernel; a kernel holding all six would spill.)
 template <int RANK, bool VEC4>
-__global__ __launch_bounds__(256, 2) void k_batch_compress(const CompressJob* __restrict__ jobs,
+__global__ __launch_bounds__(64 * kLayers, 2) void k_batch_compress(const CompressJob* __restrict__ jobs,
                                                            const int32_t* __restrict__ chunk_job, int64_t total,
                                                            uint32_t* __restrict__ ticket, uint8_t* __restrict__ stage)
 {
     __shared__ CompressLds S;
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* slot = stage + kStageSlotBytes * (int64_t)blockIdx.x;
     if (threadIdx.x == 0) {
         S.ticket = atomicAdd(ticket, 1u);
-        S.err = 0;
+        S.err[0] = S.err[1] = 0;
         S.arrived = 0;
+        S.esc_used = 0;
     }
     __syncthreads();
     int64_t t = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.ticket);
@@ -94,57 +95,71 @@ __global__ __launch_bounds__(256, 2) void k_batch_compress(const CompressJob* __
     int pend_j = -1;  // field and chunk staged in this workgroup's slot, not yet placed
     int64_t pend_c = 0;
     uint32_t pend_units = 0;
-    for (;;) {
+    Counts counts;
+    int par = 0;
+    for (;; par ^= 1) {
+        asm volatile("" : "+v"(lane));  // nothing computed from it is kept (and spilled) over the chunks
         const CompressJob& J = jobs[j];
         const Geom g = J.g;
         const int64_t c = t - J.chunk0;
-        uint8_t* scr = J.out + g.scratch_off;
+        const float* x = as_global(J.x);
+        uint8_t* out = as_global(J.out);
+        uint8_t* scr = out + g.scratch_off;
         const bool skip = reinterpret_cast<const Scratch*>(scr)->pre_status != 0;
-        const Quant inv = quant_of(J.out);
+        const Quant inv = quant_of(out);
         const Lane l = lane_geo<RANK>(g, c, lane);
-        if (!skip && !loaded) prefetch<RANK, VEC4>(J.x, g, l, wave, h, v, swept_down<RANK>(wave));
+        if (!skip && !loaded) prefetch<RANK, VEC4>(x, g, l, wave, lane, h, v);
         uint32_t tk;  // the next ticket, taken early by thread 0 (its return has the layer to arrive)
         if (threadIdx.x == 0) tk = atomicAdd(ticket, 1u);
-        uint64_t F[16], myflag = 0;
-        int nout = 0;
-        if (!skip) nout = chunk_layer<RANK, VEC4>(J.x, scr, g, c, l, wave, lane, inv, h, v, S, F, myflag);
-        if (pend_j >= 0 && wave == 0) {  // the previous chunk's offset, while the other waves finish their layers
-            const CompressJob& P = jobs[pend_j];
-            place_lookback(P.out, P.out + P.g.scratch_off, P.g, pend_c, pend_units, S, lane);
+        StatesAhead ahead;
+        uint8_t* pscr = nullptr;
+        if (pend_j >= 0 && wave == 0) {
+            pscr = as_global(jobs[pend_j].out) + jobs[pend_j].g.scratch_off;
+            states_ahead(reinterpret_cast<const uint64_t*>(pscr + kScratchStateOff), pend_c, lane, ahead);
         }
+        uint32_t W[kPlanes][4];
+        if (!skip) chunk_layer<RANK, VEC4>(x, scr, g, c, l, wave, lane, par, inv, h, v, slot, S, W);
+        if (pend_j >= 0 && wave == 0)  // the previous chunk's offset, while the other waves finish their layers
+            place_lookback(as_global(jobs[pend_j].out), pscr, jobs[pend_j].g, pend_c, pend_units, ahead, S, lane);
         if (threadIdx.x == 0) S.ticket = tk;
-        __syncthreads();
+        lds_barrier();
         const int64_t tn = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.ticket);
         const int jn = tn < total ? __builtin_amdgcn_readfirstlane(chunk_job[tn]) : -1;
-        loaded = false;
-        if (jn == j && !skip) {  // same field: start the next chunk's loads now
-            const Lane ln = lane_geo<RANK>(g, tn - J.chunk0, lane);
-            prefetch<RANK, VEC4>(J.x, g, ln, wave, h, v, swept_down<RANK>(wave));
-            loaded = true;
-        }
-        if (!loaded) {  // defined on every path, so that no value of this chunk stays live into the next
-#pragma unroll
-            for (int i = 0; i < 32; i++) { h[i] = 0.0f; v[i] = 0.0f; }
-        }
-        const uint32_t units = skip ? 0u : chunk_units(S);  // published by the chunk's last layer
-        if (pend_j >= 0) place_copy(jobs[pend_j].out, jobs[pend_j].g, pend_units, slot, S);
+        // same field: start the next chunk's loads now (else: loads that return
+        // zeros, so that the values are defined on one path)
+        loaded = jn == j && !skip;
+        prefetch<RANK, VEC4>(x, g, lane_geo<RANK>(g, loaded ? tn - J.chunk0 : c, lane), wave, lane, h, v, loaded);
+        const ChunkSum m = chunk_sum(S, par);
+        if (pend_j >= 0) place_copy(as_global(jobs[pend_j].out), jobs[pend_j].g, pend_units, S);
+        lds_barrier();  // the staged payload has been read by every wave
         pend_j = -1;
         if (!skip) {
-            stage_chunk<RANK, VEC4>(J.x, J.out, scr, g, c, wave, lane, inv, F, myflag, nout, S, slot);
-            pend_j = j;
-            pend_c = c;
-            pend_units = units;
+            if (chunk_units(m) <= kPayUnits) {
+                store_chunk(out, g, c, wave, lane, par, m, W, slot, S, (LdsUnit*)S.pay);
+                pend_j = j;
+                pend_c = c;
+                pend_units = chunk_units(m);  // published by the chunk's last wave
+            } else {
+                place_now(out, scr, g, c, wave, lane, par, m, W, slot, S);
+            }
+            counts.bricks += m.bricks;
+            counts.pairs += m.kept;
         }
+        if (jn != j) add_counts(out, counts);
         if (tn >= total) break;
         t = tn;
         j = jn;
-        __syncthreads();
     }
     if (pend_j >= 0) {
         const CompressJob& P = jobs[pend_j];
-        if (wave == 0) place_lookback(P.out, P.out + P.g.scratch_off, P.g, pend_c, pend_units, S, lane);
+        uint8_t* out = as_global(P.out);
+        if (wave == 0) {
+            StatesAhead ahead;
+            states_ahead(reinterpret_cast<const uint64_t*>(out + P.g.scratch_off + kScratchStateOff), pend_c, lane, ahead);
+            place_lookback(out, out + P.g.scratch_off, P.g, pend_c, pend_units, ahead, S, lane);
+        }
         __syncthreads();  // the staged payload and its offset are complete
-        place_copy(P.out, P.g, pend_units, slot, S);
+        place_copy(out, P.g, pend_units, S);
     }
 }
 
@@ -298,12 +313,12 @@ hipError_t plan_run(const Plan* P, hipStream_t st)
         uint32_t* tk = P->d_ticket + key;
         uint8_t* sg = static_cast<uint8_t*>(P->d_stage);
         switch (key) {
-            case 7: hipLaunchKernelGGL((k_batch_compress<3, true>), dim3((unsigned)grid), dim3(256), 0, st, jobs, tab, n, tk, sg); break;
-            case 6: hipLaunchKernelGGL((k_batch_compress<3, false>), dim3((unsigned)grid), dim3(256), 0, st, jobs, tab, n, tk, sg); break;
-            case 5: hipLaunchKernelGGL((k_batch_compress<2, true>), dim3((unsigned)grid), dim3(256), 0, st, jobs, tab, n, tk, sg); break;
-            case 4: hipLaunchKernelGGL((k_batch_compress<2, false>), dim3((unsigned)grid), dim3(256), 0, st, jobs, tab, n, tk, sg); break;
-            case 3: hipLaunchKernelGGL((k_batch_compress<1, true>), dim3((unsigned)grid), dim3(256), 0, st, jobs, tab, n, tk, sg); break;
-            default: hipLaunchKernelGGL((k_batch_compress<1, false>), dim3((unsigned)grid), dim3(256), 0, st, jobs, tab, n, tk, sg); break;
+            case 7: hipLaunchKernelGGL((k_batch_compress<3, true>), dim3((unsigned)grid), dim3(64 * kLayers), 0, st, jobs, tab, n, tk, sg); break;
+            case 6: hipLaunchKernelGGL((k_batch_compress<3, false>), dim3((unsigned)grid), dim3(64 * kLayers), 0, st, jobs, tab, n, tk, sg); break;
+            case 5: hipLaunchKernelGGL((k_batch_compress<2, true>), dim3((unsigned)grid), dim3(64 * kLayers), 0, st, jobs, tab, n, tk, sg); break;
+            case 4: hipLaunchKernelGGL((k_batch_compress<2, false>), dim3((unsigned)grid), dim3(64 * kLayers), 0, st, jobs, tab, n, tk, sg); break;
+            case 3: hipLaunchKernelGGL((k_batch_compress<1, true>), dim3((unsigned)grid), dim3(64 * kLayers), 0, st, jobs, tab, n, tk, sg); break;
+            default: hipLaunchKernelGGL((k_batch_compress<1, false>), dim3((unsigned)grid), dim3(64 * kLayers), 0, st, jobs, tab, n, tk, sg); break;
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

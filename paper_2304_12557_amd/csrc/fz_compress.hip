@@ -5,10 +5,8 @@
 // code in fz_compress_dev.hpp.  The next chunk's first loads are issued
 // before the current chunk is placed.  The device-wide prefix sum of the
 // encoder (Sec. 3.4) is a look-back over published chunk sizes: a chunk is
-// staged in its workgroup's slot and placed one chunk later, when the sizes
-// of the chunks before it are almost always published, so the look-back
-// rarely waits; then the slot, still in the cache, is copied to the chunk's
-// offset.  The grid's last workgroup to finish settles the status word.  REL
+// staged in LDS and placed one chunk later, when the sizes of the chunks
+// before it are almost always published, so the look-back rarely waits.  The grid's last workgroup to finish settles the status word.  REL
 // mode runs k_minmax first (the value range, plus k_init's work), and
 // k_compress folds the range into the eb parameters itself.
 #include <hip/hip_runtime.h>
@@ -24,12 +22,12 @@ namespace fz {
 // (the same bits everywhere) and workgroup 0 writes them to the header, so
 // no separate launch sits between the range pass and this kernel.
 template <int RANK, bool VEC4, int QM>
-__global__ __launch_bounds__(256, 2) void k_compress(const float* __restrict__ x, uint8_t* __restrict__ out,
+__global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __restrict__ x, uint8_t* __restrict__ out,
                                                      uint8_t* __restrict__ scratch, Geom g, double rel_eb, int nparts)
 {
     __shared__ CompressLds S;
     Scratch* scr = reinterpret_cast<Scratch*>(scratch);
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: keep it scalar
     Quant inv;
     if (rel_eb > 0.0) {
@@ -45,8 +43,9 @@ __global__ __launch_bounds__(256, 2) void k_compress(const float* __restrict__ x
 
     if (threadIdx.x == 0) {
         S.ticket = atomicAdd(&scr->ticket, 1u);
-        S.err = 0;
+        S.err[0] = S.err[1] = 0;
         S.arrived = 0;
+        S.esc_used = 0;
     }
     __syncthreads();
     int64_t c = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.ticket);
@@ -54,50 +53,67 @@ __global__ __launch_bounds__(256, 2) void k_compress(const float* __restrict__ x
         finish_if_last(out, scratch);
         return;
     }
+    const uint64_t* state = reinterpret_cast<const uint64_t*>(scratch + kScratchStateOff);
     float h[32], v[32];
     Lane l = lane_geo<RANK>(g, c, lane);
-    prefetch<RANK, VEC4>(x, g, l, wave, h, v, swept_down<RANK>(wave));
-    int64_t pend = -1;  // the chunk staged in this workgroup's slot, not yet placed
+    prefetch<RANK, VEC4>(x, g, l, wave, lane, h, v);
+    int64_t pend = -1;  // the chunk staged in LDS, not yet placed
     uint32_t pend_units = 0;
+    Counts counts;
+    int par = 0;
 
-    for (;;) {
-        // the next chunk's ticket, taken now so that its return has the whole
-        // layer to arrive
+    for (;; par ^= 1) {
+        asm volatile("" : "+v"(lane));  // nothing computed from it is kept (and spilled) over the chunks
+        // the next chunk's ticket, and the states the look-back starts from,
+        // taken now so that their returns have the whole layer to arrive
         uint32_t tk;  // thread 0 only: a value on the other lanes would need a copy that waits for the atomic
         if (threadIdx.x == 0) tk = atomicAdd(&scr->ticket, 1u);
-        uint64_t F[16], myflag;
+        StatesAhead ahead;
+        if (wave == 0) states_ahead(state, pend >= 0 ? pend : 0, lane, ahead);
+        uint32_t W[kPlanes][4];
         // wave priority: the layer at the lowest, the serial part after it
         // (look-back, barrier, placement, staging) at a higher one, so that
         // its few instructions issue first when the CU's other workgroup is in
-        // its layer (measured: 512^3 compression about 2 us faster)
+        // its layer
         __builtin_amdgcn_s_setprio(0);
-        const int nout = chunk_layer<RANK, VEC4, QM>(x, scratch, g, c, l, wave, lane, inv, h, v, S, F, myflag);
+        chunk_layer<RANK, VEC4, QM>(x, scratch, g, c, l, wave, lane, par, inv, h, v, slot, S, W);
         __builtin_amdgcn_s_setprio(3);
         // the previous chunk's offset: wave 0 looks back while the other waves finish their layers
-        if (pend >= 0 && wave == 0) place_lookback(out, scratch, g, pend, pend_units, S, lane);
+        if (pend >= 0 && wave == 0) place_lookback(out, scratch, g, pend, pend_units, ahead, S, lane);
         if (threadIdx.x == 0) S.ticket = tk;
-        __syncthreads();
+        lds_barrier();
         const int64_t cn = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.ticket);
-        if (cn < g.n_chunks) {  // start loading the next chunk while this one is placed
-            l = lane_geo<RANK>(g, cn, lane);
-            prefetch<RANK, VEC4>(x, g, l, wave, h, v, swept_down<RANK>(wave));
-        } else {  // defined on every path: otherwise the values of this chunk's
-                  // last step stay live across the placement and are spilled
-#pragma unroll
-            for (int i = 0; i < 32; i++) { h[i] = 0.0f; v[i] = 0.0f; }
+        const bool more = cn < g.n_chunks;
+        // start loading the next chunk while this one is placed (without one:
+        // loads that return zeros, so that the values are defined on one path)
+        l = lane_geo<RANK>(g, more ? cn : c, lane);
+        prefetch<RANK, VEC4>(x, g, l, wave, lane, h, v, more);
+        const ChunkSum m = chunk_sum(S, par);
+        if (pend >= 0) place_copy(out, g, pend_units, S);
+        lds_barrier();  // the staged payload has been read by every wave
+        if (chunk_units(m) <= kPayUnits) {
+            store_chunk(out, g, c, wave, lane, par, m, W, slot, S, (LdsUnit*)S.pay);
+            pend = c;
+            pend_units = chunk_units(m);  // published by the chunk's last wave
+        } else {
+            place_now(out, scratch, g, c, wave, lane, par, m, W, slot, S);
+            pend = -1;
         }
-        const uint32_t units = chunk_units(S);  // published by the chunk's last layer
-        if (pend >= 0) place_copy(out, g, pend_units, slot, S);
-        stage_chunk<RANK, VEC4, QM>(x, out, scratch, g, c, wave, lane, inv, F, myflag, nout, S, slot);
-        pend = c;
-        pend_units = units;
-        if (cn >= g.n_chunks) break;
+        counts.bricks += m.bricks;
+        counts.pairs += m.kept;
+        if (!more) break;
         c = cn;
-        __syncthreads();  // the LDS counts and bricks are reused by the next chunk
     }
-    if (wave == 0) place_lookback(out, scratch, g, pend, pend_units, S, lane);
-    __syncthreads();  // the staged payload and its offset are complete
-    place_copy(out, g, pend_units, slot, S);
+    if (pend >= 0) {
+        if (wave == 0) {
+            StatesAhead ahead;
+            states_ahead(state, pend, lane, ahead);
+            place_lookback(out, scratch, g, pend, pend_units, ahead, S, lane);
+        }
+        __syncthreads();  // the staged payload and its offset are complete
+        place_copy(out, g, pend_units, S);
+    }
+    add_counts(out, counts);
     finish_if_last(out, scratch);
 }
 
@@ -150,7 +166,7 @@ static hipError_t launch_rank(const float* x, uint8_t* out, uint8_t* scr, const 
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_compress<RANK, VEC4, QM>, 256, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_compress<RANK, VEC4, QM>, 64 * kLayers, 0) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
     int64_t grid = (int64_t)cus * per_cu;  // one staging slot per workgroup: at most kStageSlots
@@ -158,7 +174,7 @@ static hipError_t launch_rank(const float* x, uint8_t* out, uint8_t* scr, const 
     if (grid > g.n_chunks) grid = g.n_chunks;
     hipError_t e;
     if (t && (e = mark(t->main_begin, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_compress<RANK, VEC4, QM>), dim3((unsigned)grid), dim3(256), 0, st, x, out, scr, g, rel_eb,
+    hipLaunchKernelGGL((k_compress<RANK, VEC4, QM>), dim3((unsigned)grid), dim3(64 * kLayers), 0, st, x, out, scr, g, rel_eb,
                        nparts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (t && (e = mark(t->main_end, st)) != hipSuccess) return e;

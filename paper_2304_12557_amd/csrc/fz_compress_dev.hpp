@@ -3,21 +3,28 @@
 //
 // The path of one chunk: a workgroup of 4 waves, wave k on layer k (4 steps),
 // one lane per 32-code patch.  Per step a lane prequantizes its 32 fp32 values
-// (Sec. 2.3), applies the Lorenzo difference on the integers (Sec. 2.3 / 3.2;
-// the previous step sits in the same lane's registers, the other neighbours
-// come from adjacent lanes), maps the deltas to sign-magnitude 16-bit codes
-// (Sec. 3.2) with packed 16-bit arithmetic, and bit-transposes the 32 codes in
-// registers (the bitshuffle of Sec. 3.3).  After its 4 steps a lane holds 16
-// bricks (one per bit plane); a ballot per plane gives the bit flags of the
-// zero-block encoder (Sec. 3.4), and the nonzero bricks are compacted into
-// the workgroup's staging slot with coalesced 16-byte writes.  A layer whose
-// deltas need escapes is computed again out of line; its (index, delta) pairs
-// are written after the workgroup barrier, once every layer's count is known,
-// straight to their place behind the chunk's bricks.  A chunk cut by the
-// field's edge runs the same code; the codes of its cells outside the field
-// are cleared afterwards.  One chunk later, when
-// a look-back over the published chunk sizes (the device-wide prefix sum of
-// Sec. 3.4) has given the chunk its offset, the slot is copied there.
+// (Sec. 2.3) and takes the Lorenzo difference on the integers (Sec. 2.3 / 3.2)
+// along the sweep dimension against the previous step in its registers.  What
+// follows runs packed, two 16-bit values per instruction: the rest of the
+// difference (neighbours come from adjacent lanes), the sign-magnitude codes
+// (Sec. 3.2) and the in-register bit transpose (the bitshuffle of Sec. 3.3).
+// A lane keeps the plane words of its 4 steps: a brick (one bit plane of a
+// patch over the layer) is 4 registers of one lane, so no exchange is needed.
+// Ballots give the bit flags of the zero-block encoder (Sec. 3.4), and the
+// nonzero bricks are compacted into LDS, which holds the chunk's whole
+// payload.  One chunk later, when a look-back over the published chunk sizes
+// (the device-wide prefix sum of Sec. 3.4) has given the chunk its offset, the
+// payload is copied there.  A layer whose differences along the sweep do not
+// fit the packed arithmetic is coded again out of line in 32 bits, where
+// deltas that need escapes are logged.
+//
+// What bounds it: memory at large fields (512^3 ABS: 134 us, 4.6 TB/s of reads
+// and stores where a copy reaches 5.1; 168 us in the form before, where each
+// of 4 waves coded one layer with the plane words in LDS and the staged payload
+// in a global slot), else the chain of one chunk through a workgroup.  256
+// registers a lane (2 waves per SIMD) hold a layer's 64 plane words and the
+// next step's loads; 8 waves of half a layer each at 128 registers measured
+// 169 us with the same staging.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -27,58 +34,55 @@
 
 namespace fz {
 
-struct EscapeLog {
-    uint32_t* pairs;  // null: count only; else the layer's (index, delta) pairs in the payload
-    int count;        // escapes seen so far in this layer
-    int room;         // pairs that may be written (what the chunk's allowance leaves the layer)
+// ------------------------------------------------------------- workgroup
+// A chunk's payload is staged in LDS up to this size (60 KB; the whole
+// workgroup stays below half of a CU's 160 KB).  A larger one, more than 15
+// bits per value, is placed at once.
+constexpr uint32_t kPayUnits = 3840;
+
+// Workgroup-shared state of a compression workgroup (one chunk at a time).
+struct CompressLds {
+    uint4 pay[kPayUnits];  // the staged chunk's payload: bricks, then escape pairs
+    uint4 tile[kLayers][256];  // per wave: half a step on its way from rows to patches
+    uint32_t arrived;  // waves whose layer of the current chunk is done
+    uint64_t ticket;
+    uint64_t excl;     // offset of the chunk being placed (16-B units), from the look-back
+    // status bits, and bricks and escapes of each layer, by the chunk's parity:
+    // a wave may be one chunk ahead of one that still reads them
+    uint32_t err[2];
+    uint32_t nnz[2][kLayers], nout[2][kLayers];
+    // escapes (rare): pairs logged so far, and each step's block of them
+    uint32_t esc_used;
+    uint32_t esc_n[kSteps], esc_at[kSteps];
 };
+typedef __attribute__((address_space(3))) CompressLds LdsState;
+// The workgroup's slot of the scratch, used by layers that are coded out of
+// line: their bricks (16 KB per layer), then the chunk's escape pairs.
+constexpr int kSlotPairs = kLayers * kPlanes * kPatches * 16;
+static_assert(kSlotPairs + kChunkOutlierCap * 8 == kStageSlotBytes, "slot layout");
 
-// Slow path of a step with at least one escape: codes whose delta does not
-// fit in 15 bits become 0x8000 and their (code index, delta) pair is logged
-// in code-index order (lane-major, then cell).
-__device__ __forceinline__ void log_escapes(const int (&d)[32], uint32_t (&P)[16], EscapeLog& log, uint32_t n0, int lane)
-{
-    uint32_t emask = 0;
-#pragma unroll
-    for (int i = 0; i < 32; i++) emask |= ((uint32_t)d[i] + 32767u > kEscapeLimit ? 1u : 0u) << i;
-    const int cnt = __popc(emask);
-    const int incl = wave_incl_scan(cnt);
-    const int total = __shfl(incl, 63);
-    int pos = log.count + incl - cnt;
-#pragma unroll
-    for (int i = 0; i < 32; i++) {
-        if ((emask >> i) & 1u) {
-            if (log.pairs && pos < log.room)
-                *reinterpret_cast<uint2*>(log.pairs + 2 * pos) = make_uint2(n0 + (uint32_t)lane * kPatchCodes + i, (uint32_t)d[i]);
-            pos++;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 16; i++) {
-        if ((emask >> i) & 1u) P[i] = (P[i] & 0xFFFF0000u) | kEscape;
-        if ((emask >> (i + 16)) & 1u) P[i] = (P[i] & 0x0000FFFFu) | (kEscape << 16);
-    }
-    log.count += total;
-}
+// ---------------------------------------------------------- one step's codes
+// In the packed path the integers of the 2eb grid carry this bias (the bits of
+// 1.5 * 2^23 as a float): rounding to the nearest integer is then one float
+// add, whose result bits are bias + q, for products below 2^22 (larger ones
+// are coded out of line).  The difference along the sweep dimension cancels it.
+constexpr float kRoundMagic = 12582912.0f;
+constexpr int kRoundBias = 0x4B400000;
+constexpr float kRoundLimit = 4194304.0f;
 
-// codes -> escapes -> bit planes, shared tail of every rank's step.  The fast
-// pass (ESC = false) only reports that a step needs escapes; the layer is then
-// redone by the logging pass (ESC = true), which rewrites those codes.
-template <bool ESC>
-__device__ __forceinline__ bool finish_step(const int (&d)[32], uint32_t (&P)[16], EscapeLog& log, uint32_t n0, int lane)
-{
-    int dmin = 0, dmax = 0;
-    pack_codes(d, P, dmin, dmax);
-    const bool esc = __ballot(dmax > kMaxCodeDelta || dmin < -kMaxCodeDelta) != 0;
-    if (ESC && esc) log_escapes(d, P, log, n0, lane);
-    transpose16(P);
-    return esc;
-}
+// Largest difference along the sweep dimension whose codes the packed 16-bit
+// arithmetic gets right: the rest of the predictor adds 4 such terms in 3-D
+// and 2 in 2-D, and a code holds 32767.
+template <int RANK>
+__device__ __forceinline__ constexpr int packed_limit() { return RANK == 3 ? 8191 : RANK == 2 ? 16383 : 32767; }
+
+template <int QM>
+__device__ __forceinline__ constexpr int quant_bias() { return QM == kQuantGrid ? kRoundBias : 0; }
 
 // prequantize 32 values; `facc` tracks max |p| with NaN propagating
-// (v_maximum3_f32), so one compare per step (!(facc < 2^31)) finds NaN, Inf
-// or an overflowing product
-template <int QM>
+// (v_maximum3_f32), so one compare finds NaN, Inf or an overflowing product.
+// BIASED: the packed path's integers; else plain ones, for any product.
+template <int QM, bool BIASED>
 __device__ __forceinline__ void prequant32(const float (&v)[32], const Quant& z, float& facc, int (&q)[32])
 {
     if constexpr (QM == kQuantInt) {  // the values are already the integers q (fp64 input)
@@ -90,10 +94,15 @@ __device__ __forceinline__ void prequant32(const float (&v)[32], const Quant& z,
 #pragma unroll
     for (int i = 0; i < 32; i += 2) {
         const float p0 = v[i] * inv, p1 = v[i + 1] * inv;
-        facc = __builtin_elementwise_maximum(facc, __builtin_elementwise_maximum(__builtin_fabsf(p0), __builtin_fabsf(p1)));
+        // one instruction per two values (from the nested form the compiler
+        // builds a tree of half as many values per instruction)
+        asm("v_maximum3_f32 %0, %0, |%1|, |%2|" : "+v"(facc) : "v"(p0), "v"(p1));
         if constexpr (QM == kQuantPw) {
             q[i] = pw_quant(v[i], z);
             q[i + 1] = pw_quant(v[i + 1], z);
+        } else if constexpr (BIASED) {
+            q[i] = __float_as_int(p0 + kRoundMagic);
+            q[i + 1] = __float_as_int(p1 + kRoundMagic);
         } else {
             q[i] = (int)__builtin_rintf(p0);
             q[i + 1] = (int)__builtin_rintf(p1);
@@ -101,12 +110,45 @@ __device__ __forceinline__ void prequant32(const float (&v)[32], const Quant& z,
     }
 }
 
+// The escapes of a step (deltas that do not fit in 15 bits, of cells inside
+// the field: keep): their (code index, delta) pairs go to a block of the
+// slot's list, in code-index order (lane-major, then cell; past the chunk's
+// allowance only counted), and the deltas are replaced by -32768, whose code
+// is the escape 0x8000.  Returns their number.
+__device__ __forceinline__ uint32_t log_escapes(int (&d)[32], uint32_t keep, int s, int lane, LdsState* S, uint2* pairs)
+{
+    uint32_t emask = 0;
+#pragma unroll
+    for (int i = 0; i < 32; i++) emask |= ((uint32_t)d[i] + 32767u > kEscapeLimit ? 1u : 0u) << i;
+    emask &= keep;
+    const int cnt = __popc(emask);
+    const int incl = wave_incl_scan(cnt);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+    uint32_t at = 0;
+    if (lane == 0) {
+        at = __hip_atomic_fetch_add(&S->esc_used, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        S->esc_at[s] = at;
+        S->esc_n[s] = total;
+    }
+    uint32_t pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)(incl - cnt);
+    const uint32_t n0 = (uint32_t)s * kStepCodes + (uint32_t)lane * kPatchCodes;
+#pragma unroll
+    for (int i = 0; i < 32; i++) {
+        if ((emask >> i) & 1u) {
+            if (pos < (uint32_t)kChunkOutlierCap) pairs[pos] = make_uint2(n0 + i, (uint32_t)d[i]);
+            pos++;
+            d[i] = -32768;
+        }
+    }
+    return total;
+}
+
 // ------------------------------------------------------------------ loaders
 // Loads go through a buffer resource whose base is the (uniform) first value
-// of the step: a lane keeps one 32-bit byte offset for the whole chunk and
-// the row offsets are uniform, so no 64-bit per-lane address is held in
-// registers.  The resource's range ends at the field's last value, so a load
-// past it returns 0 without touching memory.  A chunk cut by the field's edge
+// of the step: lane offsets are 32-bit and the row offsets uniform, so no
+// 64-bit per-lane address is held in registers.  The resource's range ends at
+// the field's last value, so a load past it (its uniform offset counted)
+// returns 0 without touching memory.  A chunk cut by the field's edge
 // is loaded exactly like an interior one: its cells outside the field read 0
 // (past the end) or values of other chunks (the rest of a row, the next
 // rows), and their deltas are set to 0 afterwards (mask_outside), while the
@@ -115,8 +157,10 @@ __device__ __forceinline__ void prequant32(const float (&v)[32], const Quant& z,
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t step_rsrc(const float* __restrict__ x, const Geom& g,
                                                            const float* base, bool on = true)
 {
-    const int64_t left = 4 * (g.n[0] * g.n[1] * g.n[2] - (base - x));  // uniform
-    const int range = !on || left <= 0 ? 0 : left >= 0xFFFFFFFFll ? -1 : (int)(uint32_t)left;
+    // (uniform; in 32-bit compares, which the scalar unit has)
+    const int64_t left = 4 * (g.n[0] * g.n[1] * g.n[2] - (base - x));
+    const int hi = (int)(left >> 32);
+    const int range = !on || hi < 0 ? 0 : hi > 0 ? -1 : (int)(uint32_t)left;
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, range, kBufferFlags);
 }
 
@@ -145,7 +189,7 @@ __device__ __forceinline__ void load_run(__amdgpu_buffer_rsrc_t r, uint32_t voff
 // offsets inside a step are 32-bit.
 struct Lane {
     int64_t org[3], ext[3];
-    int L;
+    int live;      // steps of the chunk that hold cells of the field
     bool edge;
     uint32_t off;  // lane offset of its first value inside a step
 };
@@ -155,15 +199,8 @@ __device__ __forceinline__ Lane lane_geo(const Geom& g, int64_t c, int lane)
 {
     Lane l;
     chunk_box(g, c, l.org, l.ext);
-    // the box is the same on every lane, but its divisions run on the vector
-    // unit: copied to scalar registers, so that the loads' row offsets and
-    // resources built from it stay scalar
-#pragma unroll
-    for (int i = 0; i < 3; i++) {
-        l.org[i] = uniform64(l.org[i]);
-        l.ext[i] = uniform64(l.ext[i]);
-    }
-    l.L = layers_of(RANK, l.ext[0]);
+    const int e0 = (int)l.ext[0];
+    l.live = RANK == 3 ? e0 : RANK == 2 ? (e0 + 1) / 2 : (e0 + kStepCodes - 1) / kStepCodes;
     l.edge = false;
 #pragma unroll
     for (int i = 0; i < 3; i++) l.edge |= l.ext[i] < g.box[i];
@@ -187,19 +224,15 @@ __device__ __forceinline__ const float* step_base(const float* __restrict__ x, c
     return x + l.org[0] + (int64_t)kStepCodes * s;
 }
 
-// load the lane's 32 values of step s (s = 4k-1 is the halo of layer k),
-// through the step's ranged resource (step_rsrc; on = false: zeros).  NT: 3-D
-// loads nontemporal (streaming).
-template <int RANK, bool VEC4, bool NT>
-__device__ __forceinline__ void load_step_as(const float* __restrict__ x, const Geom& g, const Lane& l, int64_t s,
-                                             bool on, float (&v)[32])
+// The lane's own 32 values of step s, patch by patch (the layers coded out of line).
+template <int RANK, bool VEC4>
+__device__ __forceinline__ void load_patch(const float* __restrict__ x, const Geom& g, const Lane& l, int64_t s, float (&v)[32])
 {
-    const float* b = step_base<RANK>(x, g, l, s);
-    const __amdgpu_buffer_rsrc_t rs = step_rsrc(x, g, b, on);
+    const __amdgpu_buffer_rsrc_t rs = step_rsrc(x, g, step_base<RANK>(x, g, l, s));
     if (RANK == 3) {
         const int64_t nx = g.n[2];
 #pragma unroll
-        for (int r = 0; r < 4; r++) load_run<8, VEC4, NT>(rs, 4u * l.off, (uint32_t)(4 * r * nx), v + 8 * r);
+        for (int r = 0; r < 4; r++) load_run<8, VEC4>(rs, 4u * l.off, (uint32_t)(4 * r * nx), v + 8 * r);
     } else if (RANK == 2) {
         const int64_t nx = g.n[1];
 #pragma unroll
@@ -209,19 +242,115 @@ __device__ __forceinline__ void load_step_as(const float* __restrict__ x, const 
     }
 }
 
-// 3-D loads are nontemporal except for the top step of a layer (s mod 4 =
-// 3), which the next layer's wave reads again as its halo in the same
-// iteration and must find in the cache (measured: the 512^3 ABS compression
-// 173 -> 166 us).  After unrolling, s mod 4 is a constant.  In 2-D and 1-D a
-// lane's run spans 4 or 8 load instructions per line, and nontemporal loads
-// there measured 6 % and 40 % slower: lines left before the rest of their run
-// was read.
-template <int RANK, bool VEC4>
-__device__ __forceinline__ void load_step(const float* __restrict__ x, const Geom& g, const Lane& l, int64_t s,
-                                          float (&v)[32])
+// Step s as rows: each load covers whole lines of memory (a lane's own patch
+// would give each load 16-byte pieces 32, 64 or 128 bytes apart, every line
+// touched by several loads).  Loads 0 .. 3 and 4 .. 7 are two halves that
+// rows_to_patches exchanges one after the other:
+//   3-D: load j covers 4 rows of 64 values: rows 4 py + 0, 1 (first half) or
+//   + 2, 3 of the patch rows py = 2j, 2j + 1, a row's 16 pieces exchanged by
+//   XOR with py;
+//   2-D: 256 columns of row 0 (first half) or 1;
+//   1-D: the first or last 16 values of 16 patches.
+template <int RANK, bool VEC4, bool NT>
+__device__ __forceinline__ void load_rows_as(const float* __restrict__ x, const Geom& g, const Lane& l, int64_t s, bool on,
+                                             int lane, float (&v)[32])
 {
-    if ((s & 3) == 3) load_step_as<RANK, VEC4, false>(x, g, l, s, true, v);
-    else load_step_as<RANK, VEC4, RANK == 3>(x, g, l, s, true, v);
+    const __amdgpu_buffer_rsrc_t rs = step_rsrc(x, g, step_base<RANK>(x, g, l, s), on);
+    const uint32_t nx = (uint32_t)g.n[RANK - 1];  // (1-D: not used)
+    if (RANK == 3) {
+        const uint32_t row = 4u * (uint32_t)(lane >> 5) + (uint32_t)((lane >> 4) & 1);
+        const uint32_t piece = (uint32_t)((lane & 15) ^ (lane >> 5));
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            load_run<4, VEC4, NT>(rs, 4u * row * nx + 16u * (piece ^ (2u * (j & 3))), 4u * (8u * (j & 3) + 2u * (j >> 2)) * nx, v + 4 * j);
+    } else if (RANK == 2) {
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            load_run<4, VEC4, NT>(rs, 16u * (uint32_t)lane + 1024u * (j & 3), j < 4 ? 0u : 4u * nx, v + 4 * j);
+    } else {
+        const uint32_t at = 128u * (uint32_t)(lane >> 2) + 16u * (uint32_t)(lane & 3);
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            load_run<4, VEC4, NT>(rs, at + 2048u * (j & 3) + 64u * (j >> 2), 0u, v + 4 * j);
+    }
+}
+
+// A step's values from the rows that load_rows left in v to the lanes'
+// patches, in place, through the wave's tile in two halves.  The tile's places
+// are exchanged by XOR so that both directions spread over the banks.  One
+// wave's LDS operations execute in order, so nothing is waited for in between;
+// the compiler must only keep them in this order.
+template <int RANK>
+__device__ __forceinline__ void rows_to_patches(float (&v)[32], int lane, uint4* tile)
+{
+    const int py = lane & 7, px = lane >> 3;
+#pragma unroll
+    for (int hf = 0; hf < 2; hf++) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const float* r = v + 16 * hf + 4 * i;
+            tile[64 * i + (RANK == 3 ? lane : lane ^ (lane >> 4))] =
+                make_uint4(__float_as_uint(r[0]), __float_as_uint(r[1]), __float_as_uint(r[2]), __float_as_uint(r[3]));
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint4 t = tile[RANK == 3 ? 32 * py + 16 * (i >> 1) + ((2 * px + (i & 1)) ^ py)
+                                           : 4 * lane + (i ^ ((lane >> 2) & 3))];
+            float* w = v + 16 * hf + 4 * i;
+            w[0] = __uint_as_float(t.x); w[1] = __uint_as_float(t.y);
+            w[2] = __uint_as_float(t.z); w[3] = __uint_as_float(t.w);
+        }
+        asm volatile("" ::: "memory");
+    }
+}
+
+// Step s as rows, nontemporal except for a step that is read again in the same
+// iteration (cached: the top step of a layer, 3-D and 2-D, which is the next
+// layer's halo) and must be found in the cache, and except in 1-D, where two
+// loads share a line (measured, everything cached against this rule: 512^3
+// ABS 135.2 -> 133.6 us, 500^3 half as large 44.6 -> 41.6 us, 8192^2 75.2 -> 73.9 us; 1-D of 2^26 values
+// nontemporal 85.3, cached 78.8 us).
+template <int RANK, bool VEC4>
+__device__ __forceinline__ void load_rows(const float* __restrict__ x, const Geom& g, const Lane& l, int64_t s, bool on,
+                                          bool cached, int lane, float (&v)[32])
+{
+    if (RANK == 1 || cached) load_rows_as<RANK, VEC4, false>(x, g, l, s, on, lane, v);
+    else load_rows_as<RANK, VEC4, true>(x, g, l, s, on, lane, v);
+}
+
+// Whether layer k of a chunk is swept downwards (odd layers, 2-D and 3-D).
+// An odd layer's halo is the top step of the layer below it, and an even
+// layer's halo the top step of an odd layer; in this order each halo step is
+// loaded in the same phase as by the wave that owns it, so the second load is
+// served by the cache.
+template <int RANK>
+__device__ __forceinline__ bool swept_down(int k)
+{
+    return RANK >= 2 && (k & 1);
+}
+
+// Load the first two steps that layer k of a chunk uses ahead of time: the
+// halo and the first step (upwards), or the top two steps (downwards).
+// Branch-free: both loads are always issued, and one that has nothing to
+// read (no next chunk: on; no layer k, the halo of layer 0 or of a 1-D layer) gets a range of 0
+// and returns zeros.  A branch here would merge the loads' uniform row
+// offsets at its join, where the compiler keeps them in vector registers and
+// then has to build a loop around every later load that uses them.  The
+// halo or top step is the one another wave reads again, the other one is
+// streamed.
+template <int RANK, bool VEC4>
+__device__ __forceinline__ void prefetch(const float* __restrict__ x, const Geom& g, const Lane& l, int k,
+                                         int lane, float (&h)[32], float (&v)[32], bool on = true)
+{
+    const bool live = on && 4 * k < l.live, dn = swept_down<RANK>(k);
+    if (RANK == 1) {  // no halo step (a 1-D layer's halo is one value)
+#pragma unroll
+        for (int i = 0; i < 32; i++) h[i] = 0.0f;
+    } else {
+        load_rows<RANK, VEC4>(x, g, l, dn ? 4 * k + 3 : 4 * k - 1, live && (dn || k > 0), true, lane, h);
+    }
+    load_rows<RANK, VEC4>(x, g, l, dn ? 4 * k + 2 : 4 * k, live, false, lane, v);
 }
 
 // The lane's cells of step s inside the field, one bit per value of d (all
@@ -244,269 +373,253 @@ __device__ __forceinline__ uint32_t keep_bits(const Lane& l, int64_t s, int lane
     }
 }
 
-// Deltas of the cells of step s outside the field set to 0 (the logging
-// pass, which must not log an escape for such a cell).
-template <int RANK>
-__device__ __forceinline__ void mask_outside(int (&d)[32], const Lane& l, int64_t s, int lane)
-{
-    const uint32_t keep = keep_bits<RANK>(l, s, lane);
-#pragma unroll
-    for (int i = 0; i < 32; i++) d[i] &= __builtin_amdgcn_sbfe((int)keep, (uint32_t)i, 1u);
-}
-
-// ------------------------------------------------------------- one layer
-// In-plane part of the Lorenzo difference, after the difference along the
-// sweep dimension.  3-D: `a` is a plane difference; Dy then Dx give d.
-__device__ __forceinline__ void inplane3(const int (&a)[32], int (&d)[32], int lane)
+// ------------------------------------------------------------ one layer
+// In-plane part of the Lorenzo difference after the difference along the
+// sweep dimension, on packed values: A[i] holds cells i (low half) and i + 16.
+// 3-D: A[c] are rows 0 and 2, A[8 + c] rows 1 and 3; Dy, then Dx.
+__device__ __forceinline__ fz_short2 as_short2(uint32_t v) { return __builtin_bit_cast(fz_short2, v); }
+__device__ __forceinline__ uint32_t sub2(uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, as_short2(a) - as_short2(b)); }
+__device__ __forceinline__ void inplane3(uint32_t (&A)[16], int lane)
 {
     const int py = lane & 7, px = lane >> 3;
-    int b[32];
 #pragma unroll
-    for (int c = 0; c < 8; c++) {  // Dy; row 0 takes row 3 of lane-1 (0 for py == 0)
-        const int up = shift_up1_raw(a[24 + c]);
-        b[c] = a[c] - (py == 0 ? 0 : up);
+    for (int c = 0; c < 8; c++) {
+        // rows 0 and 2 take row 3 of lane-1 (0 for py == 0) and row 1
+        uint32_t up = (uint32_t)shift_up1_raw((int)A[8 + c]);
+        up = py == 0 ? 0u : up;
+        const uint32_t prev = __builtin_amdgcn_alignbit(A[8 + c], up, 16);
+        A[8 + c] = sub2(A[8 + c], A[c]);
+        A[c] = sub2(A[c], prev);
     }
 #pragma unroll
-    for (int r = 1; r < 4; r++)
+    for (int r = 0; r < 2; r++) {  // column 0 takes column 7 of lane-8 (0 for px == 0)
+        uint32_t left = (uint32_t)lane_value((int)A[8 * r + 7], lane - 8);
+        left = px == 0 ? 0u : left;
 #pragma unroll
-        for (int c = 0; c < 8; c++) b[8 * r + c] = a[8 * r + c] - a[8 * (r - 1) + c];
-#pragma unroll
-    for (int r = 0; r < 4; r++) {  // Dx; column 0 takes column 7 of lane-8 (0 for px == 0)
-        const int left = lane_value(b[8 * r + 7], lane - 8);
-        d[8 * r] = b[8 * r] - (px == 0 ? 0 : left);
-#pragma unroll
-        for (int c = 1; c < 8; c++) d[8 * r + c] = b[8 * r + c] - b[8 * r + c - 1];
-    }
-}
-
-// 2-D: `b` holds the two row differences of the step (rows 2s, 2s+1); Dx
-// gives d.
-__device__ __forceinline__ void inplane2(const int (&b)[32], int (&d)[32], int lane)
-{
-#pragma unroll
-    for (int r = 0; r < 2; r++) {  // Dx; column 0 takes column 15 of lane-1 (0 at lane 0)
-        const int left = shift_up1_raw(b[16 * r + 15]);
-        d[16 * r] = b[16 * r] - (lane == 0 ? 0 : left);
-#pragma unroll
-        for (int c = 1; c < 16; c++) d[16 * r + c] = b[16 * r + c] - b[16 * r + c - 1];
+        for (int c = 7; c > 0; c--) A[8 * r + c] = sub2(A[8 * r + c], A[8 * r + c - 1]);
+        A[8 * r] = sub2(A[8 * r], left);
     }
 }
 
-// `h` holds the halo (3-D: the plane before the layer; 2-D: the two rows
-// before it, of which the second is used; 1-D: unused) and `v` the first
-// step, both loaded ahead of time.  The plane-b word of step t goes to
-// Wl[(b * 4 + t) * 64 + lane] in LDS (brick (k, b, lane) = its 4 words) and
-// nz[b] collects their OR for the flags.
-// Returns whether some delta of the layer needs an escape (only the ESC pass
-// logs them).
-template <int RANK, bool VEC4, bool ESC, int QM = kQuantGrid>
-__device__ __forceinline__ bool layer(const float* __restrict__ x, const Geom& g, const Lane& l, int k, Quant inv,
-                                      int lane, float (&h)[32], float (&v)[32], uint32_t* Wl, uint32_t (&nz)[16],
-                                      float& facc, EscapeLog& log)
+// 2-D: A[c] holds column c of the step's two rows; Dx.
+__device__ __forceinline__ void inplane2(uint32_t (&A)[16], int lane)
 {
-    // the logging pass (ESC) keeps one copy of the step code: it runs rarely
-    // and must not add to the register budget of the fast pass
-    bool esc = false;
+    uint32_t left = (uint32_t)shift_up1_raw((int)A[15]);  // column 0 takes column 15 of lane-1 (0 at lane 0)
+    left = lane == 0 ? 0u : left;
 #pragma unroll
-    for (int b = 0; b < 16; b++) nz[b] = 0u;
-    // previous-step state: 3-D plane (32), 2-D row (16), 1-D last value (uniform)
-    int qprev[32];
-    int carry1 = 0;
-    if (k == 0 || RANK == 1) {
+    for (int c = 15; c > 0; c--) A[c] = sub2(A[c], A[c - 1]);
+    A[0] = sub2(A[0], left);
+}
+
+// One step: its difference along the sweep dimension (a; 1-D: its deltas) ->
+// bit planes P.  keep: the cells inside the field (the codes of the others
+// are cleared: bit i of each plane word is code i).  Returns whether some
+// difference does not fit the packed arithmetic; on the 2eb grid with every
+// |q| small (facc) none can, and the check is skipped.
+template <int RANK, int QM>
+__device__ __forceinline__ bool step_planes(const int (&a)[32], bool edge, uint32_t keep, float facc, int lane,
+                                            uint32_t (&P)[16])
+{
+    constexpr int lim = packed_limit<RANK>();
+    bool wide = false;
+    if (QM != kQuantGrid || __ballot(!(facc < (float)(lim / 2))) != 0) {
+        int mn = 0, mx = 0;
 #pragma unroll
-        for (int i = 0; i < 32; i++) qprev[i] = 0;
-        if (RANK == 1 && k > 0) {
+        for (int i = 0; i < 32; i += 2) {
+            mx = max(mx, max(a[i], a[i + 1]));
+            mn = min(mn, min(a[i], a[i + 1]));
+        }
+        wide = __ballot(mx > lim || mn < -lim) != 0;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; i++) P[i] = __builtin_amdgcn_perm((uint32_t)a[i + 16], (uint32_t)a[i], 0x05040100u);
+    if (RANK == 3) inplane3(P, lane);
+    else if (RANK == 2) inplane2(P, lane);
+    sign_magnitude(P);
+    transpose16(P);
+    if (edge) {
+#pragma unroll
+        for (int b = 0; b < 16; b++) P[b] &= keep;
+    }
+    return wide;
+}
+
+// Difference along the sweep dimension of a step with integers q against the
+// step before it (qp).  3-D: the plane before; 2-D: row 1 of the step before,
+// then row 0.
+template <int RANK>
+__device__ __forceinline__ void sweep_diff(const int (&q)[32], const int (&qp)[32], int (&a)[32])
+{
+#pragma unroll
+    for (int i = 0; i < 32; i++) a[i] = q[i] - (RANK == 3 ? qp[i] : i < 16 ? qp[16 + i] : q[i - 16]);
+}
+
+// Layer k, its steps in order upwards or downwards (DOWN); `h` and `v` hold
+// what prefetch loaded.  W[b][t]: the plane-b word of step 4k + t (the brick
+// of this lane's patch).  Returns whether the layer has to be coded out of
+// line.
+template <int RANK, bool VEC4, int QM, bool DOWN>
+__device__ __forceinline__ bool layer_fast(const float* __restrict__ x, const Geom& g, const Lane& l, int k, Quant inv,
+                                           int lane, float (&h)[32], float (&v)[32], uint4* tile, uint32_t (&W)[kPlanes][4],
+                                           float& facc)
+{
+    bool wide = false;
+    int qp[32];     // UP: the step before the one coded; DOWN: the one coded
+    int carry = 0;  // 1-D: the value before the step
+    if constexpr (RANK == 1) {
+        carry = QM == kQuantGrid ? kRoundBias : 0;
+        if (k > 0) {
             uint32_t dummy = 0;
             const float xh = x[l.org[0] + (int64_t)kStepCodes * 4 * k - 1];
-            carry1 = QM == kQuantPw ? pw_quant(xh, inv) : QM == kQuantInt ? __float_as_int(xh) : prequant(xh, inv.inv, dummy);
+            if (QM == kQuantGrid) facc = __builtin_fabsf(xh * inv.inv);
+            carry += QM == kQuantPw ? pw_quant(xh, inv) : QM == kQuantInt ? __float_as_int(xh) : prequant(xh, inv.inv, dummy);
         }
-    } else if (RANK == 3) {
-        prequant32<QM>(h, inv, facc, qprev);
     } else {
-        int qh[32];
-        prequant32<QM>(h, inv, facc, qh);
-#pragma unroll
-        for (int c = 0; c < 16; c++) qprev[c] = qh[16 + c];
+        rows_to_patches<RANK>(h, lane, tile);
+        prequant32<QM, true>(h, inv, facc, qp);
     }
-#pragma unroll ESC ? 1 : 4
-    for (int t = 0; t < 4; t++) {
-        const int s = 4 * k + t;
+#pragma unroll
+    for (int it = 0; it < 4; it++) {
+        const int t = DOWN ? 3 - it : it, s = 4 * k + t;
         float vn[32];
-        if (t < 3) load_step<RANK, VEC4>(x, g, l, s + 1, vn);
+        const int sn = DOWN ? s - 2 : s + 1;  // DOWN: 4k - 1 at it = 2, the halo
+        if (it < 3) load_rows<RANK, VEC4>(x, g, l, sn, true, (sn & 3) == 3, lane, vn);
         // keep the steps apart: the scheduler must not pull the next step's
         // arithmetic up to its loads, which would wait on them right away
         __builtin_amdgcn_sched_barrier(0);
-        int q[32];
-        prequant32<QM>(v, inv, facc, q);
-        int d[32];
-        if (RANK == 3) {
-            int a[32];
-#pragma unroll
-            for (int i = 0; i < 32; i++) {
-                a[i] = q[i] - qprev[i];  // Dz
-                qprev[i] = q[i];
-            }
-            inplane3(a, d, lane);
-        } else if (RANK == 2) {
-            int b[32];
-#pragma unroll
-            for (int c = 0; c < 16; c++) {  // Dy against the previous row of the same lane
-                b[c] = q[c] - qprev[c];
-                b[16 + c] = q[16 + c] - q[c];
-                qprev[c] = q[16 + c];
-            }
-            inplane2(b, d, lane);
-        } else {
+        int q[32], a[32];
+        rows_to_patches<RANK>(v, lane, tile);
+        prequant32<QM, true>(v, inv, facc, q);
+        if constexpr (RANK == 1) {
             const int left = shift_up1_raw(q[31]);
-            d[0] = q[0] - (lane == 0 ? carry1 : left);
+            a[0] = q[0] - (lane == 0 ? carry : left);
 #pragma unroll
-            for (int m = 1; m < 32; m++) d[m] = q[m] - q[m - 1];
-            carry1 = __builtin_amdgcn_readlane(q[31], 63);
-        }
-        if (ESC) mask_outside<RANK>(d, l, s, lane);
-        uint32_t P[16];
-        esc |= finish_step<ESC>(d, P, log, (uint32_t)s * kStepCodes, lane);
-#pragma unroll
-        for (int bb = 0; bb < 16; bb++) {
-            Wl[(bb * 4 + t) * 64 + lane] = P[bb];
-            nz[bb] |= P[bb];
-        }
-        if (t < 3) {
-#pragma unroll
-            for (int i = 0; i < 32; i++) v[i] = vn[i];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return esc;
-}
-
-// Layer k swept downwards (fast path of odd layers, 2-D and 3-D).  An odd layer's halo is the top plane of the
-// layer below it, and an even layer's halo the top plane of an odd layer; in
-// this order each halo plane is loaded in the same iteration as by the wave
-// that owns it, so the second load is served by the cache.  `h` holds the top
-// step of the layer and `v` the one below it.  The deltas and words are those
-// of the forward sweep; escapes are only detected (the out-of-line pass logs
-// them in code order).
-template <int RANK, bool VEC4, int QM = kQuantGrid>
-__device__ __forceinline__ bool layer_rev(const float* __restrict__ x, const Geom& g, const Lane& l, int k, Quant inv,
-                                          int lane, float (&h)[32], float (&v)[32], uint32_t* Wl, uint32_t (&nz)[16],
-                                          float& facc, EscapeLog& log)
-{
-    static_assert(RANK >= 2, "the 1-D halo is one value");
-    bool esc = false;
-#pragma unroll
-    for (int b = 0; b < 16; b++) nz[b] = 0u;
-    int cq[32];  // q of the step being coded (3-D: its plane; 2-D: its two rows)
-    prequant32<QM>(h, inv, facc, cq);
-#pragma unroll
-    for (int it = 0; it < 4; it++) {
-        const int t = 3 - it, s = 4 * k + t;
-        float vn[32];
-        if (it < 3) load_step<RANK, VEC4>(x, g, l, s - 2, vn);  // s - 2 = 4k - 1 at it = 2: the halo
-        __builtin_amdgcn_sched_barrier(0);
-        int ql[32];  // q of step s - 1
-        prequant32<QM>(v, inv, facc, ql);
-        int d[32];
-        if (RANK == 3) {
-            int a[32];
-#pragma unroll
-            for (int i = 0; i < 32; i++) {
-                a[i] = cq[i] - ql[i];  // Dz
-                cq[i] = ql[i];
-            }
-            inplane3(a, d, lane);
+            for (int m = 1; m < 32; m++) a[m] = q[m] - q[m - 1];
+            carry = __builtin_amdgcn_readlane(q[31], 63);
+        } else if constexpr (DOWN) {
+            sweep_diff<RANK>(qp, q, a);
         } else {
-            int b[32];
-#pragma unroll
-            for (int c = 0; c < 16; c++) {  // Dy: row 2s against row 2s-1, row 2s+1 against row 2s
-                b[c] = cq[c] - ql[16 + c];
-                b[16 + c] = cq[16 + c] - cq[c];
-            }
-#pragma unroll
-            for (int i = 0; i < 32; i++) cq[i] = ql[i];
-            inplane2(b, d, lane);
+            sweep_diff<RANK>(q, qp, a);
         }
         uint32_t P[16];
-        esc |= finish_step<false>(d, P, log, (uint32_t)s * kStepCodes, lane);
+        wide |= step_planes<RANK, QM>(a, l.edge, l.edge ? keep_bits<RANK>(l, s, lane) : 0u, facc, lane, P);
 #pragma unroll
-        for (int bb = 0; bb < 16; bb++) {
-            Wl[(bb * 4 + t) * 64 + lane] = P[bb];
-            nz[bb] |= P[bb];
-        }
+        for (int b = 0; b < kPlanes; b++) W[b][t] = P[b];
+#pragma unroll
+        for (int i = 0; i < 32; i++) qp[i] = q[i];
         if (it < 3) {
 #pragma unroll
             for (int i = 0; i < 32; i++) v[i] = vn[i];
         }
         __builtin_amdgcn_sched_barrier(0);
     }
-    return esc;
+    return wide || (QM == kQuantGrid && __ballot(!(facc < kRoundLimit)) != 0);
 }
 
-// Whether layer k of a chunk is swept downwards.
+// In-plane part of the difference in 32 bits, in place (see inplane3, inplane2).
 template <int RANK>
-__device__ __forceinline__ bool swept_down(int k)
+__device__ __forceinline__ void inplane_wide(int (&d)[32], int lane)
 {
-    return RANK >= 2 && (k & 1);
-}
-
-// Load the first two steps that layer k of a chunk uses ahead of time: the
-// halo and the first step (upwards), or the top two steps (downwards).
-// Branch-free: both loads are always issued, and one that has nothing to
-// read (no layer k, the halo of layer 0 or of a 1-D layer) gets a range of 0
-// and returns zeros.  A branch here would merge the loads' uniform row
-// offsets at its join, where the compiler keeps them in vector registers and
-// then has to build a loop around every later load that uses them.  The
-// halo or top step is the one another wave reads again (cached), the other
-// one is streamed.
-template <int RANK, bool VEC4>
-__device__ __forceinline__ void prefetch(const float* __restrict__ x, const Geom& g, const Lane& l, int k,
-                                         float (&h)[32], float (&v)[32], bool down = false)
-{
-    const bool live = k < l.L, dn = down && live;
-    if (RANK == 1) {  // no halo step (a 1-D layer's halo is one value)
+    if (RANK == 3) {
+        const int py = lane & 7, px = lane >> 3;
 #pragma unroll
-        for (int i = 0; i < 32; i++) h[i] = 0.0f;
-    } else {
-        load_step_as<RANK, VEC4, false>(x, g, l, dn ? 4 * k + 3 : 4 * k - 1, live && (dn || k > 0), h);
+        for (int c = 0; c < 8; c++) {
+            const int up = shift_up1_raw(d[24 + c]);
+#pragma unroll
+            for (int r = 3; r > 0; r--) d[8 * r + c] -= d[8 * (r - 1) + c];
+            d[c] -= py == 0 ? 0 : up;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int left = lane_value(d[8 * r + 7], lane - 8);
+#pragma unroll
+            for (int c = 7; c > 0; c--) d[8 * r + c] -= d[8 * r + c - 1];
+            d[8 * r] -= px == 0 ? 0 : left;
+        }
+    } else if (RANK == 2) {
+#pragma unroll
+        for (int r = 0; r < 2; r++) {
+            const int left = shift_up1_raw(d[16 * r + 15]);
+#pragma unroll
+            for (int c = 15; c > 0; c--) d[16 * r + c] -= d[16 * r + c - 1];
+            d[16 * r] -= lane == 0 ? 0 : left;
+        }
     }
-    load_step_as<RANK, VEC4, RANK == 3>(x, g, l, dn ? 4 * k + 2 : 4 * k, live, v);
 }
 
-// Out-of-line layer pass for the uncommon case of a layer whose deltas need
-// escapes (computed again with the escape codes).  It loads its own inputs, writes the layer's bricks to Wl, logs the
-// escape pairs to `pairs` (at most `room` of them; null: count only) and
-// returns (escape count << 32) | max-|p| bits.  The geometry is read from the copy
-// in the scratch so that nothing large crosses the call.  It stays a real
-// call: inlined, its registers would push the fast path into spills, while
-// as a call the register saves happen only on this path.
-template <int RANK, bool VEC4, int QM = kQuantGrid>
-__device__ __noinline__ uint64_t layer_slow(const float* __restrict__ x, const uint8_t* scr,
-                                            int64_t c, int k, Quant inv, int lane, uint32_t* Wl, uint32_t* pairs,
-                                            int room)
+// Layer k of chunk c in 32-bit arithmetic, with escapes: its bricks go to the
+// workgroup's slot, its escapes to the slot's list (log_escapes).  Returns
+// their number.  It loads its own inputs and reads the geometry from its copy
+// in the scratch, so that little crosses the call; a real call, as its
+// registers would push the common path into spills.
+template <int RANK, bool VEC4, int QM>
+__device__ __noinline__ uint32_t layer_wide(const float* __restrict__ x, const uint8_t* scr, int64_t c, int k, Quant inv,
+                                            int lane, uint8_t* slot, LdsState* S)
 {
     const Geom g = *reinterpret_cast<const Geom*>(scr + kScratchGeomOff);
     const Lane l = lane_geo<RANK>(g, c, lane);
-    float h[32], v[32];
-    prefetch<RANK, VEC4>(x, g, l, k, h, v);
-    uint32_t nz[16];
-    float facc = 0.0f;
-    EscapeLog log{pairs, 0, room};
-    layer<RANK, VEC4, true, QM>(x, g, l, k, inv, lane, h, v, Wl, nz, facc, log);
-    return ((uint64_t)(uint32_t)log.count << 32) | __float_as_uint(facc);
+    uint2* pairs = reinterpret_cast<uint2*>(slot + kSlotPairs);
+    uint32_t* brick = reinterpret_cast<uint32_t*>(slot) + 4 * (k * kPlanes * kPatches + lane);
+    uint32_t total = 0;
+    float facc = 0.0f, v[32];
+    int qp[32], carry = 0;
+#pragma unroll
+    for (int i = 0; i < 32; i++) qp[i] = 0;
+    if (k > 0) {
+        if (RANK == 1) {
+            uint32_t dummy = 0;
+            const float xh = x[l.org[0] + (int64_t)kStepCodes * 4 * k - 1];
+            carry = QM == kQuantPw ? pw_quant(xh, inv) : QM == kQuantInt ? __float_as_int(xh) : prequant(xh, inv.inv, dummy);
+        } else {
+            load_patch<RANK, VEC4>(x, g, l, 4 * k - 1, v);
+            prequant32<QM, false>(v, inv, facc, qp);
+        }
+    }
+#pragma unroll 1
+    for (int t = 0; t < 4; t++) {
+        const int s = 4 * k + t;
+        load_patch<RANK, VEC4>(x, g, l, s, v);
+        int q[32], d[32];
+        prequant32<QM, false>(v, inv, facc, q);
+        if (RANK == 1) {
+            const int left = shift_up1_raw(q[31]);
+            d[0] = q[0] - (lane == 0 ? carry : left);
+#pragma unroll
+            for (int m = 1; m < 32; m++) d[m] = q[m] - q[m - 1];
+            carry = __builtin_amdgcn_readlane(q[31], 63);
+        } else {
+            sweep_diff<RANK == 1 ? 2 : RANK>(q, qp, d);
+#pragma unroll
+            for (int i = 0; i < 32; i++) qp[i] = q[i];
+            inplane_wide<RANK>(d, lane);
+        }
+        const uint32_t keep = l.edge ? keep_bits<RANK>(l, s, lane) : ~0u;
+        total += log_escapes(d, keep, s, lane, S, pairs);
+        uint32_t P[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) P[i] = __builtin_amdgcn_perm((uint32_t)d[i + 16], (uint32_t)d[i], 0x05040100u);
+        sign_magnitude(P);
+        transpose16(P);
+#pragma unroll
+        for (int b = 0; b < 16; b++) brick[4 * 64 * b + t] = P[b] & keep;
+    }
+    return total;
 }
 
 // Rare path: a step saw NaN/Inf or |x*inv| >= 2^31.  Re-read the layer's
 // cells and classify them the way the format defines the status bits
-// (halo values belong to the previous layer, which reports them).
-__device__ __forceinline__ uint32_t classify_errors(const float* __restrict__ x, const uint8_t* scr,
-                                                 int64_t c, int k, Quant inv, int lane)
+// (halo values belong to the layer below, which reports them).  A real call,
+// with the geometry read from its copy in the scratch, so that nothing of it
+// adds to the registers of the common path.
+__device__ __noinline__ uint32_t classify_errors(const float* __restrict__ x, const uint8_t* scr, int64_t c, int wave,
+                                                 float inv, int lane)
 {
     const Geom g = *reinterpret_cast<const Geom*>(scr + kScratchGeomOff);
     int64_t o[3], e[3];
     chunk_box(g, c, o, e);
     uint32_t err = 0;
     for (int t = 0; t < 4; t++) {
-        const int s = 4 * k + t;
+        const int s = 4 * wave + t;
         for (int m = 0; m < 32; m++) {
             int64_t r0 = 0, r1 = 0, r2 = 0;
             if (g.rank == 3) { r0 = s; r1 = 4 * (lane % 8) + m / 8; r2 = 8 * (lane / 8) + m % 8; }
@@ -515,35 +628,33 @@ __device__ __forceinline__ uint32_t classify_errors(const float* __restrict__ x,
             if (r0 >= e[0] || r1 >= e[1] || r2 >= e[2]) continue;
             const float v = x[((o[0] + r0) * g.n[1] + o[1] + r1) * g.n[2] + o[2] + r2];
             if (!__builtin_isfinite(v)) err |= kErrNonfinite;
-            else if (!(__builtin_fabsf(v * inv.inv) < 2147483648.0f)) err |= kErrEbRange;
+            else if (!(__builtin_fabsf(v * inv) < 2147483648.0f)) err |= kErrEbRange;
         }
     }
+#pragma unroll
+    for (int sh = 32; sh > 0; sh >>= 1) err |= (uint32_t)__shfl_xor((int)err, sh);
     return err;
 }
 
-
 // ------------------------------------------------------------ one chunk
-// Workgroup-shared state of a compression workgroup (4 waves, one chunk).
-struct CompressLds {
-    uint32_t err;
-    uint32_t nnz[kLayers], nout[kLayers];
-    uint32_t arrived;  // waves whose layer of the current chunk is done
-    uint64_t ticket;
-    uint64_t excl;  // offset of the chunk being placed (16-B units), from the look-back
-    // per wave: the bricks of its layer (as plane-step words)
-    uint32_t w[kLayers][kPlanes * 4 * 64];
+// Payload of the chunk whose layers' counts are in S (16-B units): its nonzero
+// bricks, then its escape pairs padded to 16 bytes (none when the chunk holds
+// more than kChunkOutlierCap escapes: the stream then carries the OUTLIER_CAP
+// status).
+struct ChunkSum {
+    uint32_t bricks, esc, kept;
 };
-
-// Payload size of the chunk in S (16-B units): its nonzero bricks, then its
-// escape pairs padded to 16 bytes (none when the chunk holds more than
-// kChunkOutlierCap escapes: the stream then carries the OUTLIER_CAP status).
-__device__ __forceinline__ uint32_t chunk_units(const CompressLds& S)
+__device__ __forceinline__ ChunkSum chunk_sum(const CompressLds& S, int par)
 {
-    const uint32_t tn = S.nnz[0] + S.nnz[1] + S.nnz[2] + S.nnz[3];
-    const uint32_t to = S.nout[0] + S.nout[1] + S.nout[2] + S.nout[3];  // each at most 8192: no overflow
-    const uint32_t kept = to > (uint32_t)kChunkOutlierCap ? 0u : to;
-    return tn + (kept + 1) / 2;
+    ChunkSum c;
+    c.bricks = S.nnz[par][0] + S.nnz[par][1] + S.nnz[par][2] + S.nnz[par][3];
+    c.esc = S.nout[par][0] + S.nout[par][1] + S.nout[par][2] + S.nout[par][3];  // each at most 8192: no overflow
+    c.bricks = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.bricks);
+    c.esc = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.esc);
+    c.kept = c.esc > (uint32_t)kChunkOutlierCap ? 0u : c.esc;
+    return c;
 }
+__device__ __forceinline__ uint32_t chunk_units(const ChunkSum& c) { return c.bricks + (c.kept + 1) / 2; }
 
 // Chunk state words are read and written with agent-scope atomics: the
 // workgroups that publish and read them run on different XCDs, whose L2
@@ -557,239 +668,223 @@ __device__ __forceinline__ uint64_t peek_state(const uint64_t* p)
     return __hip_atomic_load(const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-
-// Tail of a wave's layer: the data-dependent status bits (NaN/Inf or an
-// overflowing product, seen in facc), the flags of the
-// zero-block encoder (one ballot per bit plane, F; lane b < 16 gets F[b] in
-// `myflag`, which stage_chunk stores), and the layer's counts in S.  Returns
-// the layer's escape count.
-__device__ __forceinline__ int layer_flags(const float* __restrict__ x, const uint8_t* __restrict__ scr, const Geom& g,
-                                           int64_t c, int wave, int lane, Quant inv, const uint32_t (&nz)[16],
-                                           float facc, const EscapeLog& log, CompressLds& S, uint64_t (&F)[16],
-                                           uint64_t& myflag)
+// Flag word of one bit plane of a layer: the lanes with a nonzero brick.
+__device__ __forceinline__ uint64_t plane_flags(const uint32_t (&w)[4])
 {
-    uint32_t err = 0;
-    if (__ballot(!(facc < 2147483648.0f))) {  // NaN, Inf or |x*inv| >= 2^31 somewhere in the layer
-        err = classify_errors(x, scr, c, wave, inv, lane);
-#pragma unroll
-        for (int sh = 32; sh > 0; sh >>= 1) err |= (uint32_t)__shfl_xor((int)err, sh);
-    }
-    const int nout = log.count;
-
-    // flags of the zero-block encoder: one ballot per bit plane
-    uint32_t nnz = 0;
-    myflag = 0;
-#pragma unroll
-    for (int b = 0; b < 16; b++) {
-        F[b] = __ballot(nz[b] != 0u);
-        nnz += __popcll(F[b]);
-        myflag = lane == b ? F[b] : myflag;
-    }
-    if (lane == 0) {
-        S.nnz[wave] = nnz;
-        S.nout[wave] = (uint32_t)nout;
-        if (err) atomicOr(&S.err, err);
-        // the chunk's last wave to get here publishes its size at once: a
-        // size published after the workgroup barrier would wait for this
-        // workgroup's look-back, and other look-backs for it in turn
-        if (__hip_atomic_fetch_add(&S.arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == kLayers - 1) {
-            S.arrived = 0;  // the next chunk's waves arrive after a barrier
-            publish_state(reinterpret_cast<uint64_t*>(const_cast<uint8_t*>(scr) + kScratchStateOff) + c,
-                          kFlagAgg | chunk_units(S));
-        }
-    }
-    return nout;
+    return __ballot((w[0] | w[1] | w[2] | w[3]) != 0u);
 }
 
-// A layer of a chunk cut by the field's edge, after the fast pass: its
-// cells outside the field were loaded as other chunks' values (or zeros past
-// the field's end), so their codes are cleared in the layer's plane words in
-// LDS (bit i of each word is code i of the lane's patch); the caller then
-// gathers the flags' nonzero bits again.  Such a cell's delta may also have
-// reported an escape; the layer has then taken the logging pass instead,
-// which zeroes those deltas before it looks for escapes.  A real call, with
-// plain arguments and LDS only: inlined, or with arrays passed to it, it
-// pushes the fast path into spills.  The words are addressed as LDS (a plain
-// pointer made them flat accesses, in 2-D each read waited for before its
-// write), a step's 16 words read before any is written back.
-typedef __attribute__((address_space(3))) uint32_t LdsWord;
-template <int RANK>
-__device__ __noinline__ void mask_layer(LdsWord* Wl, int64_t e0, int64_t e1, int64_t e2, uint32_t off, int k, int lane)
-{
-    Lane l;
-    l.ext[0] = e0;
-    l.ext[1] = e1;
-    l.ext[2] = e2;
-    l.off = off;
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-        const uint32_t keep = keep_bits<RANK>(l, 4 * k + t, lane);
-        uint32_t w[16];
-#pragma unroll
-        for (int b = 0; b < 16; b++) w[b] = Wl[(b * 4 + t) * 64 + lane];
-#pragma unroll
-        for (int b = 0; b < 16; b++) Wl[(b * 4 + t) * 64 + lane] = w[b] & keep;
-    }
-}
-
-// Wave `wave`'s layer of chunk c: bricks into S.w[wave], its brick and
-// escape counts into S.  `h` / `v` hold the prefetched halo and first step
-// (the top two steps of a layer swept downwards).  F receives the layer's per-plane ballots and `myflag` the
-// flag word lane b < 16 stores; returns the layer's escape count.
+// Wave `wave`'s layer of chunk c: its bricks in W, its counts in S.  The
+// chunk's last wave to get here publishes its size at once: a size published
+// after the workgroup barrier would wait for this workgroup's look-back, and
+// other look-backs for it in turn.
 template <int RANK, bool VEC4, int QM = kQuantGrid>
-__device__ __forceinline__ int chunk_layer(const float* __restrict__ x, const uint8_t* __restrict__ scr, const Geom& g,
-                                           int64_t c, const Lane& l, int wave, int lane, Quant inv, float (&h)[32],
-                                           float (&v)[32], CompressLds& S, uint64_t (&F)[16], uint64_t& myflag)
+__device__ __forceinline__ void chunk_layer(const float* __restrict__ x, const uint8_t* __restrict__ scr, const Geom& g,
+                                            int64_t c, const Lane& l, int wave, int lane, int par, Quant inv,
+                                            float (&h)[32], float (&v)[32], uint8_t* slot, CompressLds& S,
+                                            uint32_t (&W)[kPlanes][4])
 {
-    uint32_t nz[16];
-    float facc = 0.0f;
-    uint32_t* Wl = S.w[wave];
-    EscapeLog log{nullptr, 0, 0};
-    if (wave < l.L) {
-        bool slow;
-        if constexpr (RANK >= 2) {
-            slow = swept_down<RANK>(wave)
-                       ? layer_rev<RANK, VEC4, QM>(x, g, l, wave, inv, lane, h, v, Wl, nz, facc, log)
-                       : layer<RANK, VEC4, false, QM>(x, g, l, wave, inv, lane, h, v, Wl, nz, facc, log);
-            if (!slow && l.edge)  // uniform: clear the codes of cells outside the field
-                mask_layer<RANK>((LdsWord*)Wl, l.ext[0], l.ext[1], l.ext[2], l.off, wave, lane);
-        } else {
-            // 1-D: only a field's last chunk is cut by its edge; it takes the
-            // logging pass, which masks the deltas itself (a mask call here
-            // measured as spills in the 1-D fast path)
-            slow = layer<RANK, VEC4, false, QM>(x, g, l, wave, inv, lane, h, v, Wl, nz, facc, log) || l.edge;
-        }
-        if (slow) {  // escapes to log
-            const uint64_t r = layer_slow<RANK, VEC4, QM>(x, scr, c, wave, inv, lane, Wl, nullptr, 0);
-            log.count = (int)(r >> 32);
-            facc = __builtin_elementwise_maximum(facc, __uint_as_float((uint32_t)r));
-        }
-        if (slow || l.edge) {  // the layer's words were rewritten in LDS: their nonzero bits again
+    uint32_t nout = 0;
+    if (4 * wave < l.live) {
+        float facc = 0.0f;
+        bool wide;
+        if (swept_down<RANK>(wave)) wide = layer_fast<RANK, VEC4, QM, RANK >= 2>(x, g, l, wave, inv, lane, h, v, S.tile[wave], W, facc);
+        else wide = layer_fast<RANK, VEC4, QM, false>(x, g, l, wave, inv, lane, h, v, S.tile[wave], W, facc);
+        if (wide) {
+            nout = layer_wide<RANK, VEC4, QM>(x, scr, c, wave, inv, lane, slot, (LdsState*)&S);
+            const uint4* brick = reinterpret_cast<const uint4*>(slot) + wave * kPlanes * kPatches + lane;
 #pragma unroll
-            for (int b = 0; b < 16; b++)
-                nz[b] = Wl[(b * 4) * 64 + lane] | Wl[(b * 4 + 1) * 64 + lane] | Wl[(b * 4 + 2) * 64 + lane] |
-                        Wl[(b * 4 + 3) * 64 + lane];
+            for (int b = 0; b < kPlanes; b++) {
+                const uint4 w = brick[64 * b];
+                W[b][0] = w.x; W[b][1] = w.y; W[b][2] = w.z; W[b][3] = w.w;
+            }
+        }
+        if (QM != kQuantInt && __ballot(!(facc < 2147483648.0f))) {  // NaN, Inf or |x*inv| >= 2^31 somewhere
+            const uint32_t err = classify_errors(x, scr, c, wave, inv.inv, lane);
+            if (lane == 0 && err) atomicOr(&S.err[par], err);
         }
     } else {
 #pragma unroll
-        for (int b = 0; b < 16; b++) nz[b] = 0u;
+        for (int b = 0; b < kPlanes; b++) W[b][0] = W[b][1] = W[b][2] = W[b][3] = 0u;
     }
-    return layer_flags(x, scr, g, c, wave, lane, inv, nz, facc, log, S, F, myflag);
+    uint32_t nnz = 0;
+#pragma unroll
+    for (int b = 0; b < kPlanes; b++) nnz += (uint32_t)__builtin_popcountll(plane_flags(W[b]));
+    if (lane == 0) {
+        S.nnz[par][wave] = nnz;
+        S.nout[par][wave] = nout;
+        if (__hip_atomic_fetch_add(&S.arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == kLayers - 1) {
+            S.arrived = 0;  // the next chunk's waves arrive after a barrier
+            publish_state(reinterpret_cast<uint64_t*>(const_cast<uint8_t*>(scr) + kScratchStateOff) + c,
+                          kFlagAgg | chunk_units(chunk_sum(S, par)));
+        }
+    }
 }
 
 // polls of a look-back before it gives up (each poll sleeps about 64 cycles
 // and waits for a load that bypasses the L2; far beyond any real wait)
 constexpr int kLookbackSpins = 1 << 18;
 
+// The states of the chunks before c, read ahead of a look-back (issued before
+// the next chunk's layer, used after it): kAhead windows of 64.
+constexpr int kAhead = 4;
+struct StatesAhead {
+    uint64_t v[kAhead];
+};
+__device__ __forceinline__ void states_ahead(const uint64_t* state, int64_t c, int lane, StatesAhead& a)
+{
+#pragma unroll
+    for (int i = 0; i < kAhead; i++) {
+        const int64_t j = c - 1 - 64 * i - lane;
+        a.v[i] = j >= 0 ? peek_state(state + j) : kFlagIncl;  // before chunk 0: inclusive prefix 0
+    }
+}
+
 // Exclusive prefix of chunk c's payload size (Sec. 3.4: the offset of its
 // data blocks), by one wave: the published states of chunks c-1, c-2, ... are
-// read 64 at a time and summed back to the nearest chunk that published its
-// inclusive prefix.  Chunks that have not published their size yet are polled
-// until they do (every chunk before c was taken by a running workgroup, which
-// publishes its size without waiting for anything).  Returns false if the
-// polls ran out (the stream is then marked with an internal error).
-__device__ __forceinline__ bool lookback(const uint64_t* state, int64_t c, int lane, uint64_t& excl)
+// taken 64 at a time (the first windows as read ahead) and summed back to the
+// nearest chunk that published its inclusive prefix.  Chunks that have not
+// published their size yet are polled until they do (every chunk before c was
+// taken by a running workgroup, which publishes its size without waiting for
+// anything).  Returns false if the polls ran out (the stream is then marked
+// with an internal error).
+__device__ __forceinline__ bool lookback(const uint64_t* state, int64_t c, int lane, const StatesAhead& a, uint64_t& excl)
 {
     uint64_t sum = 0;
-    for (int64_t hi = c; hi > 0; hi -= 64) {
-        const int64_t i = hi - 1 - lane;  // lane 0 reads the nearest chunk
-        uint64_t v = i >= 0 ? peek_state(state + i) : kFlagIncl;  // before chunk 0: inclusive prefix 0
+    // one window; 1: done (excl is set), 0: go on, -1: gave up
+    auto window = [&](int64_t hi, uint64_t v) -> int {
+        const int64_t i = hi - 1 - lane;  // lane 0 has the nearest chunk
         for (int spin = 0;; spin++) {
             const uint64_t incl = __ballot((v & ~kValueMask) == kFlagIncl);
             const int first = incl ? __builtin_ctzll(incl) : 64;
             const uint64_t below = first == 64 ? ~0ull : (1ull << first) - 1;
             const uint64_t miss = __ballot((v & ~kValueMask) == 0) & below;
             if (!miss) {
-                uint64_t t = lane <= first ? (v & kValueMask) : 0;
-#pragma unroll
-                for (int sh = 32; sh > 0; sh >>= 1) t += __shfl_xor(t, sh);
-                sum += t;
+                // sizes (below 2^13 each) summed over the lanes, then the prefix
+                const int t = wave_incl_scan(lane < first ? (int)(uint32_t)v : 0);
+                sum += (uint32_t)__builtin_amdgcn_readlane(t, 63);
                 if (incl) {
-                    excl = sum;
-                    return true;
+                    const uint64_t p = v & kValueMask;
+                    sum += (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(p >> 32), first) << 32 |
+                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)p, first);
                 }
-                break;
+                excl = sum;
+                return incl ? 1 : 0;
             }
             if (spin >= kLookbackSpins) {
                 excl = 0;
-                return false;
+                return -1;
             }
             __builtin_amdgcn_s_sleep(1);
             if ((miss >> lane) & 1ull) v = peek_state(state + i);
         }
+    };
+    int64_t hi = c;
+#pragma unroll
+    for (int w = 0; w < kAhead; w++, hi -= 64) {
+        const int r = window(hi, a.v[w]);
+        if (r) return r > 0;
+    }
+    for (; hi > 0; hi -= 64) {
+        const int64_t i = hi - 1 - lane;
+        const int r = window(hi, i >= 0 ? peek_state(state + i) : kFlagIncl);
+        if (r) return r > 0;
     }
     excl = sum;
     return true;
 }
 
-// After a workgroup barrier that follows chunk_layer on all 4 waves: the
-// layer's flags go to the stream (stored only here, so that no wait before
-// the barrier covers them), the chunk's escape count to the table, the counts
-// to the header, and its payload is assembled in the workgroup's staging slot:
-// nonzero bricks in (layer, plane, patch) order, then the escape pairs padded
-// to 16 bytes.  A chunk may hold kChunkOutlierCap escapes wherever they fall;
-// past that the stream carries the OUTLIER_CAP status and no pairs are
-// written.  A layer with escapes is computed again out of line (its first
-// pass kept only the count) and writes its pairs behind those of the layers
-// before it.  The chunk's size was published by its last layer, before the
-// barrier.
-template <int RANK, bool VEC4, int QM = kQuantGrid>
-__device__ __forceinline__ void stage_chunk(const float* __restrict__ x, uint8_t* __restrict__ out,
-                                            const uint8_t* __restrict__ scr, const Geom& g,
-                                            int64_t c, int wave, int lane, Quant inv, const uint64_t (&F)[16],
-                                            uint64_t myflag, int nout, CompressLds& S, uint8_t* __restrict__ slot)
+typedef __attribute__((address_space(3))) fz_u32x4 LdsUnit;
+__device__ __forceinline__ void put_pair(LdsUnit* units, uint32_t j, uint2 p)
 {
-    if (lane < 16)
-        reinterpret_cast<uint64_t*>(out + g.flags_off + (int64_t)kFlagBytesPerChunk * c + 128 * wave)[lane] = myflag;
-    const uint32_t tn = S.nnz[0] + S.nnz[1] + S.nnz[2] + S.nnz[3];
-    const uint32_t to = S.nout[0] + S.nout[1] + S.nout[2] + S.nout[3];
-    const bool capped = to > (uint32_t)kChunkOutlierCap;
-    const uint32_t kept = capped ? 0u : to;
-    if (threadIdx.x == 0) {
-        reinterpret_cast<uint32_t*>(out + g.table_off + 8 * c)[1] = kept;
-        atomicAdd(reinterpret_cast<unsigned long long*>(out + kOffNnz), (unsigned long long)tn);
-        atomicAdd(reinterpret_cast<unsigned long long*>(out + kOffNout), (unsigned long long)kept);
-        const uint32_t err = S.err | (capped ? kErrOutlierCap : 0u);
-        if (err) atomicOr(reinterpret_cast<uint32_t*>(out + kOffStatus), err);
-        S.err = 0;
-        if (kept & 1u) *reinterpret_cast<uint2*>(slot + 16 * tn + 8 * kept) = make_uint2(0u, 0u);
-    }
-    uint64_t base = 0;
-    for (int w = 0; w < wave; w++) base += S.nnz[w];
-    uint32_t* Wl = S.w[wave];
+    __attribute__((address_space(3))) uint32_t* w = (__attribute__((address_space(3))) uint32_t*)units + 2 * j;
+    w[0] = p.x;
+    w[1] = p.y;
+}
+__device__ __forceinline__ void put_pair(fz_u32x4* units, uint32_t j, uint2 p)
+{
+    reinterpret_cast<uint2*>(units)[j] = p;
+}
+
+// After a workgroup barrier that follows chunk_layer on all waves: the layer's
+// flags go to the stream, the chunk's escape count to the table, and its
+// payload to `dst`: nonzero bricks in (layer, plane, patch) order, then the
+// escape pairs padded to 16 bytes.  dst: the LDS buffer, or the chunk's place
+// in the stream (a payload past kPayUnits, whose look-back was not put off).
+// A chunk may hold kChunkOutlierCap escapes wherever they fall; past that the
+// stream carries the OUTLIER_CAP status and no pairs are written.
+template <typename Unit>  // uint4 in LDS or in global memory
+__device__ __forceinline__ void store_chunk(uint8_t* __restrict__ out, const Geom& g, int64_t c, int wave, int lane, int par,
+                                            const ChunkSum& m, const uint32_t (&W)[kPlanes][4], const uint8_t* slot,
+                                            CompressLds& S, Unit* dst)
+{
+    uint32_t base = 0;
+    for (int w = 0; w < wave; w++) base += S.nnz[par][w];
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    uint32_t flo = 0, fhi = 0;  // lane b: the flag word of plane b
 #pragma unroll
-    for (int b = 0; b < 16; b++) {
-        if (F[b] == 0) continue;  // uniform: a bit plane without nonzero bricks
-        if ((F[b] >> lane) & 1ull) {
-            const uint64_t pos = base + mbcnt(F[b]);
-            const uint32_t* w = Wl + b * 4 * 64 + lane;
-            *reinterpret_cast<uint4*>(slot + 16 * pos) = make_uint4(w[0], w[64], w[128], w[192]);
-        }
-        base += __popcll(F[b]);
+    for (int b = 0; b < kPlanes; b++) {
+        // formed again (4 instructions) rather than kept over the placement:
+        // 16 flag words in scalar registers spilled others
+        const uint64_t f = plane_flags(W[b]);
+        const fz_u32x4 brick = {W[b][0], W[b][1], W[b][2], W[b][3]};
+        if (__builtin_amdgcn_inverse_ballot_w64(f)) dst[base + mbcnt(f)] = brick;
+        base += (uint32_t)__builtin_popcountll(f);
+        flo = lane == b ? (uint32_t)f : flo;
+        fhi = lane == b ? (uint32_t)(f >> 32) : fhi;
     }
-    if (nout && !capped) {  // rare: this layer's escape pairs, in code-index order
-        uint32_t first = 0;
-        for (int w = 0; w < wave; w++) first += S.nout[w];
-        uint32_t* pairs = reinterpret_cast<uint32_t*>(slot + 16 * tn) + 2 * first;
-        (void)layer_slow<RANK, VEC4, QM>(x, scr, c, wave, inv, lane, Wl, pairs, nout);
+    if (lane < kPlanes)
+        reinterpret_cast<uint2*>(out + g.flags_off + (int64_t)kFlagBytesPerChunk * c + 128 * wave)[lane] = make_uint2(flo, fhi);
+    if (threadIdx.x == 0) {
+        reinterpret_cast<uint32_t*>(out + g.table_off + 8 * c)[1] = m.kept;
+        const uint32_t err = atomicExch(&S.err[par], 0u) | (m.esc > (uint32_t)kChunkOutlierCap ? kErrOutlierCap : 0u);
+        if (err) atomicOr(reinterpret_cast<uint32_t*>(out + kOffStatus), err);
+    }
+    if (m.esc) {  // rare (the same on every wave)
+        if (m.kept && S.nout[par][wave]) {  // this layer's pairs, behind those of the layers before
+            uint32_t to = 0;
+            for (int w = 0; w < wave; w++) to += S.nout[par][w];
+            for (int s = 4 * wave; s < 4 * wave + 4; s++) {
+                const uint32_t n = S.esc_n[s], at = S.esc_at[s];
+                for (uint32_t j = (uint32_t)lane; j < n; j += 64) {
+                    const uint2 pr = reinterpret_cast<const uint2*>(slot + kSlotPairs)[at + j];
+                    put_pair(dst + m.bricks, to + j, pr);
+                }
+                to += n;
+            }
+        }
+        if (threadIdx.x == 0) {
+            if (m.kept & 1u) put_pair(dst + m.bricks, m.kept, make_uint2(0u, 0u));
+            S.esc_used = 0;
+        }
+        __syncthreads();  // the list is written again by the next chunk's layers
     }
 }
 
-// Placement of chunk p, staged in a workgroup's slot with `units` 16-B units
-// of payload, in two parts.  place_lookback, by one wave (any time after the
-// staging, before a barrier that precedes place_copy): the look-back finds
-// the offset, thread 0 publishes the inclusive prefix, writes the offset to
+// A workgroup barrier for data in LDS only: it waits for this wave's LDS
+// operations but leaves its loads and stores to memory in flight (the plain
+// barrier waits for those too, here the next chunk's first loads).
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Placement of chunk p, staged with `units` 16-B units of payload, in two
+// parts.  place_lookback, by one wave (any time after the staging, before a
+// barrier that precedes place_copy): the look-back finds the offset, thread 0 publishes the inclusive prefix, writes the offset to
 // the table and, for the field's last chunk, the stream's total size to the
 // header, and leaves the offset in S.excl.  A failed look-back marks the
 // stream with an internal error and still publishes (as if at offset 0), so
 // that no later chunk waits on this one; every offset stays inside the
 // stream's bound.
 __device__ __forceinline__ void place_lookback(uint8_t* __restrict__ out, uint8_t* __restrict__ scr, const Geom& g,
-                                               int64_t p, uint32_t units, CompressLds& S, int lane)
+                                               int64_t p, uint32_t units, const StatesAhead& ahead, CompressLds& S, int lane)
 {
     uint64_t* state = reinterpret_cast<uint64_t*>(scr + kScratchStateOff);
     uint64_t excl;
-    const bool ok = lookback(state, p, lane, excl);
+    const bool ok = lookback(state, p, lane, ahead, excl);
     if (lane == 0) {
         if (!ok) atomicOr(reinterpret_cast<uint32_t*>(out + kOffStatus), kErrInternal);
         const uint64_t at = ok ? excl : 0;
@@ -800,19 +895,47 @@ __device__ __forceinline__ void place_lookback(uint8_t* __restrict__ out, uint8_
     }
 }
 
-// place_copy, by the whole workgroup: the staged payload goes to its offset
-// (read from the cache: the slot was written one chunk earlier).  Ends with a
-// barrier, so the slot may be written again.
-__device__ __forceinline__ void place_copy(uint8_t* __restrict__ out, const Geom& g, uint32_t units,
-                                           const uint8_t* __restrict__ slot, const CompressLds& S)
+// place_copy, by the whole workgroup: the staged payload goes from LDS to its
+// offset.
+__device__ __forceinline__ void place_copy(uint8_t* __restrict__ out, const Geom& g, uint32_t units, const CompressLds& S)
 {
     const uint64_t excl = S.excl;
-    if (excl != ~0ull) {
-        const uint4* src = reinterpret_cast<const uint4*>(slot);
-        uint4* dst = reinterpret_cast<uint4*>(out + g.payload_off) + excl;
-        for (uint32_t i = threadIdx.x; i < units; i += blockDim.x) dst[i] = src[i];
+    if (excl == ~0ull) return;
+    uint4* dst = reinterpret_cast<uint4*>(out + g.payload_off) + excl;
+    for (uint32_t i = threadIdx.x; i < units; i += 64 * kLayers) dst[i] = S.pay[i];
+}
+
+// A chunk whose payload does not fit the LDS buffer: looked up and stored at
+// once, straight from the registers (after the barrier behind the previous
+// chunk's place_copy; ends with a barrier).
+__device__ __forceinline__ void place_now(uint8_t* __restrict__ out, uint8_t* __restrict__ scr, const Geom& g, int64_t c,
+                                          int wave, int lane, int par, const ChunkSum& m, const uint32_t (&W)[kPlanes][4],
+                                          const uint8_t* slot, CompressLds& S)
+{
+    if (wave == 0) {
+        StatesAhead ahead;
+        states_ahead(reinterpret_cast<const uint64_t*>(scr + kScratchStateOff), c, lane, ahead);
+        place_lookback(out, scr, g, c, chunk_units(m), ahead, S, lane);
     }
     __syncthreads();
+    const uint64_t excl = S.excl;
+    // a failed look-back marked the stream; its offset is 0, inside the bound
+    store_chunk(out, g, c, wave, lane, par, m, W, slot, S, reinterpret_cast<fz_u32x4*>(out + g.payload_off) + (excl == ~0ull ? 0 : excl));
+    lds_barrier();
+}
+
+// What a workgroup has stored of a field so far, added to the header's counts
+// once (by thread 0): one atomic per workgroup, not per chunk.
+struct Counts {
+    uint64_t bricks = 0, pairs = 0;
+};
+__device__ __forceinline__ void add_counts(uint8_t* __restrict__ out, Counts& n)
+{
+    if (threadIdx.x == 0) {
+        if (n.bricks) atomicAdd(reinterpret_cast<unsigned long long*>(out + kOffNnz), (unsigned long long)n.bricks);
+        if (n.pairs) atomicAdd(reinterpret_cast<unsigned long long*>(out + kOffNout), (unsigned long long)n.pairs);
+    }
+    n = Counts{};
 }
 
 // ------------------------------------------------- per-field pipeline steps

@@ -168,22 +168,15 @@ __device__ __forceinline__ int prequant(float v, const Quant& z, uint32_t& acc)
 
 typedef short fz_short2 __attribute__((ext_vector_type(2)));
 
-// Sign-magnitude 16-bit codes of d[i] and d[i+16] packed into one word
-// (Sec. 3.2: sign in the MSB, magnitude below), computed on the packed low
-// halves with 16-bit lane arithmetic.  `dmin` / `dmax` collect the range of
-// the deltas (one v_min3 / v_max3 per pair) so that one compare per step
-// finds deltas outside [-32767, 32767], whose codes the escape path then
-// replaces.
-__device__ __forceinline__ void pack_codes(const int (&d)[32], uint32_t (&P)[16], int& dmin, int& dmax)
+// Sign-magnitude 16-bit codes of packed 16-bit deltas, in place (Sec. 3.2:
+// sign in the MSB, magnitude below); -32768 becomes the escape code 0x8000.
+__device__ __forceinline__ void sign_magnitude(uint32_t (&P)[16])
 {
 #pragma unroll
     for (int i = 0; i < 16; i++) {
-        const uint32_t x = __builtin_amdgcn_perm((uint32_t)d[i + 16], (uint32_t)d[i], 0x05040100u);
-        const fz_short2 xs = __builtin_bit_cast(fz_short2, x);
-        const fz_short2 mag = __builtin_elementwise_max(xs, (fz_short2)0 - xs);
-        P[i] = __builtin_bit_cast(uint32_t, mag) | (x & 0x80008000u);
-        dmax = max(dmax, max(d[i], d[i + 16]));
-        dmin = min(dmin, min(d[i], d[i + 16]));
+        const fz_short2 x = __builtin_bit_cast(fz_short2, P[i]);
+        const fz_short2 mag = __builtin_elementwise_max(x, (fz_short2)0 - x);
+        P[i] = __builtin_bit_cast(uint32_t, mag) | (P[i] & 0x80008000u);
     }
 }
 constexpr uint32_t kEscapeLimit = 65534u;  // d + 32767 above this (as unsigned): an escape
