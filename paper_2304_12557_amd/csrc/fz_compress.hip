@@ -36,7 +36,12 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __res
         if (r.status) return;  // the same in every workgroup
         inv = Quant{r.inv, 0u, 0u};
     } else {
-        if (scr->pre_status) return;  // set before this launch: uniform across the grid
+        // set before this launch: uniform across the grid.  On integers the
+        // errors are those of the pass that wrote them, whose bits in the
+        // status word this kernel never sets itself.
+        if (QM == kQuantInt ? *reinterpret_cast<const uint32_t*>(out + kOffStatus) & (kErrNonfinite | kErrEbRange)
+                            : scr->pre_status)
+            return;
         inv = quant_of(out);
     }
     uint8_t* slot = scratch + g.scr_stage + kStageSlotBytes * (int64_t)blockIdx.x;
@@ -123,13 +128,12 @@ __global__ __launch_bounds__(256) void k_init(uint8_t* __restrict__ out, uint8_t
     init_field(out, scratch, g, h, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
-// the range pass; with `init` it also does k_init's work (a REL compression
-// starts with it)
+// the range pass, which also does k_init's work (a REL compression starts with
+// it)
 __global__ __launch_bounds__(256) void k_minmax(const float* __restrict__ x, int64_t n, uint8_t* __restrict__ out,
-                                                uint8_t* __restrict__ scratch, Geom g, HeaderImage h, int init)
+                                                uint8_t* __restrict__ scratch, Geom g, HeaderImage h)
 {
-    if (init)
-        init_field(out, scratch, g, h, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+    init_field(out, scratch, g, h, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
     minmax_block(x, n, scratch, g, blockIdx.x, gridDim.x);
 }
 
@@ -212,12 +216,13 @@ hipError_t launch_compress_f64(const double* x, uint8_t* out, const Geom& g, con
     return launch_main_int(out, g, st);
 }
 
-// the value range and the eb parameters of the relative bound (after k_init)
-static hipError_t launch_range(const float* x, uint8_t* out, uint8_t* scr, const Geom& g, double eb, hipStream_t st)
+// the value range (with k_init's work) and the eb parameters of the relative bound
+static hipError_t launch_range(const float* x, uint8_t* out, uint8_t* scr, const Geom& g, const HeaderImage& h, double eb,
+                               hipStream_t st)
 {
     const int64_t n = g.n[0] * g.n[1] * g.n[2];
     const int64_t blocks = minmax_blocks(n);
-    hipLaunchKernelGGL(k_minmax, dim3((unsigned)blocks), dim3(256), 0, st, x, n, out, scr, g, HeaderImage{}, 0);
+    hipLaunchKernelGGL(k_minmax, dim3((unsigned)blocks), dim3(256), 0, st, x, n, out, scr, g, h);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_params, dim3(1), dim3(256), 0, st, out, scr, g, eb, (int)blocks);
@@ -228,10 +233,9 @@ hipError_t launch_compress_global(const float* x, uint8_t* out, const Geom& g, c
                                   double eb, hipStream_t st)
 {
     uint8_t* scr = out + g.scratch_off;
-    hipError_t e = launch_init(out, scr, g, h, st);
+    hipError_t e = mode == FZ_EB_REL ? launch_range(x, out, scr, g, h, eb, st) : launch_init(out, scr, g, h, st);
     if (e != hipSuccess) return e;
-    if (mode == FZ_EB_REL && (e = launch_range(x, out, scr, g, eb, st)) != hipSuccess) return e;
-    if ((e = launch_face(x, out, g, st)) != hipSuccess) return e;
+    if ((e = launch_face(x, out, g, mode == FZ_EB_PWREL, st)) != hipSuccess) return e;
     return launch_main_int(out, g, st);
 }
 
@@ -247,7 +251,7 @@ hipError_t launch_compress(const float* x, uint8_t* out, uint8_t* scr, const Geo
         if (t && (e = mark(t->range_begin, st)) != hipSuccess) return e;
         const int64_t n = g.n[0] * g.n[1] * g.n[2];
         const int64_t blocks = minmax_blocks(n);
-        hipLaunchKernelGGL(k_minmax, dim3((unsigned)blocks), dim3(256), 0, st, x, n, out, scr, g, h, 1);
+        hipLaunchKernelGGL(k_minmax, dim3((unsigned)blocks), dim3(256), 0, st, x, n, out, scr, g, h);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         rel_eb = eb;
         nparts = (int)blocks;

@@ -291,6 +291,22 @@ __device__ __forceinline__ void chunk_box(const Geom& g, int64_t c, int64_t org[
     }
 }
 
+// The chunk of block b of n in kernels that read or write a field in place:
+// runs of kXcdRun chunks, side by side along the contiguous axis, go to one
+// XCD (blocks go round the 8 XCDs in turn), so that its L2 joins the lines that
+// neighbouring chunks share, while the blocks in flight still cover one stretch
+// of the field.  Measured, blocks in chunk order / runs of 8: 100x500x500
+// decompression 33.7 / 31.8 us, the same in double with its compression 201 /
+// 193 us, its field-global round trip 220 / 200 us (runs
+// of 4: 207, one run per XCD: 213 and 2 to 4 % slower than chunk order at whole lines).
+constexpr uint32_t kXcds = 8, kXcdRun = 8;
+__device__ __forceinline__ int64_t xcd_order(uint32_t b, int64_t n)
+{
+    constexpr uint32_t window = kXcds * kXcdRun;
+    if (b >= ((uint32_t)n & ~(window - 1))) return b;
+    return (b & ~(window - 1)) + kXcdRun * (b & (kXcds - 1)) + ((b / kXcds) & (kXcdRun - 1));
+}
+
 // stored layers of a chunk whose extent along the step dimension is e
 __device__ __forceinline__ int layers_of(int rank, int64_t e)
 {

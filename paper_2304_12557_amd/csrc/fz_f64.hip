@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kF64Threads) void k_params64(uint8_t* __restrict__ 
 
 // q = (int32) rint(x * inv) in double, round half to even, into the integer
 // buffer; NaN/Inf and |x * inv| >= 2^31 set the status bits and end the
-// pipeline (the compression kernel sees pre_status).
+// pipeline (the compression kernel sees the status).
 __global__ __launch_bounds__(kF64Threads) void k_prequant64(const double* __restrict__ x, int64_t n,
                                                            uint8_t* __restrict__ out, Geom g)
 {
@@ -178,24 +178,6 @@ __global__ __launch_bounds__(kF64Threads) void k_prequant64(const double* __rest
     }
 }
 
-// The pre_status of k_compress must see the errors of a pass that wrote the
-// integers (fp64 prequantization, the field-global faces): a second tiny
-// kernel copies the header's status there (a failed block cannot know that
-// the others finished).
-__global__ void k_pre_status(uint8_t* __restrict__ out, Geom g)
-{
-    if (threadIdx.x == 0) {
-        const uint32_t st = *reinterpret_cast<const uint32_t*>(out + kOffStatus);
-        if (st) reinterpret_cast<Scratch*>(out + g.scratch_off)->pre_status = st;
-    }
-}
-
-hipError_t launch_pre_status(uint8_t* out, const Geom& g, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_pre_status, dim3(1), dim3(64), 0, st, out, g);
-    return hipGetLastError();
-}
-
 hipError_t launch_f64_front(const double* x, uint8_t* out, const Geom& g, int mode, double eb, hipStream_t st)
 {
     const int64_t n = g.n[0] * g.n[1] * g.n[2];
@@ -211,8 +193,7 @@ hipError_t launch_f64_front(const double* x, uint8_t* out, const Geom& g, int mo
     int64_t blocks = (n / 4 + kF64Threads - 1) / kF64Threads;
     blocks = blocks < 1 ? 1 : blocks > 4096 ? 4096 : blocks;
     hipLaunchKernelGGL(k_prequant64, dim3((unsigned)blocks), dim3(kF64Threads), 0, st, x, n, out, g);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_pre_status(out, g, st);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------ decompression
