@@ -15,7 +15,7 @@ __global__ __launch_bounds__(512, 4) void k_decompress(const uint8_t* __restrict
 {
     __shared__ DecompressLds<8> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    decompress_chunk<RANK, float, 8>(s, sb, y, STREAM, g, d_err, blockIdx.x, wave, threadIdx.x & 63, S);
+    decompress_chunk<RANK, float, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g), wave, threadIdx.x & 63, S);
 }
 
 // the same with NW waves, one step each (fields with few chunks; launched

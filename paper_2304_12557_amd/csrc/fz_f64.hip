@@ -203,7 +203,7 @@ __global__ __launch_bounds__(512, 4) void k_decompress64(const uint8_t* __restri
 {
     __shared__ DecompressLds<8> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    decompress_chunk<RANK, double, 8>(s, sb, y, STREAM, g, d_err, blockIdx.x, wave, threadIdx.x & 63, S);
+    decompress_chunk<RANK, double, 8>(s, sb, y, STREAM, g, d_err, xcd_order(blockIdx.x, g.n_chunks), wave, threadIdx.x & 63, S);
 }
 
 __global__ void k_clear_err(uint32_t* p)
