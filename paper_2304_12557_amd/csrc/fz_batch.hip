@@ -118,7 +118,8 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_batch_compress(const Compre
             states_ahead(reinterpret_cast<const uint64_t*>(pscr + kScratchStateOff), pend_c, lane, ahead);
         }
         uint32_t W[kPlanes][4];
-        if (!skip) chunk_layer<RANK, VEC4>(x, scr, g, c, l, wave, lane, par, inv, h, v, slot, S, W);
+        Flags F;
+        if (!skip) chunk_layer<RANK, VEC4>(x, scr, g, c, l, wave, lane, par, inv, h, v, slot, S, W, F);
         if (pend_j >= 0 && wave == 0)  // the previous chunk's offset, while the other waves finish their layers
             place_lookback(as_global(jobs[pend_j].out), pscr, jobs[pend_j].g, pend_c, pend_units, ahead, S, lane);
         if (threadIdx.x == 0) S.ticket = tk;
@@ -129,18 +130,18 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_batch_compress(const Compre
         // zeros, so that the values are defined on one path)
         loaded = jn == j && !skip;
         prefetch<RANK, VEC4>(x, g, lane_geo<RANK>(g, loaded ? tn - J.chunk0 : c, lane), wave, lane, h, v, loaded);
-        const ChunkSum m = chunk_sum(S, par);
+        const ChunkSum m = chunk_sum(S, par, wave);
         if (pend_j >= 0) place_copy(as_global(jobs[pend_j].out), jobs[pend_j].g, pend_units, S);
         lds_barrier();  // the staged payload has been read by every wave
         pend_j = -1;
         if (!skip) {
             if (chunk_units(m) <= kPayUnits) {
-                store_chunk(out, g, c, wave, lane, par, m, W, slot, S, (LdsUnit*)S.pay);
+                store_chunk(out, g, c, wave, lane, par, m, W, F, slot, S, (LdsUnit*)S.pay);
                 pend_j = j;
                 pend_c = c;
                 pend_units = chunk_units(m);  // published by the chunk's last wave
             } else {
-                place_now(out, scr, g, c, wave, lane, par, m, W, slot, S);
+                place_now(out, scr, g, c, wave, lane, par, m, W, F, slot, S);
             }
             counts.bricks += m.bricks;
             counts.pairs += m.kept;

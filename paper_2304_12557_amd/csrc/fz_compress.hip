@@ -19,7 +19,7 @@ namespace fz {
 
 // rel_eb > 0: a REL compression whose range pass (k_minmax) left nparts
 // partial ranges; every workgroup folds them itself into the eb parameters
-// (the same bits everywhere) and workgroup 0 writes them to the header, so
+// (the same bits everywhere) and the first chunk's writes them to the header, so
 // no separate launch sits between the range pass and this kernel.
 template <int RANK, bool VEC4, int QM>
 __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __restrict__ x, uint8_t* __restrict__ out,
@@ -29,21 +29,12 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __res
     Scratch* scr = reinterpret_cast<Scratch*>(scratch);
     int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: keep it scalar
-    Quant inv;
-    if (rel_eb > 0.0) {
-        const RelParams r = fold_params(scratch, g, rel_eb, nparts);
-        if (blockIdx.x == 0 && threadIdx.x == 0) write_params(out, scratch, g, r);
-        if (r.status) return;  // the same in every workgroup
-        inv = Quant{r.inv, 0u, 0u};
-    } else {
-        // set before this launch: uniform across the grid.  On integers the
-        // errors are those of the pass that wrote them, whose bits in the
-        // status word this kernel never sets itself.
-        if (QM == kQuantInt ? *reinterpret_cast<const uint32_t*>(out + kOffStatus) & (kErrNonfinite | kErrEbRange)
-                            : scr->pre_status)
-            return;
-        inv = quant_of(out);
-    }
+    // set before this launch: uniform across the grid.  On integers the errors
+    // are those of the pass that wrote them, whose bits in the status word this
+    // kernel never sets itself.
+    if (QM == kQuantInt ? *reinterpret_cast<const uint32_t*>(out + kOffStatus) & (kErrNonfinite | kErrEbRange)
+                        : rel_eb == 0.0 && scr->pre_status)
+        return;
     uint8_t* slot = scratch + g.scr_stage + kStageSlotBytes * (int64_t)blockIdx.x;
 
     if (threadIdx.x == 0) {
@@ -62,6 +53,17 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __res
     float h[32], v[32];
     Lane l = lane_geo<RANK>(g, c, lane);
     prefetch<RANK, VEC4>(x, g, l, wave, lane, h, v);
+    // while the first chunk's loads are on their way (measured: 2 us, and the
+    // grid's first tickets on one address take up to 7)
+    Quant inv;
+    if (rel_eb > 0.0) {
+        const RelParams r = fold_params(scratch, g, rel_eb, nparts);
+        if (c == 0 && threadIdx.x == 0) write_params(out, scratch, g, r);
+        if (r.status) return;  // the same in every workgroup
+        inv = Quant{r.inv, 0u, 0u};
+    } else {
+        inv = quant_of(out);
+    }
     int64_t pend = -1;  // the chunk staged in LDS, not yet placed
     uint32_t pend_units = 0;
     Counts counts;
@@ -76,12 +78,13 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __res
         StatesAhead ahead;
         if (wave == 0) states_ahead(state, pend >= 0 ? pend : 0, lane, ahead);
         uint32_t W[kPlanes][4];
+        Flags F;
         // wave priority: the layer at the lowest, the serial part after it
         // (look-back, barrier, placement, staging) at a higher one, so that
         // its few instructions issue first when the CU's other workgroup is in
         // its layer
         __builtin_amdgcn_s_setprio(0);
-        chunk_layer<RANK, VEC4, QM>(x, scratch, g, c, l, wave, lane, par, inv, h, v, slot, S, W);
+        chunk_layer<RANK, VEC4, QM>(x, scratch, g, c, l, wave, lane, par, inv, h, v, slot, S, W, F);
         __builtin_amdgcn_s_setprio(3);
         // the previous chunk's offset: wave 0 looks back while the other waves finish their layers
         if (pend >= 0 && wave == 0) place_lookback(out, scratch, g, pend, pend_units, ahead, S, lane);
@@ -93,15 +96,15 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __res
         // loads that return zeros, so that the values are defined on one path)
         l = lane_geo<RANK>(g, more ? cn : c, lane);
         prefetch<RANK, VEC4>(x, g, l, wave, lane, h, v, more);
-        const ChunkSum m = chunk_sum(S, par);
+        const ChunkSum m = chunk_sum(S, par, wave);
         if (pend >= 0) place_copy(out, g, pend_units, S);
         lds_barrier();  // the staged payload has been read by every wave
         if (chunk_units(m) <= kPayUnits) {
-            store_chunk(out, g, c, wave, lane, par, m, W, slot, S, (LdsUnit*)S.pay);
+            store_chunk(out, g, c, wave, lane, par, m, W, F, slot, S, (LdsUnit*)S.pay);
             pend = c;
             pend_units = chunk_units(m);  // published by the chunk's last wave
         } else {
-            place_now(out, scratch, g, c, wave, lane, par, m, W, slot, S);
+            place_now(out, scratch, g, c, wave, lane, par, m, W, F, slot, S);
             pend = -1;
         }
         counts.bricks += m.bricks;

@@ -381,31 +381,33 @@ __device__ __forceinline__ fz_short2 as_short2(uint32_t v) { return __builtin_bi
 __device__ __forceinline__ uint32_t sub2(uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, as_short2(a) - as_short2(b)); }
 __device__ __forceinline__ void inplane3(uint32_t (&A)[16], int lane)
 {
-    const int py = lane & 7, px = lane >> 3;
+    const uint32_t below = (lane & 7) == 0 ? 0u : ~0u;  // whether a patch row comes before
+    const int px = lane >> 3;
+    uint32_t left[2];
 #pragma unroll
-    for (int c = 0; c < 8; c++) {
-        // rows 0 and 2 take row 3 of lane-1 (0 for py == 0) and row 1
-        uint32_t up = (uint32_t)shift_up1_raw((int)A[8 + c]);
-        up = py == 0 ? 0u : up;
+    for (int c = 7; c >= 0; c--) {
+        // rows 0 and 2 take row 3 of lane-1 (0 for py == 0; mask and shift are one instruction) and row 1
+        const uint32_t up = shift_up1_zero(A[8 + c]) & below;
         const uint32_t prev = __builtin_amdgcn_alignbit(A[8 + c], up, 16);
         A[8 + c] = sub2(A[8 + c], A[c]);
         A[c] = sub2(A[c], prev);
+        if (c == 7) {  // column 0 takes column 7 of lane-8 (0 for px == 0), asked for early
+            left[0] = (uint32_t)lane_value((int)A[7], lane - 8);
+            left[1] = (uint32_t)lane_value((int)A[15], lane - 8);
+        }
     }
 #pragma unroll
-    for (int r = 0; r < 2; r++) {  // column 0 takes column 7 of lane-8 (0 for px == 0)
-        uint32_t left = (uint32_t)lane_value((int)A[8 * r + 7], lane - 8);
-        left = px == 0 ? 0u : left;
+    for (int r = 0; r < 2; r++) {
 #pragma unroll
         for (int c = 7; c > 0; c--) A[8 * r + c] = sub2(A[8 * r + c], A[8 * r + c - 1]);
-        A[8 * r] = sub2(A[8 * r], left);
+        A[8 * r] = sub2(A[8 * r], px == 0 ? 0u : left[r]);
     }
 }
 
 // 2-D: A[c] holds column c of the step's two rows; Dx.
 __device__ __forceinline__ void inplane2(uint32_t (&A)[16], int lane)
 {
-    uint32_t left = (uint32_t)shift_up1_raw((int)A[15]);  // column 0 takes column 15 of lane-1 (0 at lane 0)
-    left = lane == 0 ? 0u : left;
+    const uint32_t left = shift_up1_zero(A[15]);  // column 0 takes column 15 of lane-1 (0 at lane 0)
 #pragma unroll
     for (int c = 15; c > 0; c--) A[c] = sub2(A[c], A[c - 1]);
     A[0] = sub2(A[0], left);
@@ -643,13 +645,17 @@ __device__ __noinline__ uint32_t classify_errors(const float* __restrict__ x, co
 // status).
 struct ChunkSum {
     uint32_t bricks, esc, kept;
+    uint32_t base;  // bricks of the layers before the wave's
 };
-__device__ __forceinline__ ChunkSum chunk_sum(const CompressLds& S, int par)
+__device__ __forceinline__ ChunkSum chunk_sum(const CompressLds& S, int par, int wave)
 {
     ChunkSum c;
-    c.bricks = S.nnz[par][0] + S.nnz[par][1] + S.nnz[par][2] + S.nnz[par][3];
+    uint32_t n[kLayers];
+#pragma unroll
+    for (int k = 0; k < kLayers; k++) n[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.nnz[par][k]);
+    c.bricks = n[0] + n[1] + n[2] + n[3];
+    c.base = (wave > 0 ? n[0] : 0u) + (wave > 1 ? n[1] : 0u) + (wave > 2 ? n[2] : 0u);
     c.esc = S.nout[par][0] + S.nout[par][1] + S.nout[par][2] + S.nout[par][3];  // each at most 8192: no overflow
-    c.bricks = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.bricks);
     c.esc = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.esc);
     c.kept = c.esc > (uint32_t)kChunkOutlierCap ? 0u : c.esc;
     return c;
@@ -668,11 +674,11 @@ __device__ __forceinline__ uint64_t peek_state(const uint64_t* p)
     return __hip_atomic_load(const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Flag word of one bit plane of a layer: the lanes with a nonzero brick.
-__device__ __forceinline__ uint64_t plane_flags(const uint32_t (&w)[4])
-{
-    return __ballot((w[0] | w[1] | w[2] | w[3]) != 0u);
-}
+// Flag words of a layer's bit planes (the lanes with a nonzero brick), the two
+// halves of plane b's on lane b.
+struct Flags {
+    uint32_t lo, hi;
+};
 
 // Wave `wave`'s layer of chunk c: its bricks in W, its counts in S.  The
 // chunk's last wave to get here publishes its size at once: a size published
@@ -682,7 +688,7 @@ template <int RANK, bool VEC4, int QM = kQuantGrid>
 __device__ __forceinline__ void chunk_layer(const float* __restrict__ x, const uint8_t* __restrict__ scr, const Geom& g,
                                             int64_t c, const Lane& l, int wave, int lane, int par, Quant inv,
                                             float (&h)[32], float (&v)[32], uint8_t* slot, CompressLds& S,
-                                            uint32_t (&W)[kPlanes][4])
+                                            uint32_t (&W)[kPlanes][4], Flags& F)
 {
     uint32_t nout = 0;
     if (4 * wave < l.live) {
@@ -708,15 +714,21 @@ __device__ __forceinline__ void chunk_layer(const float* __restrict__ x, const u
         for (int b = 0; b < kPlanes; b++) W[b][0] = W[b][1] = W[b][2] = W[b][3] = 0u;
     }
     uint32_t nnz = 0;
+    F = Flags{0u, 0u};
 #pragma unroll
-    for (int b = 0; b < kPlanes; b++) nnz += (uint32_t)__builtin_popcountll(plane_flags(W[b]));
+    for (int b = 0; b < kPlanes; b++) {
+        const uint64_t f = __ballot((W[b][0] | W[b][1] | W[b][2] | W[b][3]) != 0u);
+        nnz += (uint32_t)__builtin_popcountll(f);
+        set_lane(F.lo, b, (uint32_t)f);
+        set_lane(F.hi, b, (uint32_t)(f >> 32));
+    }
     if (lane == 0) {
         S.nnz[par][wave] = nnz;
         S.nout[par][wave] = nout;
         if (__hip_atomic_fetch_add(&S.arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == kLayers - 1) {
             S.arrived = 0;  // the next chunk's waves arrive after a barrier
             publish_state(reinterpret_cast<uint64_t*>(const_cast<uint8_t*>(scr) + kScratchStateOff) + c,
-                          kFlagAgg | chunk_units(chunk_sum(S, par)));
+                          kFlagAgg | chunk_units(chunk_sum(S, par, 0)));
         }
     }
 }
@@ -733,11 +745,10 @@ struct StatesAhead {
 };
 __device__ __forceinline__ void states_ahead(const uint64_t* state, int64_t c, int lane, StatesAhead& a)
 {
+    // branch-free (chunk numbers stay below 2^31): before chunk 0, chunk 0's
+    // state, which lookback takes for an inclusive prefix of 0
 #pragma unroll
-    for (int i = 0; i < kAhead; i++) {
-        const int64_t j = c - 1 - 64 * i - lane;
-        a.v[i] = j >= 0 ? peek_state(state + j) : kFlagIncl;  // before chunk 0: inclusive prefix 0
-    }
+    for (int i = 0; i < kAhead; i++) a.v[i] = peek_state(state + max((int)c - 1 - 64 * i - lane, 0));
 }
 
 // Exclusive prefix of chunk c's payload size (Sec. 3.4: the offset of its
@@ -752,13 +763,15 @@ __device__ __forceinline__ bool lookback(const uint64_t* state, int64_t c, int l
 {
     uint64_t sum = 0;
     // one window; 1: done (excl is set), 0: go on, -1: gave up
-    auto window = [&](int64_t hi, uint64_t v) -> int {
-        const int64_t i = hi - 1 - lane;  // lane 0 has the nearest chunk
+    auto window = [&](int hi, uint64_t v) -> int {
+        const int i = hi - 1 - lane;  // lane 0 has the nearest chunk
+        if (i < 0) v = kFlagIncl;     // before chunk 0: inclusive prefix 0
         for (int spin = 0;; spin++) {
-            const uint64_t incl = __ballot((v & ~kValueMask) == kFlagIncl);
+            const uint32_t flag = (uint32_t)(v >> 62);
+            const uint64_t incl = __ballot(flag == (uint32_t)(kFlagIncl >> 62));
             const int first = incl ? __builtin_ctzll(incl) : 64;
             const uint64_t below = first == 64 ? ~0ull : (1ull << first) - 1;
-            const uint64_t miss = __ballot((v & ~kValueMask) == 0) & below;
+            const uint64_t miss = __ballot(flag == 0u) & below;
             if (!miss) {
                 // sizes (below 2^13 each) summed over the lanes, then the prefix
                 const int t = wave_incl_scan(lane < first ? (int)(uint32_t)v : 0);
@@ -779,19 +792,16 @@ __device__ __forceinline__ bool lookback(const uint64_t* state, int64_t c, int l
             if ((miss >> lane) & 1ull) v = peek_state(state + i);
         }
     };
-    int64_t hi = c;
+    int hi = (int)c;
 #pragma unroll
     for (int w = 0; w < kAhead; w++, hi -= 64) {
         const int r = window(hi, a.v[w]);
         if (r) return r > 0;
     }
-    for (; hi > 0; hi -= 64) {
-        const int64_t i = hi - 1 - lane;
-        const int r = window(hi, i >= 0 ? peek_state(state + i) : kFlagIncl);
+    for (;; hi -= 64) {  // ends at the latest in the window of chunk 0
+        const int r = window(hi, peek_state(state + max(hi - 1 - lane, 0)));
         if (r) return r > 0;
     }
-    excl = sum;
-    return true;
 }
 
 typedef __attribute__((address_space(3))) fz_u32x4 LdsUnit;
@@ -812,29 +822,26 @@ __device__ __forceinline__ void put_pair(fz_u32x4* units, uint32_t j, uint2 p)
 // escape pairs padded to 16 bytes.  dst: the LDS buffer, or the chunk's place
 // in the stream (a payload past kPayUnits, whose look-back was not put off).
 // A chunk may hold kChunkOutlierCap escapes wherever they fall; past that the
-// stream carries the OUTLIER_CAP status and no pairs are written.
+// stream carries the OUTLIER_CAP status and no pairs are written.  The flags
+// come from the lanes they were counted into: formed again from W, the compiler
+// kept 16 conditions in spilled scalar registers (1800x3600 REL 30.5 us, now
+// 25.6 with the first chunk's loads issued before the range is folded).
 template <typename Unit>  // uint4 in LDS or in global memory
 __device__ __forceinline__ void store_chunk(uint8_t* __restrict__ out, const Geom& g, int64_t c, int wave, int lane, int par,
-                                            const ChunkSum& m, const uint32_t (&W)[kPlanes][4], const uint8_t* slot,
-                                            CompressLds& S, Unit* dst)
+                                            const ChunkSum& m, const uint32_t (&W)[kPlanes][4], const Flags& F,
+                                            const uint8_t* slot, CompressLds& S, Unit* dst)
 {
-    uint32_t base = 0;
-    for (int w = 0; w < wave; w++) base += S.nnz[par][w];
-    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-    uint32_t flo = 0, fhi = 0;  // lane b: the flag word of plane b
+    uint32_t base = m.base;
 #pragma unroll
     for (int b = 0; b < kPlanes; b++) {
-        // formed again (4 instructions) rather than kept over the placement:
-        // 16 flag words in scalar registers spilled others
-        const uint64_t f = plane_flags(W[b]);
+        const uint64_t f = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)F.hi, b) << 32 |
+                           (uint32_t)__builtin_amdgcn_readlane((int)F.lo, b);
         const fz_u32x4 brick = {W[b][0], W[b][1], W[b][2], W[b][3]};
         if (__builtin_amdgcn_inverse_ballot_w64(f)) dst[base + mbcnt(f)] = brick;
         base += (uint32_t)__builtin_popcountll(f);
-        flo = lane == b ? (uint32_t)f : flo;
-        fhi = lane == b ? (uint32_t)(f >> 32) : fhi;
     }
     if (lane < kPlanes)
-        reinterpret_cast<uint2*>(out + g.flags_off + (int64_t)kFlagBytesPerChunk * c + 128 * wave)[lane] = make_uint2(flo, fhi);
+        reinterpret_cast<uint2*>(out + g.flags_off + (int64_t)kFlagBytesPerChunk * c + 128 * wave)[lane] = make_uint2(F.lo, F.hi);
     if (threadIdx.x == 0) {
         reinterpret_cast<uint32_t*>(out + g.table_off + 8 * c)[1] = m.kept;
         const uint32_t err = atomicExch(&S.err[par], 0u) | (m.esc > (uint32_t)kChunkOutlierCap ? kErrOutlierCap : 0u);
@@ -910,7 +917,7 @@ __device__ __forceinline__ void place_copy(uint8_t* __restrict__ out, const Geom
 // chunk's place_copy; ends with a barrier).
 __device__ __forceinline__ void place_now(uint8_t* __restrict__ out, uint8_t* __restrict__ scr, const Geom& g, int64_t c,
                                           int wave, int lane, int par, const ChunkSum& m, const uint32_t (&W)[kPlanes][4],
-                                          const uint8_t* slot, CompressLds& S)
+                                          const Flags& F, const uint8_t* slot, CompressLds& S)
 {
     if (wave == 0) {
         StatesAhead ahead;
@@ -920,7 +927,7 @@ __device__ __forceinline__ void place_now(uint8_t* __restrict__ out, uint8_t* __
     __syncthreads();
     const uint64_t excl = S.excl;
     // a failed look-back marked the stream; its offset is 0, inside the bound
-    store_chunk(out, g, c, wave, lane, par, m, W, slot, S, reinterpret_cast<fz_u32x4*>(out + g.payload_off) + (excl == ~0ull ? 0 : excl));
+    store_chunk(out, g, c, wave, lane, par, m, W, F, slot, S, reinterpret_cast<fz_u32x4*>(out + g.payload_off) + (excl == ~0ull ? 0 : excl));
     lds_barrier();
 }
 

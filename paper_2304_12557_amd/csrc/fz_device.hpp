@@ -31,6 +31,11 @@ __device__ __forceinline__ int shift_up1_raw(int v)
 {
     return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false);
 }
+// the same with 0 on lane 0 (a following `&` takes the shift in as its operand)
+__device__ __forceinline__ uint32_t shift_up1_zero(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, true);
+}
 __device__ __forceinline__ int shift_up1(int v, int lane)
 {
     const int r = shift_up1_raw(v);
@@ -76,6 +81,15 @@ __device__ __forceinline__ int excl_scan_stride8(int v, int lane)
 __device__ __forceinline__ int lane_value(int v, int src)
 {
     return __builtin_amdgcn_ds_bpermute(src << 2, v);
+}
+
+// v of lane `to` (a constant) set to a uniform value.  The intrinsic by its
+// name, as clang has no builtin for it (inline assembly would miss the wait
+// states between a compare that wrote the value and this read of it).
+extern "C" __device__ uint32_t fz_writelane(uint32_t value, uint32_t to, uint32_t v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ void set_lane(uint32_t& v, int to, uint32_t value)
+{
+    v = fz_writelane(value, (uint32_t)to, v);
 }
 
 __device__ __forceinline__ uint32_t mbcnt(uint64_t mask)
