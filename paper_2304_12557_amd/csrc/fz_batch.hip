@@ -36,24 +36,22 @@
 namespace fz {
 
 // ---------------------------------------------------------------- kernels
-__global__ __launch_bounds__(256) void k_batch_init(const CompressJob* __restrict__ jobs, int n_jobs,
-                                                    uint32_t* __restrict__ ticket)
+// The fields' headers and scratch (a block per field, and one for the ticket
+// counters), and beside them the range pass of the REL fields: a field's
+// partials are no part of what its first block clears.
+__global__ __launch_bounds__(256) void k_batch_front(const CompressJob* __restrict__ jobs, int n_jobs,
+                                                     uint32_t* __restrict__ ticket, const int32_t* __restrict__ mm_job)
 {
-    if ((int)blockIdx.x == n_jobs) {
+    const int b = (int)blockIdx.x - (n_jobs + 1);
+    if (b >= 0) {
+        const CompressJob& J = jobs[mm_job[b]];
+        minmax_block(J.x, J.g.n[0] * J.g.n[1] * J.g.n[2], J.out + J.g.scratch_off, J.g, (int64_t)b - J.mm0, J.mm_blocks);
+    } else if (b == -1) {
         if (threadIdx.x < 8) ticket[threadIdx.x] = 0u;  // one ticket counter per class
-        return;
+    } else {
+        const CompressJob& J = jobs[blockIdx.x];
+        init_field(J.out, J.out + J.g.scratch_off, J.g, J.h, threadIdx.x, 256);
     }
-    const CompressJob& J = jobs[blockIdx.x];
-    init_field(J.out, J.out + J.g.scratch_off, J.g, J.h, threadIdx.x, 256);
-}
-
-__global__ __launch_bounds__(256) void k_batch_minmax(const CompressJob* __restrict__ jobs,
-                                                      const int32_t* __restrict__ mm_job)
-{
-    const int j = mm_job[blockIdx.x];
-    const CompressJob& J = jobs[j];
-    minmax_block(J.x, J.g.n[0] * J.g.n[1] * J.g.n[2], J.out + J.g.scratch_off, J.g, (int64_t)blockIdx.x - J.mm0,
-                 J.mm_blocks);
 }
 
 __global__ __launch_bounds__(256) void k_batch_params(const CompressJob* __restrict__ jobs)
@@ -145,8 +143,12 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_batch_compress(const Compre
             }
             counts.bricks += m.bricks;
             counts.pairs += m.kept;
+            counts.chunks++;
         }
-        if (jn != j) add_counts(out, counts);
+        if (jn != j) {  // the workgroup's last chunk of this field
+            if (counts.chunks) finish_part(out, scr, counts.chunks, (uint32_t)g.n_chunks);
+            add_counts(out, counts);
+        }
         if (tn >= total) break;
         t = tn;
         j = jn;
@@ -162,13 +164,6 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_batch_compress(const Compre
         __syncthreads();  // the staged payload and its offset are complete
         place_copy(out, P.g, pend_units, S);
     }
-}
-
-// after every chunk of every field is placed: each field's final status word
-__global__ __launch_bounds__(64) void k_batch_finish(const CompressJob* __restrict__ jobs)
-{
-    const CompressJob& J = jobs[blockIdx.x];
-    if (threadIdx.x == 0) finish_field(J.out, J.out + J.g.scratch_off);
 }
 
 __global__ __launch_bounds__(256) void k_batch_clear_err(const DecompressJob* __restrict__ jobs, int n_jobs)
@@ -296,11 +291,10 @@ hipError_t plan_run(const Plan* P, hipStream_t st)
         return hipGetLastError();
     }
     const CompressJob* jobs = static_cast<const CompressJob*>(P->d_jobs);
-    hipLaunchKernelGGL(k_batch_init, dim3(P->n_jobs + 1), dim3(256), 0, st, jobs, P->n_jobs, P->d_ticket);
+    const int64_t front = P->n_jobs + 1 + (P->any_rel ? P->total_mm : 0);
+    hipLaunchKernelGGL(k_batch_front, dim3((unsigned)front), dim3(256), 0, st, jobs, P->n_jobs, P->d_ticket, P->d_mm_job);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (P->any_rel) {
-        hipLaunchKernelGGL(k_batch_minmax, dim3((unsigned)P->total_mm), dim3(256), 0, st, jobs, P->d_mm_job);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(k_batch_params, dim3(P->n_jobs), dim3(256), 0, st, jobs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -323,8 +317,7 @@ hipError_t plan_run(const Plan* P, hipStream_t st)
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_batch_finish, dim3(P->n_jobs), dim3(64), 0, st, jobs);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 int plan_compress(Plan* Pp, int n, const fz_compress_job* jobs)

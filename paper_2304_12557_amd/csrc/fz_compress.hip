@@ -46,7 +46,7 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __res
     __syncthreads();
     int64_t c = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.ticket);
     if (c >= g.n_chunks) {  // the others took every chunk
-        finish_if_last(out, scratch);
+        finish_part(out, scratch, 1u, gridDim.x);
         return;
     }
     const uint64_t* state = reinterpret_cast<const uint64_t*>(scratch + kScratchStateOff);
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __res
         place_copy(out, g, pend_units, S);
     }
     add_counts(out, counts);
-    finish_if_last(out, scratch);
+    finish_part(out, scratch, 1u, gridDim.x);
 }
 
 __global__ __launch_bounds__(256) void k_init(uint8_t* __restrict__ out, uint8_t* __restrict__ scratch, Geom g,
@@ -188,7 +188,7 @@ static hipError_t launch_rank(const float* x, uint8_t* out, uint8_t* scr, const 
     return t ? mark(t->done, st) : hipSuccess;
 }
 
-static hipError_t launch_init(uint8_t* out, uint8_t* scr, const Geom& g, const HeaderImage& h, hipStream_t st)
+hipError_t launch_init(uint8_t* out, uint8_t* scr, const Geom& g, const HeaderImage& h, hipStream_t st)
 {
     const int64_t init_threads = g.n_chunks > kHeaderBytes / 4 ? g.n_chunks : kHeaderBytes / 4;
     const unsigned init_blocks = (unsigned)((init_threads + 255) / 256 < 1024 ? (init_threads + 255) / 256 : 1024);
@@ -213,9 +213,8 @@ static hipError_t launch_main_int(uint8_t* out, const Geom& g, hipStream_t st)
 hipError_t launch_compress_f64(const double* x, uint8_t* out, const Geom& g, const HeaderImage& h, int mode,
                                double eb, hipStream_t st)
 {
-    hipError_t e = launch_init(out, out + g.scratch_off, g, h, st);
+    const hipError_t e = launch_f64_front(x, out, g, h, mode, eb, st);
     if (e != hipSuccess) return e;
-    if ((e = launch_f64_front(x, out, g, mode, eb, st)) != hipSuccess) return e;
     return launch_main_int(out, g, st);
 }
 

@@ -935,6 +935,7 @@ __device__ __forceinline__ void place_now(uint8_t* __restrict__ out, uint8_t* __
 // once (by thread 0): one atomic per workgroup, not per chunk.
 struct Counts {
     uint64_t bricks = 0, pairs = 0;
+    uint32_t chunks = 0;  // (batches: the field's chunks it has coded)
 };
 __device__ __forceinline__ void add_counts(uint8_t* __restrict__ out, Counts& n)
 {
@@ -1121,39 +1122,27 @@ __device__ __forceinline__ void params_field(uint8_t* __restrict__ out, uint8_t*
     if (threadIdx.x == 0) write_params(out, scratch, g, r);
 }
 
-// End of one field's compression, after every chunk is placed (a launch of
-// its own): a failed prequantization anywhere (NaN/Inf, overflow) ends the
-// pipeline before the encoder, so the escape-cap bit of chunks that went on
-// counts only when no such bit is set.
-__device__ __forceinline__ void finish_field(uint8_t* __restrict__ out, const uint8_t* __restrict__ scratch)
-{
-    const Scratch* scr = reinterpret_cast<const Scratch*>(scratch);
-    if (scr->pre_status) return;  // the range pass failed: nothing was compressed
-    uint32_t* st = reinterpret_cast<uint32_t*>(out + kOffStatus);
-    const uint32_t v = *st;
-    if (v & (kErrNonfinite | kErrEbRange)) *st = v & ~kErrOutlierCap;
-}
-
-// The same inside the per-field compression kernel, by thread 0 of each
-// workgroup as it ends (after its last placement and barrier): the last
-// workgroup of the grid to count itself done settles the status word, so
-// that no launch of its own is needed.  The status word and the count are
-// only touched with agent-scope atomics, which every XCD sees in one order
-// (their L2 caches are not coherent with one another, so nothing here may
-// rely on them).  Thread 0 set its workgroup's status bits; an explicit wait
-// for its outstanding memory operations (not an agent-scope release, which
-// adds an L2 write-back at every workgroup's end: +9 us on 512^3) makes those
-// atomics complete before the count is issued, and the last workgroup
-// reads and clears the word only after its count has returned.  Workgroups
-// that return because the range pass failed (pre_status) do not count;
-// nothing is settled then.
-__device__ __forceinline__ void finish_if_last(uint8_t* __restrict__ out, uint8_t* __restrict__ scratch)
+// End of one field's compression inside the kernel that codes it, by thread 0
+// of a workgroup that adds its `part` (workgroups or chunks) of `all`: the last
+// one settles the status word, so that no launch of its own is needed.  A
+// failed prequantization anywhere (NaN/Inf, overflow) ends the pipeline before
+// the encoder, so the escape-cap bit of chunks that went on counts only when no
+// such bit is set.  The status word and the count are only touched with
+// agent-scope atomics, which every XCD sees in one order (their L2 caches are
+// not coherent with one another, so nothing here may rely on them).  Thread 0
+// set its workgroup's status bits; an explicit wait for its outstanding memory
+// operations (not an agent-scope release, which adds an L2 write-back at every
+// workgroup's end: +9 us on 512^3) makes those atomics complete before the
+// count is issued, and the last workgroup reads and clears the word only after
+// its count has returned.  Workgroups that return because the range pass failed
+// (pre_status) do not count; nothing is settled then.
+__device__ __forceinline__ void finish_part(uint8_t* __restrict__ out, uint8_t* __restrict__ scratch, uint32_t part, uint32_t all)
 {
     if (threadIdx.x != 0) return;
     Scratch* scr = reinterpret_cast<Scratch*>(scratch);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // no memory operation moves below this point
     __builtin_amdgcn_s_waitcnt(0);  // and every one of this thread's has completed (the fence alone emits no wait)
-    if (__hip_atomic_fetch_add(&scr->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
+    if (__hip_atomic_fetch_add(&scr->done, part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != all - part) return;
     uint32_t* st = reinterpret_cast<uint32_t*>(out + kOffStatus);
     const uint32_t v = __hip_atomic_load(st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (v & (kErrNonfinite | kErrEbRange))

@@ -28,7 +28,10 @@ hipError_t launch_decompress(const uint8_t* s, uint64_t sb, float* y, const Geom
 // kernel on those integers
 hipError_t launch_compress_f64(const double* x, uint8_t* out, const Geom& g, const HeaderImage& h, int mode,
                                double eb, hipStream_t st);
-hipError_t launch_f64_front(const double* x, uint8_t* out, const Geom& g, int mode, double eb, hipStream_t st);
+hipError_t launch_f64_front(const double* x, uint8_t* out, const Geom& g, const HeaderImage& h, int mode, double eb,
+                            hipStream_t st);
+// a field's header, scratch and chunk states
+hipError_t launch_init(uint8_t* out, uint8_t* scr, const Geom& g, const HeaderImage& h, hipStream_t st);
 hipError_t launch_decompress_f64(const uint8_t* s, uint64_t sb, double* y, const Geom& g, uint32_t* d_err,
                                  hipStream_t st);
 // field-global Lorenzo predictor: compression (any fp32 mode) and
