@@ -415,11 +415,38 @@ __device__ __forceinline__ void inplane2(uint32_t (&A)[16], int lane)
     A[0] = sub2(A[0], left);
 }
 
+// Whether some delta of a step may be an escape, from the differences along the
+// sweep dimension in 256ths (H, packed, below 2^12 in magnitude; changed): the
+// in-plane part of those is the delta in 256ths, off by less than 2.  keep: the
+// cells that count.
+template <int RANK>
+__device__ __forceinline__ bool plane_escapes(uint32_t (&H)[16], bool edge, uint32_t keep, int lane)
+{
+    if (RANK == 3) inplane3(H, lane);
+    else inplane2(H, lane);
+    if (edge) {
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            H[i] &= ((keep >> i) & 1u ? 0xFFFFu : 0u) | ((keep >> (i + 16)) & 1u ? 0xFFFF0000u : 0u);
+    }
+    fz_short2 mx = as_short2(H[0]), mn = mx;
+#pragma unroll
+    for (int i = 1; i < 16; i++) {
+        mx = __builtin_elementwise_max(mx, as_short2(H[i]));
+        mn = __builtin_elementwise_min(mn, as_short2(H[i]));
+    }
+    return __ballot(max(mx.x, mx.y) > 126 || min(mn.x, mn.y) < -126) != 0;
+}
+
 // One step: its difference along the sweep dimension (a; 1-D: its deltas) ->
 // bit planes P.  keep: the cells inside the field (the codes of the others
-// are cleared: bit i of each plane word is code i).  Returns whether some
-// difference does not fit the packed arithmetic; on the 2eb grid with every
-// |q| small (facc) none can, and the check is skipped.
+// are cleared: bit i of each plane word is code i).  Returns whether some delta
+// may be an escape.  The packed arithmetic is exact modulo 2^16, so its codes are
+// right whenever none is; differences within packed_limit cannot give one, and
+// on the 2eb grid with every |q| small (facc) none lies past it.  Otherwise the
+// deltas are formed in 256ths and looked at (a field that varies by more than
+// the limit within a plane, 320x192x192 ABS: 42.9 us with every such layer
+// coded out of line, 28.2 so; 33.5 before any layer was packed).
 // head: the step holds the chunk's first cell, whose delta is `first`.
 template <int RANK, int QM>
 __device__ __forceinline__ bool step_planes(const int (&a)[32], bool edge, uint32_t keep, float facc, int lane,
@@ -435,6 +462,12 @@ __device__ __forceinline__ bool step_planes(const int (&a)[32], bool edge, uint3
             mn = min(mn, min(a[i], a[i + 1]));
         }
         wide = __ballot(mx > lim || mn < -lim) != 0;
+        if (RANK >= 2 && wide && __ballot(mx >= (1 << 20) || mn < -(1 << 20)) == 0) {
+            uint32_t H[16];
+#pragma unroll
+            for (int i = 0; i < 16; i++) H[i] = __builtin_amdgcn_perm((uint32_t)a[i + 16], (uint32_t)a[i], 0x06050201u);
+            wide = plane_escapes<RANK>(H, edge, keep, lane);
+        }
     }
 #pragma unroll
     for (int i = 0; i < 16; i++) P[i] = __builtin_amdgcn_perm((uint32_t)a[i + 16], (uint32_t)a[i], 0x05040100u);
