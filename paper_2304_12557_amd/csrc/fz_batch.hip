@@ -4,10 +4,11 @@
 // A plan holds, in device memory, one descriptor per field and a chunk -> field
 // table over the concatenated chunks of all fields.  Running a compression
 // plan enqueues a fixed sequence of launches whatever the number of fields:
-//   init (all fields) -> value range + eb (REL fields) -> one persistent
-//   compression launch per (rank, row-alignment) class present (at most six,
-//   usually three), each over every chunk of every field of its class, which
-//   also places the chunks -> the final status word of each field
+//   init (all fields) with the value range (REL fields) beside it -> eb (REL
+//   fields) -> one persistent compression launch per (rank, row-alignment)
+//   class present (at most six, usually three), each over every chunk of every
+//   field of its class, which also places the chunks and settles each field's
+//   status word
 // and a decompression plan one launch over every chunk of every field.  Each
 // field's bytes are exactly those of the per-field call: the per-chunk and
 // per-field device code is the same (fz_compress_dev.hpp,
@@ -64,10 +65,9 @@ __global__ __launch_bounds__(256) void k_batch_params(const CompressJob* __restr
 // field of that class: tickets run over the class's part of the chunk table,
 // which maps a ticket to its field.  Within a field the next chunk's first
 // loads are issued before the current one is placed, as in the per-field
-// kernel, and chunks are placed as there: staged in the workgroup's slot of
-// the plan's staging area and copied to their offset one chunk later, after
-// a look-back over the field's published chunk sizes.  Fields whose REL pass
-// failed are skipped.  (One instantiation per launch keeps the register
+// kernel, and chunks are placed as there: staged in LDS and copied to their
+// offset one chunk later, after a look-back over the field's published chunk
+// sizes.  Fields whose REL pass failed are skipped.  (One instantiation per launch keeps the register
 // budget of the per-field kernel; a kernel holding all six would spill.)
 template <int RANK, bool VEC4>
 __global__ __launch_bounds__(64 * kLayers, 2) void k_batch_compress(const CompressJob* __restrict__ jobs,

@@ -69,10 +69,10 @@ constexpr int kScratchGeomOff = 64;
 constexpr int kScratchStateOff = 512;
 // per-block partial value ranges of the REL pass, after the chunk states
 constexpr int kMinmaxBlocks = 2048;
-// staging: each compression workgroup assembles a chunk's compacted payload
-// in a slot of its own (at scr_stage + workgroup * slot bytes in the scratch)
-// and copies it to its place in the stream once the chunk's offset is known;
-// the grid has at most kStageSlots workgroups
+// slots: each compression workgroup has one of its own (at scr_stage +
+// workgroup * slot bytes in the scratch) for the bricks and escape pairs of
+// layers that are coded out of line; the grid has at most kStageSlots
+// workgroups
 constexpr int64_t kStageSlotBytes = kChunkPayloadBound;
 constexpr int kStageSlots = 768;
 
