@@ -138,9 +138,9 @@ inline bool make_geom(int rank, const uint64_t* dims, Geom* g)
     g->n_chunks = 1;
     for (int i = 0; i < 3; i++) {
         g->grid[i] = (g->n[i] + g->box[i] - 1) / g->box[i];
-        g->n_chunks *= g->grid[i];
+        // each factor below 2^41: checked one by one, no product overflows
+        if (g->grid[i] >= (1ll << 31) || (g->n_chunks *= g->grid[i]) >= (1ll << 31)) return false;
     }
-    if (g->n_chunks >= (1ll << 31)) return false;
     g->div[0] = divisor((uint64_t)g->grid[1]);
     g->div[1] = divisor((uint64_t)g->grid[2]);
     int64_t table = (8 * g->n_chunks + 15) / 16 * 16;
