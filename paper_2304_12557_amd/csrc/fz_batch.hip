@@ -79,13 +79,13 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_batch_compress(const Compre
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* slot = stage + kStageSlotBytes * (int64_t)blockIdx.x;
     if (threadIdx.x == 0) {
-        S.ticket = atomicAdd(ticket, 1u);
+        S.first = atomicAdd(ticket, 1u);
         S.err[0] = S.err[1] = 0;
         S.arrived = 0;
         S.esc_used = 0;
     }
     __syncthreads();
-    int64_t t = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.ticket);
+    int64_t t = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.first);
     if (t >= total) return;
     int j = __builtin_amdgcn_readfirstlane(chunk_job[t]);
     float h[32], v[32];

@@ -38,13 +38,13 @@ __global__ __launch_bounds__(64 * kLayers, 2) void k_compress(const float* __res
     uint8_t* slot = scratch + g.scr_stage + kStageSlotBytes * (int64_t)blockIdx.x;
 
     if (threadIdx.x == 0) {
-        S.ticket = atomicAdd(&scr->ticket, 1u);
+        S.first = atomicAdd(&scr->ticket, 1u);
         S.err[0] = S.err[1] = 0;
         S.arrived = 0;
         S.esc_used = 0;
     }
     __syncthreads();
-    int64_t c = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.ticket);
+    int64_t c = (int64_t)__builtin_amdgcn_readfirstlane((uint32_t)S.first);
     if (c >= g.n_chunks) {  // the others took every chunk
         finish_part(out, scratch, 1u, gridDim.x);
         return;

@@ -45,7 +45,10 @@ struct CompressLds {
     uint4 pay[kPayUnits];  // the staged chunk's payload: bricks, then escape pairs
     uint4 tile[kLayers][256];  // per wave: half a step on its way from rows to patches
     uint32_t arrived;  // waves whose layer of the current chunk is done
-    uint64_t ticket;
+    // the workgroup's first ticket, in a word of its own: thread 0 leaves the
+    // next one without a barrier after the other waves' read of this one
+    uint64_t first;
+    uint64_t ticket;   // the next ticket
     uint64_t excl;     // offset of the chunk being placed (16-B units), from the look-back
     // status bits, and bricks and escapes of each layer, by the chunk's parity:
     // a wave may be one chunk ahead of one that still reads them
