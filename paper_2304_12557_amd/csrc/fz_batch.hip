@@ -173,11 +173,12 @@ __global__ __launch_bounds__(256) void k_batch_clear_err(const DecompressJob* __
 }
 
 __global__ __launch_bounds__(512, 4) void k_batch_decompress(const DecompressJob* __restrict__ jobs,
-                                                             const int32_t* __restrict__ chunk_job)
+                                                             const int32_t* __restrict__ chunk_job, uint32_t first)
 {
     __shared__ DecompressLds<8> S;
-    const DecompressJob& J = jobs[chunk_job[blockIdx.x]];
-    const int64_t c = (int64_t)blockIdx.x - J.chunk0;
+    const uint32_t b = first + blockIdx.x;
+    const DecompressJob& J = jobs[chunk_job[b]];
+    const int64_t c = (int64_t)b - J.chunk0;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const bool stream = (J.key & 1) != 0;
     const uint8_t* s = as_global(J.s);
@@ -287,8 +288,9 @@ hipError_t plan_run(const Plan* P, hipStream_t st)
         const DecompressJob* jobs = static_cast<const DecompressJob*>(P->d_jobs);
         hipLaunchKernelGGL(k_batch_clear_err, dim3((P->n_jobs + 255) / 256), dim3(256), 0, st, jobs, P->n_jobs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_batch_decompress, dim3((unsigned)P->total_chunks), dim3(512), 0, st, jobs, P->d_chunk_job);
-        return hipGetLastError();
+        return launch_chunks(P->total_chunks, [&](uint32_t first, dim3 blocks) {
+            hipLaunchKernelGGL(k_batch_decompress, blocks, dim3(512), 0, st, jobs, P->d_chunk_job, first);
+        });
     }
     const CompressJob* jobs = static_cast<const CompressJob*>(P->d_jobs);
     const int64_t front = P->n_jobs + 1 + (P->any_rel ? P->total_mm : 0);

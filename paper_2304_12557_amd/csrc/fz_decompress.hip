@@ -9,13 +9,14 @@
 namespace fz {
 
 // 128 registers (4 waves per SIMD) and 72 KB of LDS: two workgroups per CU.
+// first: the launch's first block of the field (launch_chunks).
 template <int RANK, bool STREAM>
 __global__ __launch_bounds__(512, 4) void k_decompress(const uint8_t* __restrict__ s, uint64_t sb,
-                                                       float* __restrict__ y, Geom g, uint32_t* d_err)
+                                                       float* __restrict__ y, Geom g, uint32_t* d_err, uint32_t first)
 {
     __shared__ DecompressLds<8> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    decompress_chunk<RANK, float, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g), wave, threadIdx.x & 63, S);
+    decompress_chunk<RANK, float, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g, first + blockIdx.x), wave, threadIdx.x & 63, S);
 }
 
 // the same with NW waves, one step each (fields with few chunks; launched
@@ -44,12 +45,12 @@ constexpr int64_t kSplitChunks = 256;
 template <int RANK, bool STREAM>
 static hipError_t launch_rank(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
-    if (g.n_chunks <= kSplitChunks)
-        hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), dim3((unsigned)g.n_chunks), dim3(1024), 0, st, s, sb,
-                           y, g, d_err);
-    else
-        hipLaunchKernelGGL((k_decompress<RANK, STREAM>), dim3((unsigned)g.n_chunks), dim3(512), 0, st, s, sb, y, g, d_err);
-    return hipGetLastError();
+    return launch_chunks(g.n_chunks, [&](uint32_t first, dim3 blocks) {
+        if (g.n_chunks <= kSplitChunks)
+            hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), blocks, dim3(1024), 0, st, s, sb, y, g, d_err);
+        else
+            hipLaunchKernelGGL((k_decompress<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first);
+    });
 }
 
 hipError_t launch_decompress(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)

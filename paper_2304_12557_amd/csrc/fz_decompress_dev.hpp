@@ -631,12 +631,12 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
     }
 }
 
-// The chunk of this block of an fp32-sized decompression: streaming stores
+// The chunk of block b of an fp32-sized decompression: streaming stores
 // fill whole lines, which no two chunks share.
 template <bool STREAM>
-__device__ __forceinline__ int64_t in_place_chunk(const Geom& g)
+__device__ __forceinline__ int64_t in_place_chunk(const Geom& g, uint32_t b)
 {
-    return STREAM ? (int64_t)blockIdx.x : xcd_order(blockIdx.x, g.n_chunks);
+    return STREAM ? (int64_t)b : xcd_order(b, g.n_chunks);
 }
 
 }  // namespace fz

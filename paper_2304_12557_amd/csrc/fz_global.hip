@@ -168,7 +168,8 @@ __device__ __noinline__ uint32_t face_errors(const float* __restrict__ x, const 
 // several planes, which keep the common difference in registers, measured the
 // same at 2 planes and 2 % slower at 4.
 template <int RANK, int QM>
-__global__ __launch_bounds__(kRunThreads) void k_face(const float* __restrict__ x, uint8_t* __restrict__ out, Geom g)
+__global__ __launch_bounds__(kRunThreads) void k_face(const float* __restrict__ x, uint8_t* __restrict__ out, Geom g,
+                                                      uint32_t first_block)
 {
     uint8_t* scr = out + g.scratch_off;
     if (reinterpret_cast<const Scratch*>(scr)->pre_status) return;  // set before this launch (REL range pass): uniform
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(kRunThreads) void k_face(const float* __restrict__ 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n = g.n[0] * g.n[1] * g.n[2];
-    const int64_t c = xcd_order(blockIdx.x, g.n_chunks);
+    const int64_t c = xcd_order(first_block + blockIdx.x, g.n_chunks);
     const Runs r = runs_of<RANK>(g, c, lane);
     if (!part_live<RANK>(r, wave)) return;  // (no barrier below)
     const bool inz = RANK == 3 && r.org[0] > 0;                    // 3-D: a plane Z
@@ -251,31 +252,31 @@ __global__ __launch_bounds__(kRunThreads) void k_face(const float* __restrict__ 
 }
 
 template <int RANK>
-static void launch_face_rank(const float* x, uint8_t* out, const Geom& g, bool pw, hipStream_t st)
+static hipError_t launch_face_rank(const float* x, uint8_t* out, const Geom& g, bool pw, hipStream_t st)
 {
-    const dim3 grid((unsigned)g.n_chunks), block(kRunThreads);
-    if (pw) hipLaunchKernelGGL((k_face<RANK, kQuantPw>), grid, block, 0, st, x, out, g);
-    else hipLaunchKernelGGL((k_face<RANK, kQuantGrid>), grid, block, 0, st, x, out, g);
+    return launch_chunks(g.n_chunks, [&](uint32_t first, dim3 blocks) {
+        if (pw) hipLaunchKernelGGL((k_face<RANK, kQuantPw>), blocks, dim3(kRunThreads), 0, st, x, out, g, first);
+        else hipLaunchKernelGGL((k_face<RANK, kQuantGrid>), blocks, dim3(kRunThreads), 0, st, x, out, g, first);
+    });
 }
 
 hipError_t launch_face(const float* x, uint8_t* out, const Geom& g, bool pw, hipStream_t st)
 {
     switch (g.rank) {
-        case 3: launch_face_rank<3>(x, out, g, pw, st); break;
-        case 2: launch_face_rank<2>(x, out, g, pw, st); break;
-        default: launch_face_rank<1>(x, out, g, pw, st); break;
+        case 3: return launch_face_rank<3>(x, out, g, pw, st);
+        case 2: return launch_face_rank<2>(x, out, g, pw, st);
+        default: return launch_face_rank<1>(x, out, g, pw, st);
     }
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------------ decompression
 template <int RANK, bool STREAM>
 __global__ __launch_bounds__(512, 4) void k_decompress_int(const uint8_t* __restrict__ s, uint64_t sb,
-                                                           int32_t* __restrict__ y, Geom g, uint32_t* d_err)
+                                                           int32_t* __restrict__ y, Geom g, uint32_t* d_err, uint32_t first)
 {
     __shared__ DecompressLds<8> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    decompress_chunk<RANK, int32_t, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g), wave, threadIdx.x & 63, S);
+    decompress_chunk<RANK, int32_t, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g, first + blockIdx.x), wave, threadIdx.x & 63, S);
 }
 
 // Carries of the field-global prefix sums.  Along axis ax the field splits
@@ -380,7 +381,8 @@ __global__ __launch_bounds__(kGlobalThreads) void k_seg_carry(const uint32_t* __
 // writing the field: 100x500x500 36 us, 5.6 TB/s (a thread per cell: 104 us).
 template <int RANK, bool STREAM>
 __global__ __launch_bounds__(kRunThreads) void k_seg_final(uint32_t* __restrict__ f, const uint32_t* __restrict__ w,
-                                                              Carries k, Geom g, const uint8_t* __restrict__ s)
+                                                              Carries k, Geom g, const uint8_t* __restrict__ s,
+                                                              uint32_t first)
 {
     const float ebx2 = *reinterpret_cast<const float*>(s + kOffEbx2);
     const bool pw = s[kOffEbMode] == 2;
@@ -388,7 +390,7 @@ __global__ __launch_bounds__(kRunThreads) void k_seg_final(uint32_t* __restrict_
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n = g.n[0] * g.n[1] * g.n[2];
-    const int64_t c = xcd_order(blockIdx.x, g.n_chunks);
+    const int64_t c = xcd_order(first + blockIdx.x, g.n_chunks);
     const Runs r = runs_of<RANK>(g, c, lane);
     if (!part_live<RANK>(r, wave)) return;
     // the carries of this chunk's segment of each axis
@@ -438,17 +440,19 @@ template <int RANK, bool STREAM>
 static hipError_t launch_rank_int(const uint8_t* s, uint64_t sb, int32_t* y, const Geom& g, uint32_t* d_err,
                                   hipStream_t st)
 {
-    hipLaunchKernelGGL((k_decompress_int<RANK, STREAM>), dim3((unsigned)g.n_chunks), dim3(512), 0, st, s, sb, y, g, d_err);
-    return hipGetLastError();
+    return launch_chunks(g.n_chunks, [&](uint32_t first, dim3 blocks) {
+        hipLaunchKernelGGL((k_decompress_int<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first);
+    });
 }
 
 template <int RANK>
-static void launch_final(uint32_t* f, const uint32_t* w, const Carries& k, const Geom& g, const uint8_t* s,
-                         bool stream, hipStream_t st)
+static hipError_t launch_final(uint32_t* f, const uint32_t* w, const Carries& k, const Geom& g, const uint8_t* s,
+                               bool stream, hipStream_t st)
 {
-    const dim3 grid((unsigned)g.n_chunks), block(kRunThreads);
-    if (stream) hipLaunchKernelGGL((k_seg_final<RANK, true>), grid, block, 0, st, f, w, k, g, s);
-    else hipLaunchKernelGGL((k_seg_final<RANK, false>), grid, block, 0, st, f, w, k, g, s);
+    return launch_chunks(g.n_chunks, [&](uint32_t first, dim3 blocks) {
+        if (stream) hipLaunchKernelGGL((k_seg_final<RANK, true>), blocks, dim3(kRunThreads), 0, st, f, w, k, g, s, first);
+        else hipLaunchKernelGGL((k_seg_final<RANK, false>), blocks, dim3(kRunThreads), 0, st, f, w, k, g, s, first);
+    });
 }
 
 // Threads per line: enough for one pass over its segments, but at least 16
@@ -498,11 +502,10 @@ hipError_t launch_decompress_global(const uint8_t* s, uint64_t sb, float* y, con
     if (g.rank >= 2 && (e = launch_carry<1>(f, w, k, st)) != hipSuccess) return e;
     if (g.rank == 3 && (e = launch_carry<0>(f, w, k, st)) != hipSuccess) return e;
     switch (g.rank) {
-        case 3: launch_final<3>(f, w, k, g, s, stream, st); break;
-        case 2: launch_final<2>(f, w, k, g, s, stream, st); break;
-        default: launch_final<1>(f, w, k, g, s, stream, st); break;
+        case 3: return launch_final<3>(f, w, k, g, s, stream, st);
+        case 2: return launch_final<2>(f, w, k, g, s, stream, st);
+        default: return launch_final<1>(f, w, k, g, s, stream, st);
     }
-    return hipGetLastError();
 }
 
 }  // namespace fz

@@ -6,6 +6,24 @@
 
 namespace fz {
 
+// Kernels with a workgroup per chunk take the chunks of a field in launches of
+// at most this many: a launch's threads are counted in 32 bits (2^31 here, at
+// 1024 threads a workgroup), and one past that is cut short without an error.
+// The rest starts at a whole window of xcd_order.
+constexpr int64_t kLaunchChunks = 1 << 21;
+
+// launch(first, blocks) for every such part of n chunks
+template <typename L>
+inline hipError_t launch_chunks(int64_t n, L launch)
+{
+    for (int64_t first = 0; first < n; first += kLaunchChunks) {
+        launch((uint32_t)first, dim3((unsigned)(n - first < kLaunchChunks ? n - first : kLaunchChunks)));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 struct HeaderImage {
     uint32_t w[kHeaderBytes / 4];
 };
