@@ -8,13 +8,16 @@
 
 namespace fz {
 
-// 128 registers (4 waves per SIMD) and 72 KB of LDS: two workgroups per CU.
-// first: the launch's first block of the field (launch_chunks).
+// 128 registers (4 waves per SIMD) and 9 KB of LDS a wave: two workgroups per
+// CU, or more where they have fewer waves (chunk_waves), whose regions are the
+// launch's dynamic LDS.  first: the launch's first block of the field
+// (launch_chunks).
 template <int RANK, bool STREAM>
 __global__ __launch_bounds__(512, 4) void k_decompress(const uint8_t* __restrict__ s, uint64_t sb,
                                                        float* __restrict__ y, Geom g, uint32_t* d_err, uint32_t first)
 {
-    __shared__ DecompressLds<8> S;
+    extern __shared__ uint4 lds[];
+    DecompressLds<8>& S = *reinterpret_cast<DecompressLds<8>*>(lds);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     decompress_chunk<RANK, float, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g, first + blockIdx.x), wave, threadIdx.x & 63, S);
 }
@@ -42,14 +45,27 @@ __global__ void k_set_u32(uint32_t* p, uint32_t v)
 // waves share a CU (256^3, 512 chunks: 21 us against 30 us).
 constexpr int64_t kSplitChunks = 256;
 
+// Waves of a chunk's workgroup, two steps each.  In a field of one layer of
+// chunks that is thinner than they are (2-D, 3-D), all chunks have the same few
+// steps, and waves without one would only hold LDS and wave slots (1x2048x2048:
+// 8 waves 19.8 us, 1 wave 11.0; 4x2048x2048: 27.4, 2 waves 16.5).
+static int chunk_waves(const Geom& g)
+{
+    if (g.rank == 1 || g.grid[0] > 1) return 8;
+    const int64_t steps = g.rank == 3 ? g.n[0] : (g.n[0] + 1) / 2;
+    return (int)((steps + 1) / 2);
+}
+
 template <int RANK, bool STREAM>
 static hipError_t launch_rank(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
+    const int waves = chunk_waves(g);
     return launch_chunks(g.n_chunks, [&](uint32_t first, dim3 blocks) {
         if (g.n_chunks <= kSplitChunks)
             hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), blocks, dim3(1024), 0, st, s, sb, y, g, d_err);
         else
-            hipLaunchKernelGGL((k_decompress<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first);
+            hipLaunchKernelGGL((k_decompress<RANK, STREAM>), blocks, dim3(64 * waves), waves * 4 * kRegionWords, st, s, sb, y,
+                               g, d_err, first);
     });
 }
 

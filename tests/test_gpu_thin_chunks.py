@@ -1,0 +1,70 @@
+"""Decompression of fields of one layer of thin chunks: a chunk's workgroup has
+a wave per two steps that the field reaches, from 1 wave to 8.
+
+More than 256 chunks each (fewer take 16 waves whatever their depth); escapes in
+the first and the last step; the oracle's values bit for bit.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2304_12557_amd as fz
+from oracle import oracle as O
+import synth
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(n, 1030, 530) for n in (1, 2, 3, 4, 5, 8, 9, 14, 15, 16, 17)] + [(n, 300_001) for n in (1, 2, 4, 5, 8, 13, 28, 29, 32, 33)]
+ALIGNED = [(2, 1056, 576), (6, 1056, 576), (3, 264 * 1024), (12, 264 * 1024)]  # rows of whole lines: streaming stores
+
+
+def field(shape, escapes):
+    x = np.round(synth.sine_field(shape, seed=sum(shape)) * 200).astype(np.float32)
+    if escapes:
+        flat = x.reshape(-1)
+        flat[1000::50_021] += 70_000
+        x[0, ..., -1] += 50_000
+        x[-1, ..., 3] -= 60_000
+    return x
+
+
+@pytest.mark.parametrize("escapes", [False, True])
+@pytest.mark.parametrize("shape", SHAPES + ALIGNED)
+def test_thin_fields(shape, escapes):
+    x = field(shape, escapes)
+    print("case", shape, escapes, flush=True)
+    ref, st = O.compress(x, 0.5, O.EB_ABS, threads=8)
+    assert st == 0
+    s = torch.from_numpy(ref).cuda()
+    guard = torch.full((x.size + 128,), -7.0, device="cuda")
+    y = guard[64:64 + x.size].view(shape)
+    err = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    fz.decompress(s, shape, out=y, err=err)
+    assert int(err.item()) == 0
+    assert np.array_equal(y.cpu().numpy(), x)
+    assert bool((guard[:64] == -7).all()) and bool((guard[64 + x.size:] == -7).all())
+
+
+@pytest.mark.parametrize("shape", [(2, 1030, 530), (7, 1030, 530), (3, 300_001)])
+def test_a_pair_that_does_not_match(shape):
+    x = field(shape, True)
+    ref, st = O.compress(x, 0.5, O.EB_ABS, threads=8)
+    assert st == 0
+    tab = ref[128:].view(np.uint8)[:8].view(np.uint32)
+    nout = int(tab[1])
+    assert nout > 0 and int(tab[0]) == 0
+    n_chunks = fz.stream_info(ref[:128].tobytes())["n_chunks"]
+    flags = 128 + (8 * n_chunks + 15) // 16 * 16
+    nnz = int(np.unpackbits(ref[flags:flags + 512]).sum())
+    pairs = ref[fz.header_bytes(shape) + 16 * nnz:][:8 * nout].view(np.uint32)
+    pairs[-2] = 16 * 2048 - 1  # a cell of a step the field does not reach
+    y = torch.full(shape, -7.0, device="cuda")
+    err = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    fz.decompress(torch.from_numpy(ref).cuda(), shape, out=y, err=err)
+    assert int(err.item()) == 6
+    box = (32, 64) if len(shape) == 3 else (1024,)
+    first = tuple([slice(None)] + [slice(0, b) for b in box])
+    got = y.cpu().numpy()
+    assert (got[first] == -7).all()  # the bad chunk is not written
+    got[first] = x[first]
+    assert np.array_equal(got, x)
