@@ -44,9 +44,6 @@ struct Tuning {
     int mm_cap;  // range-pass blocks per field, at most
 };
 
-// compute units of the current device (1 if unknown)
-int cu_count();
-
 // staging slots of a compression plan (one per persistent workgroup) and
 // their bytes, for a device with `cus` compute units
 inline int stage_slots(int cus) { return 2 * cus < kStageSlots ? 2 * cus : kStageSlots; }

@@ -22,20 +22,27 @@
 
 namespace fz {
 
+// The stream's header as 32-bit words.
+struct Header {
+    uint32_t w[kHeaderBytes / 4];
+};
+__device__ __forceinline__ Header load_header(const uint8_t* __restrict__ s)
+{
+    const ConstMem<uint32_t>* hw = const_mem<uint32_t>(s);
+    Header h;
+#pragma unroll
+    for (int i = 0; i < kHeaderBytes / 4; i++) h.w[i] = hw[i];
+    return h;
+}
+
 // dtype: 0 for an fp32 output, 1 for fp64; predictor: the header byte 15
 // the caller handles (0 chunk-local Lorenzo, 1 field-global); s_bytes: the
 // bytes readable at s (at least the header, table and flags, checked on the
 // host)
-__device__ __forceinline__ uint32_t check_header(const uint8_t* __restrict__ s, const Geom& g, int rank, int dtype,
-                                                 int predictor, uint64_t s_bytes)
+__device__ __forceinline__ uint32_t check_header(const Header& h, const Geom& g, int rank, int dtype, int predictor,
+                                                 uint64_t s_bytes)
 {
-    // the whole header at once, as 32-bit words, and every check on them
-    // without an early exit: the loads are uniform and issued together (one
-    // wait), where byte loads behind branches would each wait in turn
-    const ConstMem<uint32_t>* hw = const_mem<uint32_t>(s);
-    uint32_t w[kHeaderBytes / 4];
-#pragma unroll
-    for (int i = 0; i < kHeaderBytes / 4; i++) w[i] = hw[i];
+    const uint32_t (&w)[kHeaderBytes / 4] = h.w;
     auto byte_at = [&](int off) { return (w[off / 4] >> (8 * (off % 4))) & 0xFFu; };
     auto u64_at = [&](int off) { return (uint64_t)w[off / 4] | ((uint64_t)w[off / 4 + 1] << 32); };
     bool bad = byte_at(kOffDtype) != (uint32_t)dtype || byte_at(kOffRank) != (uint32_t)rank ||
@@ -393,6 +400,13 @@ __device__ __forceinline__ void step_prefix(int (&d)[32], int lane)
     }
 }
 
+// A following chunk's payload is brought into the L2 up to this size (32 KB):
+// those of the 64 chunks at work on an XCD then take up to half of its 4 MB.
+// Measured (us, cached / cold, none / up to 32 KB / all): 512^3 of 23 KB a chunk
+// 109.9 / 136.6, 107.7 / 118.1, 106.6 / 118.7; of 37 KB 114.0 / 137.7, 111.9 /
+// 134.7, 121.6 / 128.6.
+constexpr uint32_t kWarmUnits = 32768 / 16;
+
 // Decompress chunk c of a field with a workgroup of NW waves; wave w runs
 // the 16 / NW steps from w * 16 / NW.  A stream that fails a check writes an
 // fz_status code to *d_err (if given) and leaves the chunk's output
@@ -414,10 +428,15 @@ __device__ __forceinline__ void step_prefix(int (&d)[32], int lane)
 // 113 -> 107 us, 100x500x500 50 -> 34 us, 101x499x501 68 -> 36 us, 5001x5003
 // 69 -> 32 us, 2^26 values 64 -> 52 us, 1800x3600 19 -> 12 us, 64^3 18 -> 11 us
 // (times of a pass, rotating over three fields).
-template <int RANK, typename T, int NW>
+//
+// WARM: next_c is the chunk that takes this one's place on the device (-1: none).  Its
+// flags and payload are brought into the L2 while this one is worked on: the
+// chain of a chunk starts with two reads one after the other (table and flags,
+// then bricks), whose latency from HBM two workgroups a CU do not cover.
+template <int RANK, typename T, int NW, bool WARM = false>
 __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, uint64_t s_bytes, T* __restrict__ y,
                                                  bool stream, const Geom& g, uint32_t* d_err, int64_t c, int wave, int lane,
-                                                 DecompressLds<NW>& S)
+                                                 DecompressLds<NW>& S, int64_t next_c = -1)
 {
     static_assert(NW == 8 || NW == 16, "2 or 1 steps per wave");
     constexpr int NS = kSteps / NW;
@@ -427,19 +446,35 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
     // wave's own layer's words also come as scalars
     const uint8_t* flags = s + g.flags_off + (int64_t)kFlagBytesPerChunk * c;
     const uint64_t f = reinterpret_cast<const uint64_t*>(flags)[lane];
+    // words 0 .. 2 of the next chunk's place in the table on lanes 0 .. 2: its
+    // offset, and (not for the last chunk) the next one's
+    uint32_t next_tab = 0u;
+    if constexpr (WARM)
+        next_tab = __builtin_amdgcn_raw_buffer_load_b32(
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(s) + g.table_off + 8 * max(next_c, (int64_t)0), (short)0,
+                                              next_c < 0 ? 0 : next_c + 1 < g.n_chunks ? 12 : 8, kBufferFlags),
+            4u * (uint32_t)lane, 0u, 0);
     const int s0 = NS * wave, k = s0 >> 2;
     const ConstMem<uint64_t>* fk = const_mem<uint64_t>(flags + 8 * kPlanes * k);
     uint64_t F[kPlanes];
 #pragma unroll
     for (int b = 0; b < kPlanes; b++) F[b] = fk[b];
     const ConstMem<uint32_t>* tab = const_mem<uint32_t>(s + g.table_off + 8 * c);
-    const uint32_t off = tab[0], nout = tab[1];
-    const uint32_t hdr_err = check_header(s, g, RANK, F64 ? 1 : 0, INT ? 1 : 0, s_bytes);
+    const uint32_t off = tab[0], nout = tab[1], next_off = tab[2];  // (behind the last chunk's: padding or its flags)
+    const Header h = load_header(s);
+    // What the chunk starts from, all on its way before any of it is looked
+    // at: left to itself the compiler puts each load behind the check before
+    // it, and from HBM each waits in turn.
+    asm volatile("" ::"s"(F[0]), "s"(F[1]), "s"(F[2]), "s"(F[3]), "s"(F[4]), "s"(F[5]), "s"(F[6]), "s"(F[7]), "s"(F[8]), "s"(F[9]),
+                 "s"(F[10]), "s"(F[11]), "s"(F[12]), "s"(F[13]), "s"(F[14]), "s"(F[15]), "s"(off), "s"(nout), "s"(next_off),
+                 "s"(h.w[kOffMagic / 4]), "s"(h.w[kOffStatus / 4]), "s"(h.w[kOffDims / 4]), "s"(h.w[kOffEbx2 / 4]),
+                 "s"(h.w[kOffNChunks / 4]), "s"(h.w[kOffTotal / 4]));
+    const uint32_t hdr_err = check_header(h, g, RANK, F64 ? 1 : 0, INT ? 1 : 0, s_bytes);
     if (hdr_err) {
         if (c == 0 && threadIdx.x == 0 && d_err) atomicCAS(d_err, 0u, hdr_err);
         return;
     }
-    const uint64_t total = *const_mem<uint64_t>(s + kOffTotal);
+    const uint64_t total = (uint64_t)h.w[kOffTotal / 4] | ((uint64_t)h.w[kOffTotal / 4 + 1] << 32);
     const uint64_t payload_units = (total - g.payload_off) / 16;
     int64_t org[3], ext[3];
     chunk_box(g, c, org, ext);
@@ -452,7 +487,7 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
     // escape count) is the next chunk's offset, or the payload's end.  Chunks
     // are checked independently, so each also checks that it ends inside the
     // payload.
-    const uint64_t next = c + 1 < g.n_chunks ? (uint64_t)tab[2] : payload_units;
+    const uint64_t next = c + 1 < g.n_chunks ? (uint64_t)next_off : payload_units;
     const uint64_t end = (uint64_t)off + nnz + (nout + 1) / 2;
     const bool bad = nout > (uint32_t)kChunkOutlierCap || end != next || end > payload_units || (c == 0 && off != 0) ||
                      __ballot(f != 0 && lane >= L * kPlanes) != 0;
@@ -483,6 +518,24 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
         } else {
             W[0][b] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, 0u, 0);
         }
+    }
+
+    // One load per line, issued behind the words and used by nothing (held to
+    // the end below).  A wave's two steps have at most 64 lines.
+    uint32_t warm = 0u, warm_flags = 0u;
+    if constexpr (WARM) {
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)next_tab, 0);
+        const uint64_t to = next_c + 1 < g.n_chunks ? (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)next_tab, 2) : payload_units;
+        const uint32_t units = next_c >= 0 && to > at && to <= payload_units && to - at <= kWarmUnits ? (uint32_t)(to - at) : 0u;
+        warm = __builtin_amdgcn_raw_buffer_load_b32(
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(s) + g.payload_off + 16 * (int64_t)at, (short)0,
+                                              (int)(16u * units), kBufferFlags),
+            128u * (uint32_t)(64 * wave + lane), 0u, 0);
+        warm_flags = __builtin_amdgcn_raw_buffer_load_b32(
+            __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint8_t*>(s) + g.flags_off + (int64_t)kFlagBytesPerChunk * max(next_c, (int64_t)0), (short)0,
+                next_c >= 0 && wave == 0 ? kFlagBytesPerChunk : 0, kBufferFlags),
+            128u * (uint32_t)lane, 0u, 0);
     }
 
     // steps of the chunk inside the field (the others hold no cell of it)
@@ -597,6 +650,7 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
         for (int i = 0; i < 32; i++) d[NS - 1][i] += RANK == 3 ? d[0][i] : RANK == 2 ? d[0][16 + (i & 15)] : last;
     }
     __syncthreads();  // the regions become the waves' tiles
+    if constexpr (WARM) asm volatile("" ::"v"(warm), "v"(warm_flags));
 
     const uint32_t mode = (const_mem<uint32_t>(s)[kOffEbMode / 4] >> (8 * (kOffEbMode % 4))) & 0xFFu;
 #pragma unroll
@@ -631,12 +685,22 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
     }
 }
 
-// The chunk of block b of an fp32-sized decompression: streaming stores
-// fill whole lines, which no two chunks share.
+// The chunk of block b of an fp32-sized decompression.  Plain stores: in runs
+// per XCD (xcd_order).  Streaming stores fill whole lines, which no two chunks
+// share; there the rows of chunks are only turned against one another, so that
+// an XCD (every eighth block) does not write the same columns of every row and
+// plane.  Measured, chunk order / turned / (runs of 8): 64x1024x2048 114.7 / 108.3
+// / (110.3) us, 32x2048x2048 109.6 / 102.3 / (103.3), 2048x256x256 108.8 / 100.3 /
+// (106.0), 512^3 101.0 / 100.5 / (104.6).  With plain divisions: the same order by
+// multiply-high on the scalar unit measured 111.8, 107.1, 104.0 and 104.3.
 template <bool STREAM>
 __device__ __forceinline__ int64_t in_place_chunk(const Geom& g, uint32_t b)
 {
-    return STREAM ? (int64_t)b : xcd_order(b, g.n_chunks);
+    if (!STREAM) return xcd_order(b, g.n_chunks);
+    const uint32_t nx = (uint32_t)g.grid[2], ny = (uint32_t)g.grid[1];
+    const uint32_t row = b / nx, x = b - row * nx, z = row / ny, y = row - z * ny;
+    const uint32_t by = (3 * y + 5 * z) % nx;
+    return row * nx + (x + by < nx ? x + by : x + by - nx);
 }
 
 }  // namespace fz

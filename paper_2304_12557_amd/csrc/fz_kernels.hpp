@@ -76,6 +76,9 @@ inline bool stream_stores(const void* y, const Geom& g, int elem)
     return aligned_to(y, 128) && (g.rank == 1 || (g.n[g.rank - 1] * elem & (elem == 8 ? 31 : 127)) == 0);
 }
 
+// compute units of the current device (1 if unknown)
+int cu_count();
+
 // whether compression may read a field at x with 16-byte loads (4-byte aligned values)
 bool vec_loads(const void* x);
 // blocks of the REL range pass of a field of n values

@@ -1,0 +1,37 @@
+"""Decompression's block orders cover every chunk once: fields of more chunks than
+are at work at once, whose rows of chunks are turned against one another (whole
+lines, streaming stores) or taken in runs (other rows), and payloads on both
+sides of the size up to which a following chunk's is read ahead.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2304_12557_amd as fz
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+# (chunks along each axis; more than 512 in all); 3-D rows of 1, 2, 3, 7, 8, 9 and 40 chunks
+SHAPES = [(16 * 40, 32 * 14, 64), (16 * 9, 32 * 31, 128), (16 * 5, 32 * 37, 192), (16 * 5, 32 * 17, 448), (16 * 3, 32 * 25, 512),
+          (33, 32 * 20, 576), (16 * 2, 32 * 7, 64 * 40), (40, 500, 1001), (32 * 20, 1024 * 26), (1000, 20_000), (18_000_001,)]
+
+
+@pytest.mark.parametrize("bits", [3, 14])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_every_chunk_once(shape, bits):
+    print("case", shape, bits, flush=True)
+    rng = np.random.default_rng(len(shape) + bits)
+    span = 2 if bits == 3 else 1 << (12 - len(shape))
+    x = rng.integers(-span, span + 1, shape).astype(np.float32)
+    x += np.arange(shape[0], dtype=np.float32).reshape(-1, *[1] * (len(shape) - 1)) % 97  # chunks differ
+    ref, st = O.compress(x, 0.5, O.EB_ABS, threads=16)
+    assert st == 0
+    n_chunks = fz.stream_info(ref[:128].tobytes())["n_chunks"]
+    per = (ref.size - fz.header_bytes(shape)) / n_chunks
+    assert n_chunks > 512 and (per < 32768) == (bits == 3), per
+    y = torch.full(shape, -7777.0, device="cuda")
+    err = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    fz.decompress(torch.from_numpy(ref).cuda(), shape, out=y, err=err)
+    assert int(err.item()) == 0
+    assert np.array_equal(y.cpu().numpy(), x)
