@@ -8,21 +8,61 @@
 
 namespace fz {
 
-// 128 registers (4 waves per SIMD) and 9 KB of LDS a wave: two workgroups per
-// CU, or more where they have fewer waves (chunk_waves), whose regions are the
-// launch's dynamic LDS.  first: the launch's first block of the field
-// (launch_chunks); ahead: how many blocks are at work at once.
+// The last layer of a field's chunks (2-D, 3-D), if the field reaches at most 8
+// of their 16 steps: as waves take two steps each, 1, 2 or 4 of them run such a
+// chunk, and a workgroup of 8 several chunks.  With all 8 on one chunk, those
+// without a step only hold wave slots and LDS (1x2048x2048: 19.8 us, now 10.8;
+// 4x2048x2048: 27.4, now 17.8; 33x2016x1984, a third of whose chunks have one
+// plane: 116.6, now 104.7).
+struct ThinLayer {
+    uint32_t full;  // chunks before it, one per block
+    int lg;         // log2 of the waves that run one of its chunks
+    uint32_t blocks(const Geom& g) const
+    {
+        const uint32_t per = 8u >> lg;
+        return full + ((uint32_t)g.n_chunks - full + per - 1) / per;
+    }
+};
+// at_once: the blocks at work at once.  Chunks that find room in the last round
+// of the blocks before them are better spread over the CUs it leaves idle
+// (100x500x500: 34.3 us shared, 30.0 not).
+static ThinLayer thin_layer(const Geom& g, uint32_t at_once)
+{
+    const ThinLayer none{(uint32_t)g.n_chunks, 3};
+    if (g.rank == 1) return none;
+    const int64_t e = g.n[0] - (g.grid[0] - 1) * g.box[0], steps = g.rank == 3 ? e : (e + 1) / 2;
+    if (steps > 8) return none;
+    const ThinLayer t{(uint32_t)(g.n_chunks - g.grid[1] * g.grid[2]), steps > 4 ? 2 : steps > 2 ? 1 : 0};
+    const uint32_t last = t.full % at_once, room = t.full && !last ? 0u : at_once - last;
+    return none.full - t.full > room ? t : none;
+}
+
+// 128 registers (4 waves per SIMD) and 72 KB of LDS: two workgroups per CU.
+// first: the launch's first block of the field (launch_chunks); ahead: how many
+// blocks are at work at once.
 template <int RANK, bool STREAM>
 __global__ __launch_bounds__(512, 4) void k_decompress(const uint8_t* __restrict__ s, uint64_t sb,
                                                        float* __restrict__ y, Geom g, uint32_t* d_err, uint32_t first,
-                                                       uint32_t ahead)
+                                                       uint32_t ahead, ThinLayer thin)
 {
-    extern __shared__ uint4 lds[];
-    DecompressLds<8>& S = *reinterpret_cast<DecompressLds<8>*>(lds);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __shared__ DecompressLds<8> S;
+    int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = 8, w0 = 0;
     const uint32_t b = first + blockIdx.x;
-    decompress_chunk<RANK, float, 8, true>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g, b), wave, threadIdx.x & 63, S,
-                                           b + ahead < (uint64_t)g.n_chunks ? in_place_chunk<STREAM>(g, b + ahead) : -1);
+    int64_t c, next = -1;
+    if (b < thin.full) {
+        c = in_place_chunk<STREAM>(g, b, thin.full);
+        if (b + ahead < thin.full) next = in_place_chunk<STREAM>(g, b + ahead, thin.full);
+    } else {
+        const int lg = thin.lg, per = 8 >> lg;
+        c = (int64_t)thin.full + (int64_t)(b - thin.full) * per + (wave >> lg);
+        if (c >= g.n_chunks) return;
+        if (c + (int64_t)ahead * per < g.n_chunks) next = c + (int64_t)ahead * per;
+        waves = 1 << lg;
+        w0 = wave & ~(waves - 1);
+        wave -= w0;
+    }
+    decompress_chunk<RANK, float, 8, true>(s, sb, y, STREAM, g, d_err, c, wave, threadIdx.x & 63,
+                                           *reinterpret_cast<DecompressLds<8>*>(S.region[w0]), next, waves);
 }
 
 // the same with NW waves, one step each (fields with few chunks; launched
@@ -48,30 +88,18 @@ __global__ void k_set_u32(uint32_t* p, uint32_t v)
 // waves share a CU (256^3, 512 chunks: 21 us against 30 us).
 constexpr int64_t kSplitChunks = 256;
 
-// Waves of a chunk's workgroup, two steps each.  In a field of one layer of
-// chunks that is thinner than they are (2-D, 3-D), all chunks have the same few
-// steps, and waves without one would only hold LDS and wave slots (1x2048x2048:
-// 8 waves 19.8 us, 1 wave 11.0; 4x2048x2048: 27.4, 2 waves 16.5).  Five to seven
-// waves leave room for two or three workgroups a CU only: 8 waves there
-// (12x1024x2048: 6 waves 31.6 us, 8 waves 27.2).
-static int chunk_waves(const Geom& g)
-{
-    if (g.rank == 1 || g.grid[0] > 1) return 8;
-    const int64_t steps = g.rank == 3 ? g.n[0] : (g.n[0] + 1) / 2;
-    return steps <= 8 ? (int)((steps + 1) / 2) : 8;
-}
-
 template <int RANK, bool STREAM>
 static hipError_t launch_rank(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
-    const int waves = chunk_waves(g);
-    const uint32_t ahead = (uint32_t)(cu_count() * (16 / waves));
-    return launch_chunks(g.n_chunks, [&](uint32_t first, dim3 blocks) {
-        if (g.n_chunks <= kSplitChunks)
-            hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), blocks, dim3(1024), 0, st, s, sb, y, g, d_err);
-        else
-            hipLaunchKernelGGL((k_decompress<RANK, STREAM>), blocks, dim3(64 * waves), waves * 4 * kRegionWords, st, s, sb, y,
-                               g, d_err, first, ahead);
+    if (g.n_chunks <= kSplitChunks) {
+        hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), dim3((unsigned)g.n_chunks), dim3(1024), 0, st, s, sb, y, g,
+                           d_err);
+        return hipGetLastError();
+    }
+    const uint32_t ahead = 2u * (uint32_t)cu_count();
+    const ThinLayer thin = thin_layer(g, ahead);
+    return launch_chunks(thin.blocks(g), [&](uint32_t first, dim3 blocks) {
+        hipLaunchKernelGGL((k_decompress<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first, ahead, thin);
     });
 }
 

@@ -102,6 +102,7 @@ __device__ __forceinline__ void wave_lds_sync()
 // wave's 16-byte accesses over the banks.  fp64 steps pass through it half by
 // half.
 constexpr int kRegionWords = 2048 + 4 * (2048 / 32);
+constexpr int kRegionBad = 2048;  // beside the carry: whether the wave found a bad escape
 // places in a 2-D or 1-D tile, written so that all but the lane's part is an
 // immediate offset: value i sits at i + 4 (i / 32), double i (of 1024, which
 // fill a region) at i + 2 (i / 16)
@@ -407,12 +408,15 @@ __device__ __forceinline__ void step_prefix(int (&d)[32], int lane)
 // 134.7, 121.6 / 128.6.
 constexpr uint32_t kWarmUnits = 32768 / 16;
 
-// Decompress chunk c of a field with a workgroup of NW waves; wave w runs
-// the 16 / NW steps from w * 16 / NW.  A stream that fails a check writes an
-// fz_status code to *d_err (if given) and leaves the chunk's output
-// untouched.  No byte at or past s + s_bytes is read: the header's total is
-// checked against s_bytes, and every chunk's payload against the total.
-// All checks give the same result in every wave, so the waves return together.
+// Decompress chunk c of a field with `waves` waves of a workgroup, whose LDS
+// regions are S; wave w runs the 16 / NW steps from w * 16 / NW, and waves = NW
+// unless the chunk has no cells past the steps of fewer.  A stream that fails a
+// check writes an fz_status code to *d_err (if given) and leaves the chunk's
+// output untouched.  No byte at or past s + s_bytes is read: the header's total
+// is checked against s_bytes, and every chunk's payload against the total.
+// All checks give the same result in every wave of a chunk, so they return
+// together; between the waves of a workgroup's other chunks, which go on, the
+// barriers only count those left.
 //
 // Sweep dimension: what a step adds to the later ones is its last in-plane
 // prefix (3-D: the plane; 2-D: its second row; 1-D: its last value).  Each
@@ -436,7 +440,7 @@ constexpr uint32_t kWarmUnits = 32768 / 16;
 template <int RANK, typename T, int NW, bool WARM = false>
 __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, uint64_t s_bytes, T* __restrict__ y,
                                                  bool stream, const Geom& g, uint32_t* d_err, int64_t c, int wave, int lane,
-                                                 DecompressLds<NW>& S, int64_t next_c = -1)
+                                                 DecompressLds<NW>& S, int64_t next_c = -1, int waves = NW)
 {
     static_assert(NW == 8 || NW == 16, "2 or 1 steps per wave");
     constexpr int NS = kSteps / NW;
@@ -471,7 +475,7 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
                  "s"(h.w[kOffNChunks / 4]), "s"(h.w[kOffTotal / 4]));
     const uint32_t hdr_err = check_header(h, g, RANK, F64 ? 1 : 0, INT ? 1 : 0, s_bytes);
     if (hdr_err) {
-        if (c == 0 && threadIdx.x == 0 && d_err) atomicCAS(d_err, 0u, hdr_err);
+        if (c == 0 && wave == 0 && lane == 0 && d_err) atomicCAS(d_err, 0u, hdr_err);
         return;
     }
     const uint64_t total = (uint64_t)h.w[kOffTotal / 4] | ((uint64_t)h.w[kOffTotal / 4 + 1] << 32);
@@ -492,7 +496,7 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
     const bool bad = nout > (uint32_t)kChunkOutlierCap || end != next || end > payload_units || (c == 0 && off != 0) ||
                      __ballot(f != 0 && lane >= L * kPlanes) != 0;
     if (bad) {
-        if (threadIdx.x == 0 && d_err) atomicCAS(d_err, 0u, 6u);
+        if (wave == 0 && lane == 0 && d_err) atomicCAS(d_err, 0u, 6u);
         return;
     }
 
@@ -584,13 +588,6 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
         }
         __builtin_amdgcn_sched_barrier(0);  // one step's arrays at a time: 128 registers
     }
-    if (nout) {  // every escape code has its pair and every pair its escape code
-        if (__syncthreads_or(esc_bad)) {
-            if (threadIdx.x == 0 && d_err) atomicCAS(d_err, 0u, 6u);
-            return;
-        }
-    }
-
     // sums along the sweep dimension: what the wave's steps add to later ones
     // goes to its region, those of the waves before are added to its first
     // step, and that one to its second
@@ -625,7 +622,16 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
     };
     if (RANK >= 2) put_sum();
     else if (lane == 63) S.region[wave][0] = (uint32_t)(d[NS - 1][31] + (NS == 2 ? d[0][31] : 0));
+    if (nout) {
+        const bool any = __ballot(esc_bad != 0u) != 0;
+        if (lane == 0) S.region[wave][kRegionBad] = any ? 1u : 0u;
+    }
     __syncthreads();
+    if (nout && __ballot(S.region[lane < waves ? lane : 0][kRegionBad] != 0u)) {
+        // not every escape code has its pair, or not every pair its escape code
+        if (wave == 0 && lane == 0 && d_err) atomicCAS(d_err, 0u, 6u);
+        return;
+    }
     if (RANK >= 2) {
         // in groups of 4 waves: first the waves before in the group, then the
         // groups before, whose sum their last wave leaves in its region (no
@@ -693,10 +699,11 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
 // / (110.3) us, 32x2048x2048 109.6 / 102.3 / (103.3), 2048x256x256 108.8 / 100.3 /
 // (106.0), 512^3 101.0 / 100.5 / (104.6).  With plain divisions: the same order by
 // multiply-high on the scalar unit measured 111.8, 107.1, 104.0 and 104.3.
+// n: the chunks so ordered, whole layers of the field's.
 template <bool STREAM>
-__device__ __forceinline__ int64_t in_place_chunk(const Geom& g, uint32_t b)
+__device__ __forceinline__ int64_t in_place_chunk(const Geom& g, uint32_t b, int64_t n)
 {
-    if (!STREAM) return xcd_order(b, g.n_chunks);
+    if (!STREAM) return xcd_order(b, n);
     const uint32_t nx = (uint32_t)g.grid[2], ny = (uint32_t)g.grid[1];
     const uint32_t row = b / nx, x = b - row * nx, z = row / ny, y = row - z * ny;
     const uint32_t by = (3 * y + 5 * z) % nx;

@@ -1,5 +1,5 @@
-"""Decompression of fields of one layer of thin chunks: a chunk's workgroup has
-a wave per two steps that the field reaches, from 1 wave to 8.
+"""Decompression of fields whose last layer of chunks is thin: as many waves as it
+has pairs of steps run one of its chunks, and a workgroup several chunks.
 
 More than 256 chunks each (fewer take 16 waves whatever their depth); escapes in
 the first and the last step; the oracle's values bit for bit.
@@ -15,7 +15,11 @@ import synth
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(n, 1030, 530) for n in (1, 2, 3, 4, 5, 8, 9, 14, 15, 16, 17)] + [(n, 300_001) for n in (1, 2, 4, 5, 8, 13, 28, 29, 32, 33)]
-ALIGNED = [(2, 1056, 576), (6, 1056, 576), (3, 264 * 1024), (12, 264 * 1024)]  # rows of whole lines: streaming stores
+# a thin layer of more chunks than are at work at once, and whole layers before
+# one that does not fit the last round behind them; the last workgroup not full
+SHAPES += [(n, 1030, 1060) for n in (1, 2, 3, 5, 8)] + [(n, 560_001) for n in (1, 3, 8, 15)]
+SHAPES += [(n, 530, 1030) for n in (18, 20, 21, 24, 25, 33)] + [(n, 290_001) for n in (34, 37, 40, 47, 49, 65)]
+ALIGNED = [(33, 530, 1024), (36, 512, 1024), (38, 290 * 1024), (2, 1056, 576), (6, 1056, 576), (3, 264 * 1024), (12, 264 * 1024)]  # rows of whole lines: streaming stores
 
 
 def field(shape, escapes):
