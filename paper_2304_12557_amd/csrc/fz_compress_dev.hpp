@@ -60,7 +60,8 @@ struct CompressLds {
 };
 typedef __attribute__((address_space(3))) CompressLds LdsState;
 // The workgroup's slot of the scratch, used by layers that are coded out of
-// line: their bricks (16 KB per layer), then the chunk's escape pairs.
+// line: the words of their bricks (16 KB per layer; plane, step and lane, so that
+// each store and load moves whole lines), then the chunk's escape pairs.
 constexpr int kSlotPairs = kLayers * kPlanes * kPatches * 16;
 static_assert(kSlotPairs + kChunkOutlierCap * 8 == kStageSlotBytes, "slot layout");
 
@@ -620,7 +621,7 @@ __device__ __noinline__ uint32_t layer_wide(const float* __restrict__ x, const u
     const Geom g = *reinterpret_cast<const Geom*>(scr + kScratchGeomOff);
     const Lane l = lane_geo<RANK>(g, c, lane);
     uint2* pairs = reinterpret_cast<uint2*>(slot + kSlotPairs);
-    uint32_t* brick = reinterpret_cast<uint32_t*>(slot) + 4 * (k * kPlanes * kPatches + lane);
+    uint32_t* word = reinterpret_cast<uint32_t*>(slot) + 4 * k * kPlanes * kPatches + lane;
     uint32_t total = 0;
     float facc = 0.0f, v[32];
     int qp[32], carry = 0;
@@ -662,7 +663,7 @@ __device__ __noinline__ uint32_t layer_wide(const float* __restrict__ x, const u
         sign_magnitude(P);
         transpose16(P);
 #pragma unroll
-        for (int b = 0; b < 16; b++) brick[4 * 64 * b + t] = P[b] & keep;
+        for (int b = 0; b < 16; b++) word[64 * (4 * b + t)] = P[b] & keep;
     }
     return total;
 }
@@ -758,12 +759,11 @@ __device__ __forceinline__ void chunk_layer(const float* __restrict__ x, const u
         else wide = layer_fast<RANK, VEC4, QM, false>(x, g, l, wave, inv, lane, h, v, S.tile[wave], W, facc, first);
         if (wide) {
             nout = layer_wide<RANK, VEC4, QM>(x, scr, c, wave, inv, lane, slot, (LdsState*)&S);
-            const uint4* brick = reinterpret_cast<const uint4*>(slot) + wave * kPlanes * kPatches + lane;
+            const uint32_t* word = reinterpret_cast<const uint32_t*>(slot) + 4 * wave * kPlanes * kPatches + lane;
 #pragma unroll
-            for (int b = 0; b < kPlanes; b++) {
-                const uint4 w = brick[64 * b];
-                W[b][0] = w.x; W[b][1] = w.y; W[b][2] = w.z; W[b][3] = w.w;
-            }
+            for (int b = 0; b < kPlanes; b++)
+#pragma unroll
+                for (int t = 0; t < 4; t++) W[b][t] = word[64 * (4 * b + t)];
         }
         else if (escapes(first)) {  // the chunk's first cell, the only escape of layer 0
             nout = 1;
