@@ -258,8 +258,8 @@ int fz_decompress_global(const void *d_stream, size_t stream_bytes, float *d_out
 
 /* ------------------------------------------------------------ batches
  * Many fields of uneven rank and size in a fixed, small number of launches
- * (one persistent compression launch per rank and row-alignment class, over
- * every chunk of every field of that class; one decompression launch).  The
+ * (one persistent compression launch per rank, over every chunk of every field
+ * of that rank; one decompression launch, or several past 2^21 chunks).  The
  * bytes each field gets are exactly those of fz_compress / fz_decompress on
  * that field alone.
  *

@@ -5,11 +5,12 @@
 // table over the concatenated chunks of all fields.  Running a compression
 // plan enqueues a fixed sequence of launches whatever the number of fields:
 //   init (all fields) with the value range (REL fields) beside it -> eb (REL
-//   fields) -> one persistent compression launch per (rank, row-alignment)
-//   class present (at most six, usually three), each over every chunk of every
-//   field of its class, which also places the chunks and settles each field's
-//   status word
-// and a decompression plan one launch over every chunk of every field.  Each
+//   fields) -> one persistent compression launch per rank present, over every
+//   chunk of every field of that rank, which also places the chunks and settles
+//   each field's status word
+// and a decompression plan one launch over every chunk of every field (several
+// past kLaunchChunks).  (A class also tells whether a field's values are 4-byte
+// aligned; plans refuse others, see vec_loads.)  Each
 // field's bytes are exactly those of the per-field call: the per-chunk and
 // per-field device code is the same (fz_compress_dev.hpp,
 // fz_decompress_dev.hpp), only the mapping of workgroups to fields differs.

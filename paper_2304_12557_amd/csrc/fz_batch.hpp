@@ -20,7 +20,7 @@ struct CompressJob {
     Geom g;
     HeaderImage h;
     double eb;
-    int32_t key;  // rank * 2 + (16-byte aligned rows ? 1 : 0)
+    int32_t key;  // rank * 2 + (16-byte loads ? 1 : 0), see vec_loads
     int32_t rel;
     int64_t chunk0;     // first ticket of this field in its class's part of the chunk table
     int64_t chunkg;     // first entry of this field in the whole chunk table

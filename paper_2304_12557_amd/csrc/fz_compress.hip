@@ -158,7 +158,8 @@ static hipError_t mark(hipEvent_t e, hipStream_t st) { return e ? hipEventRecord
 
 // Whether the compression kernels may read the field with 16-byte loads (the
 // VEC4 instantiations): whenever its values are 4-byte aligned, whatever the
-// row length.  gfx950 buffer loads need only 4-byte alignment, and their range
+// row length.  Every entry point refuses other addresses, so that the
+// instantiations with one load per value are never launched.  gfx950 buffer loads need only 4-byte alignment, and their range
 // is checked per dword (measured: a 16-byte load straddling the end of the
 // range returns the dwords inside it and zeros for the rest), so a load that
 // runs past the field's last value still returns that value.  The values a

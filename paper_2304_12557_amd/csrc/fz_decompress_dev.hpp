@@ -3,7 +3,8 @@
 //
 // The inverse of the compression pass (Sec. 4.4 calls the two pipelines
 // symmetric).  A workgroup per chunk, its 16 steps shared out over the waves
-// (8 waves of 2 steps, or 16 of 1).  Each lane loads its steps' words of its
+// (8 waves of 2 steps, or 16 of 1; several chunks of a thin last layer to a
+// workgroup).  Each lane loads its steps' words of its
 // nonzero bricks (their positions follow from the bit flags by popcount and
 // mbcnt, Sec. 3.4), undoes the bitshuffle with the same in-register
 // transpose, decodes the sign-magnitude codes (Sec. 3.2), and inverts the
@@ -428,10 +429,11 @@ constexpr uint32_t kWarmUnits = 32768 / 16;
 // What bounds it: VALU issue (584 instructions per step and wave, 68 % of the
 // cycles on 512^3) with the stores behind it; two workgroups per CU overlap
 // one's loads and barriers with the other's arithmetic.  Measured against one
-// wave per chunk (4 waves for at most 512 chunks) before: 512^3 REL 1e-3
-// 113 -> 107 us, 100x500x500 50 -> 34 us, 101x499x501 68 -> 36 us, 5001x5003
-// 69 -> 32 us, 2^26 values 64 -> 52 us, 1800x3600 19 -> 12 us, 64^3 18 -> 11 us
-// (times of a pass, rotating over three fields).
+// wave per chunk (4 waves for at most 512 chunks) before, REL 1e-3, buffers in
+// turn / from cold caches: 512^3 113 -> 101 / 127 -> 116 us, 100x500x500 50 -> 30 /
+// 54 -> 32, 8192^2 55 -> 51 / 59 -> 59, 2^26 values 63 -> 53 / 70 -> 62, 1800x3600
+// 19 -> 12 / 26 -> 15, 64^3 17 -> 10 / 26 -> 13.  Without the reads ahead (next_c)
+// the large ones were slower from cold caches: 512^3 141, 8192^2 70 us.
 //
 // WARM: next_c is the chunk that takes this one's place on the device (-1: none).  Its
 // flags and payload are brought into the L2 while this one is worked on: the

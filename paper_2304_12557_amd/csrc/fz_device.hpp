@@ -19,10 +19,9 @@ typedef double fz_f64x2 __attribute__((ext_vector_type(2)));
 // cache policy of a buffer access: nontemporal (the nt bit).  Used where a
 // kernel streams data it never touches again -- the reconstructed field,
 // the range pass over the input -- so that the lines do not displace what
-// the next kernel reads (measured: the 512^3 decompression 137 -> 116 us,
-// the range pass about 9 us faster).  Only for stores that fill whole
-// 128-byte lines per instruction: partial-line nontemporal stores lose the
-// merging in L2 (measured 3-6x slower).
+// the next kernel reads.  fp32 stores use it only where every instruction fills
+// whole 128-byte lines, as partial lines lose the merging in the L2; which
+// outputs are streamed, and both sides measured: stream_stores.
 constexpr int kCacheStream = 2;
 // lane l receives lane l-1's value (DPP wave_shr:1).  Lane 0 receives an
 // unspecified value: the compiler may leave the DPP destination of a lane
@@ -35,11 +34,6 @@ __device__ __forceinline__ int shift_up1_raw(int v)
 __device__ __forceinline__ uint32_t shift_up1_zero(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, true);
-}
-__device__ __forceinline__ int shift_up1(int v, int lane)
-{
-    const int r = shift_up1_raw(v);
-    return lane == 0 ? 0 : r;
 }
 
 // value of `v` held by lane - SH within the same row of 16 lanes (0 for the
@@ -172,14 +166,6 @@ __device__ __forceinline__ float pw_dequant(int q, uint32_t step)
     return __uint_as_float(b | (q < 0 ? 0x80000000u : 0u));
 }
 
-// one value through the stream's quantizer; acc flags NaN/Inf (and in the
-// grid modes |x * inv| >= 2^31)
-__device__ __forceinline__ int prequant(float v, const Quant& z, uint32_t& acc)
-{
-    const int q = prequant(v, z.inv, acc);
-    return z.step ? pw_quant(v, z) : q;
-}
-
 typedef short fz_short2 __attribute__((ext_vector_type(2)));
 
 // Sign-magnitude 16-bit codes of packed 16-bit deltas, in place (Sec. 3.2:
@@ -194,7 +180,6 @@ __device__ __forceinline__ void sign_magnitude(uint32_t (&P)[16])
     }
 }
 constexpr uint32_t kEscapeLimit = 65534u;  // d + 32767 above this (as unsigned): an escape
-constexpr int kMaxCodeDelta = 32767;
 
 // In-register bit transpose: on entry P[i] holds code i (low half) and code
 // i+16 (high half); on exit P[b] bit m = bit b of code m (Sec. 3.3's

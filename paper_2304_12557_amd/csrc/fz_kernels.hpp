@@ -65,12 +65,14 @@ size_t global_work_bytes(const Geom& g);
 // Whether a decompression's interior stores are streaming ones (nontemporal).
 // They pay where they fill whole 128-byte lines: the output starts on a line
 // and, past 1-D, its rows are whole lines (fp32 rows of 64 values per chunk
-// are two lines; measured: 512^3 107 us streaming, 155 us plain; 2^26 values
-// 1-D 52 / 75 us).  Otherwise two of a row segment's three lines are partial,
-// and plain stores merge them in the L2 (100x500x500: 48 us streaming, 40 us
-// plain).  Of an fp64 segment's five lines only the two ends are partial;
-// there streaming pays for rows of whole 32-byte pieces (the same field in
-// double, round trip: 214 us streaming, 225 us plain).
+// are two lines; three outputs in turn, streaming / plain: 512^3 102 / 113 us,
+// 2^26 values 1-D 53 / 63 us; from cold caches the same within 5 %).  Otherwise
+// two of a row segment's three lines are partial, and plain stores merge them
+// in the L2 (100x500x500: 43 / 30 us).  Of an fp64 segment's five lines only the
+// two ends are partial, and rows of whole 32-byte pieces are streamed too, for
+// what the stores leave in the caches: 100x500x500 in turn 54 / 57 us, round
+// trip of 250x500x500 426 / 441 us.  It is not so everywhere (round trip of
+// 100x500x500 185 / 177 us; from cold caches 60 / 47 us).
 inline bool stream_stores(const void* y, const Geom& g, int elem)
 {
     return aligned_to(y, 128) && (g.rank == 1 || (g.n[g.rank - 1] * elem & (elem == 8 ? 31 : 127)) == 0);
