@@ -8,6 +8,27 @@
 
 namespace fz {
 
+// 128 registers (4 waves per SIMD) and 72 KB of LDS: two workgroups per CU.
+template <int RANK, bool STREAM>
+__global__ __launch_bounds__(512, 4) void k_decompress(const uint8_t* __restrict__ s, uint64_t sb,
+                                                       float* __restrict__ y, Geom g, uint32_t* d_err)
+{
+    __shared__ DecompressLds<8> S;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    decompress_chunk<RANK, float, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g, blockIdx.x), wave, threadIdx.x & 63, S);
+}
+
+// the same with NW waves, one step each (fields with few chunks; launched
+// with NW = 16)
+template <int RANK, bool STREAM, int NW>
+__global__ __launch_bounds__(64 * NW, 4) void k_decompress_split(const uint8_t* __restrict__ s, uint64_t sb,
+                                                                 float* __restrict__ y, Geom g, uint32_t* d_err)
+{
+    __shared__ DecompressLds<NW> S;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    decompress_chunk<RANK, float, NW>(s, sb, y, STREAM, g, d_err, blockIdx.x, wave, threadIdx.x & 63, S);
+}
+
 // The last layer of a field's chunks (2-D, 3-D), if the field reaches at most 8
 // of their 16 steps: as waves take two steps each, 1, 2 or 4 of them run such a
 // chunk, and a workgroup of 8 several chunks.  With all 8 on one chunk, those
@@ -37,21 +58,22 @@ static ThinLayer thin_layer(const Geom& g, uint32_t at_once)
     return none.full - t.full > room ? t : none;
 }
 
-// 128 registers (4 waves per SIMD) and 72 KB of LDS: two workgroups per CU.
-// first: the launch's first block of the field (launch_chunks); ahead: how many
-// blocks are at work at once.
+// k_decompress for fields of more chunks than are at work at once (`ahead`): a
+// workgroup reads ahead for the chunk that takes its place, chunks are taken in
+// turned_chunk's order, and a thin last layer shares workgroups.  first: the
+// launch's first block of the field (launch_chunks).
 template <int RANK, bool STREAM>
-__global__ __launch_bounds__(512, 4) void k_decompress(const uint8_t* __restrict__ s, uint64_t sb,
-                                                       float* __restrict__ y, Geom g, uint32_t* d_err, uint32_t first,
-                                                       uint32_t ahead, ThinLayer thin)
+__global__ __launch_bounds__(512, 4) void k_decompress_ahead(const uint8_t* __restrict__ s, uint64_t sb,
+                                                             float* __restrict__ y, Geom g, uint32_t* d_err, uint32_t first,
+                                                             uint32_t ahead, ThinLayer thin)
 {
     __shared__ DecompressLds<8> S;
     int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = 8, w0 = 0;
     const uint32_t b = first + blockIdx.x;
     int64_t c, next = -1;
     if (b < thin.full) {
-        c = in_place_chunk<STREAM>(g, b, thin.full);
-        if (b + ahead < thin.full) next = in_place_chunk<STREAM>(g, b + ahead, thin.full);
+        c = turned_chunk<RANK, STREAM>(g, b, thin.full);
+        if (b + ahead < thin.full) next = turned_chunk<RANK, STREAM>(g, b + ahead, thin.full);
     } else {
         const int lg = thin.lg, per = 8 >> lg;
         c = (int64_t)thin.full + (int64_t)(b - thin.full) * per + (wave >> lg);
@@ -65,17 +87,6 @@ __global__ __launch_bounds__(512, 4) void k_decompress(const uint8_t* __restrict
                                            *reinterpret_cast<DecompressLds<8>*>(S.region[w0]), next, waves);
 }
 
-// the same with NW waves, one step each (fields with few chunks; launched
-// with NW = 16)
-template <int RANK, bool STREAM, int NW>
-__global__ __launch_bounds__(64 * NW, 4) void k_decompress_split(const uint8_t* __restrict__ s, uint64_t sb,
-                                                                 float* __restrict__ y, Geom g, uint32_t* d_err)
-{
-    __shared__ DecompressLds<NW> S;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    decompress_chunk<RANK, float, NW>(s, sb, y, STREAM, g, d_err, blockIdx.x, wave, threadIdx.x & 63, S);
-}
-
 __global__ void k_set_u32(uint32_t* p, uint32_t v)
 {
     if (threadIdx.x == 0) *p = v;
@@ -85,22 +96,29 @@ __global__ void k_set_u32(uint32_t* p, uint32_t v)
 // with 16 waves per chunk: a lone workgroup of 8 waves leaves a SIMD with two
 // waves to hide each other's latency, one of 16 with four (128x128x256, 128
 // chunks: 11.0 us against 11.2-12.0 us a pass).  Beyond, two workgroups of 8
-// waves share a CU (256^3, 512 chunks: 21 us against 30 us).
+// waves share a CU (256^3, 512 chunks: 21 us against 30 us).  Fields of more
+// chunks than that take k_decompress_ahead; without a chunk to read ahead for it
+// is the slower one (96x100352, 294 chunks: 12.8 us, ahead 14.8; 48x512x512, 384:
+// 15.5 and 17.0).
 constexpr int64_t kSplitChunks = 256;
 
 template <int RANK, bool STREAM>
 static hipError_t launch_rank(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
-    if (g.n_chunks <= kSplitChunks) {
-        hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), dim3((unsigned)g.n_chunks), dim3(1024), 0, st, s, sb, y, g,
-                           d_err);
-        return hipGetLastError();
+    const uint32_t at_once = 2u * (uint32_t)cu_count();
+    if (g.n_chunks > at_once) {
+        const ThinLayer thin = thin_layer(g, at_once);
+        return launch_chunks(thin.blocks(g), [&](uint32_t first, dim3 blocks) {
+            hipLaunchKernelGGL((k_decompress_ahead<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first, at_once,
+                               thin);
+        });
     }
-    const uint32_t ahead = 2u * (uint32_t)cu_count();
-    const ThinLayer thin = thin_layer(g, ahead);
-    return launch_chunks(thin.blocks(g), [&](uint32_t first, dim3 blocks) {
-        hipLaunchKernelGGL((k_decompress<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first, ahead, thin);
-    });
+    const dim3 blocks((unsigned)g.n_chunks);
+    if (g.n_chunks <= kSplitChunks)
+        hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), blocks, dim3(1024), 0, st, s, sb, y, g, d_err);
+    else
+        hipLaunchKernelGGL((k_decompress<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err);
+    return hipGetLastError();
 }
 
 hipError_t launch_decompress(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)

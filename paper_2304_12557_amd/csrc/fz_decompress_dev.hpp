@@ -468,13 +468,14 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
     const ConstMem<uint32_t>* tab = const_mem<uint32_t>(s + g.table_off + 8 * c);
     const uint32_t off = tab[0], nout = tab[1], next_off = tab[2];  // (behind the last chunk's: padding or its flags)
     const Header h = load_header(s);
-    // What the chunk starts from, all on its way before any of it is looked
-    // at: left to itself the compiler puts each load behind the check before
+    // WARM: what the chunk starts from, all on its way before any of it is looked
+    // at; left to itself the compiler puts each load behind the check before
     // it, and from HBM each waits in turn.
-    asm volatile("" ::"s"(F[0]), "s"(F[1]), "s"(F[2]), "s"(F[3]), "s"(F[4]), "s"(F[5]), "s"(F[6]), "s"(F[7]), "s"(F[8]), "s"(F[9]),
-                 "s"(F[10]), "s"(F[11]), "s"(F[12]), "s"(F[13]), "s"(F[14]), "s"(F[15]), "s"(off), "s"(nout), "s"(next_off),
-                 "s"(h.w[kOffMagic / 4]), "s"(h.w[kOffStatus / 4]), "s"(h.w[kOffDims / 4]), "s"(h.w[kOffEbx2 / 4]),
-                 "s"(h.w[kOffNChunks / 4]), "s"(h.w[kOffTotal / 4]));
+    if constexpr (WARM)
+        asm volatile("" ::"s"(F[0]), "s"(F[1]), "s"(F[2]), "s"(F[3]), "s"(F[4]), "s"(F[5]), "s"(F[6]), "s"(F[7]), "s"(F[8]), "s"(F[9]),
+                     "s"(F[10]), "s"(F[11]), "s"(F[12]), "s"(F[13]), "s"(F[14]), "s"(F[15]), "s"(off), "s"(nout), "s"(next_off),
+                     "s"(h.w[kOffMagic / 4]), "s"(h.w[kOffStatus / 4]), "s"(h.w[kOffDims / 4]), "s"(h.w[kOffEbx2 / 4]),
+                     "s"(h.w[kOffNChunks / 4]), "s"(h.w[kOffTotal / 4]));
     const uint32_t hdr_err = check_header(h, g, RANK, F64 ? 1 : 0, INT ? 1 : 0, s_bytes);
     if (hdr_err) {
         if (c == 0 && wave == 0 && lane == 0 && d_err) atomicCAS(d_err, 0u, hdr_err);
@@ -695,17 +696,28 @@ __device__ __forceinline__ void decompress_chunk(const uint8_t* __restrict__ s, 
 
 // The chunk of block b of an fp32-sized decompression.  Plain stores: in runs
 // per XCD (xcd_order).  Streaming stores fill whole lines, which no two chunks
-// share; there the rows of chunks are only turned against one another, so that
-// an XCD (every eighth block) does not write the same columns of every row and
-// plane.  Measured, chunk order / turned / (runs of 8): 64x1024x2048 114.7 / 108.3
-// / (110.3) us, 32x2048x2048 109.6 / 102.3 / (103.3), 2048x256x256 108.8 / 100.3 /
-// (106.0), 512^3 101.0 / 100.5 / (104.6).  With plain divisions: the same order by
-// multiply-high on the scalar unit measured 111.8, 107.1, 104.0 and 104.3.
-// n: the chunks so ordered, whole layers of the field's.
+// share: in order.
 template <bool STREAM>
-__device__ __forceinline__ int64_t in_place_chunk(const Geom& g, uint32_t b, int64_t n)
+__device__ __forceinline__ int64_t in_place_chunk(const Geom& g, uint32_t b)
 {
-    if (!STREAM) return xcd_order(b, n);
+    return STREAM ? (int64_t)b : xcd_order(b, g.n_chunks);
+}
+
+// The same where more chunks than are at work at once make up n chunks in whole
+// layers.  With streaming stores each XCD (every eighth block) would write the
+// same columns of every row and plane, in 2-D where rows are multiples of 32 KB
+// the same 4 KB modulo 32 KB.  So in 3-D the rows of chunks are turned against one
+// another, and such 2-D fields take runs of 8 per XCD.  Measured, in order /
+// turned / (runs of 8): 64x1024x2048 114.7 / 108.3 / (110.3) us, 32x2048x2048 109.6
+// / 102.3 / (103.3), 2048x256x256 108.8 / 100.3 / (106.0), 512^3 101.0 / 100.5 /
+// (104.6); 2-D 64x2^20 70.7 / - / (58.7), 32x2^20 39.1 / - / (33.9), 1000x100000
+// 73.4 / - / (78.5).  With plain divisions: the turned order by multiply-high on
+// the scalar unit measured 111.8, 107.1, 104.0 and 104.3.
+template <int RANK, bool STREAM>
+__device__ __forceinline__ int64_t turned_chunk(const Geom& g, uint32_t b, int64_t n)
+{
+    if (!STREAM || (RANK == 2 && (g.n[1] & 8191) == 0)) return xcd_order(b, n);
+    if (RANK != 3) return b;
     const uint32_t nx = (uint32_t)g.grid[2], ny = (uint32_t)g.grid[1];
     const uint32_t row = b / nx, x = b - row * nx, z = row / ny, y = row - z * ny;
     const uint32_t by = (3 * y + 5 * z) % nx;

@@ -276,7 +276,7 @@ __global__ __launch_bounds__(512, 4) void k_decompress_int(const uint8_t* __rest
 {
     __shared__ DecompressLds<8> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    decompress_chunk<RANK, int32_t, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g, first + blockIdx.x, g.n_chunks), wave, threadIdx.x & 63, S);
+    decompress_chunk<RANK, int32_t, 8>(s, sb, y, STREAM, g, d_err, in_place_chunk<STREAM>(g, first + blockIdx.x), wave, threadIdx.x & 63, S);
 }
 
 // Carries of the field-global prefix sums.  Along axis ax the field splits
