@@ -704,7 +704,8 @@ def round_trips(xt, shape, eb, mode, buf, y, stream, reps, evict):
     pass (k_minmax, REL; it also writes the header image and clears the
     scratch) and the main kernel (k_compress, whose last workgroup also
     settles the status word); the decompression call is its one kernel
-    (k_decompress: no error word is passed)."""
+    (k_decompress, or k_decompress_ahead for more than 512 chunks: no error
+    word is passed)."""
     import numpy as np
     import torch
 

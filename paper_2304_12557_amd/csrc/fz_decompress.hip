@@ -1,6 +1,7 @@
 // fz_decompress.hip -- per-field decompression kernels of libfzmi (gfx950):
-// a workgroup of 8 waves per chunk, or for fields with few chunks one of 16
-// waves, running the device code of fz_decompress_dev.hpp.
+// a workgroup of 8 waves per chunk, of 16 for fields with few chunks, or of 8
+// that reads ahead for fields with many, running the device code of
+// fz_decompress_dev.hpp.
 #include <hip/hip_runtime.h>
 
 #include "fz_decompress_dev.hpp"
@@ -32,9 +33,9 @@ __global__ __launch_bounds__(64 * NW, 4) void k_decompress_split(const uint8_t* 
 // The last layer of a field's chunks (2-D, 3-D), if the field reaches at most 8
 // of their 16 steps: as waves take two steps each, 1, 2 or 4 of them run such a
 // chunk, and a workgroup of 8 several chunks.  With all 8 on one chunk, those
-// without a step only hold wave slots and LDS (1x2048x2048: 19.8 us, now 10.8;
-// 4x2048x2048: 27.4, now 17.8; 33x2016x1984, a third of whose chunks have one
-// plane: 116.6, now 104.7).
+// without a step only hold wave slots and LDS (1x2048x2048: 19.8 us, now 11.0;
+// 4x2048x2048: 27.4, now 17.7; 33x2016x1984, a third of whose chunks have one
+// plane: 116.6, now 103.6).
 struct ThinLayer {
     uint32_t full;  // chunks before it, one per block
     int lg;         // log2 of the waves that run one of its chunks
@@ -105,20 +106,20 @@ constexpr int64_t kSplitChunks = 256;
 template <int RANK, bool STREAM>
 static hipError_t launch_rank(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
-    const uint32_t at_once = 2u * (uint32_t)cu_count();
-    if (g.n_chunks > at_once) {
-        const ThinLayer thin = thin_layer(g, at_once);
-        return launch_chunks(thin.blocks(g), [&](uint32_t first, dim3 blocks) {
-            hipLaunchKernelGGL((k_decompress_ahead<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first, at_once,
-                               thin);
-        });
+    const dim3 all((unsigned)g.n_chunks);  // (fits one launch where it is used)
+    if (g.n_chunks <= kSplitChunks) {
+        hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), all, dim3(1024), 0, st, s, sb, y, g, d_err);
+        return hipGetLastError();
     }
-    const dim3 blocks((unsigned)g.n_chunks);
-    if (g.n_chunks <= kSplitChunks)
-        hipLaunchKernelGGL((k_decompress_split<RANK, STREAM, 16>), blocks, dim3(1024), 0, st, s, sb, y, g, d_err);
-    else
-        hipLaunchKernelGGL((k_decompress<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err);
-    return hipGetLastError();
+    const uint32_t at_once = 2u * (uint32_t)cu_count();
+    if (g.n_chunks <= at_once) {
+        hipLaunchKernelGGL((k_decompress<RANK, STREAM>), all, dim3(512), 0, st, s, sb, y, g, d_err);
+        return hipGetLastError();
+    }
+    const ThinLayer thin = thin_layer(g, at_once);
+    return launch_chunks(thin.blocks(g), [&](uint32_t first, dim3 blocks) {
+        hipLaunchKernelGGL((k_decompress_ahead<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first, at_once, thin);
+    });
 }
 
 hipError_t launch_decompress(const uint8_t* s, uint64_t sb, float* y, const Geom& g, uint32_t* d_err, hipStream_t st)

@@ -29,13 +29,13 @@ def res():
 
 
 def family(res, name):
-    out = {k: v for k, v in res.items() if k.startswith("_ZN2fz%d%s" % (len(name), name))}
+    out = {k: v for k, v in res.items() if k.startswith("_ZN2fz%d%s" % (len(name), name))}  # (the length ends the name)
     assert out, name
     return out
 
 
-@pytest.mark.parametrize("name,lds", [("k_decompress", 80 * KB), ("k_decompress64", 80 * KB), ("k_decompress_int", 80 * KB),
-                                      ("k_batch_decompress", 80 * KB), ("k_decompress_split", 160 * KB)])
+@pytest.mark.parametrize("name,lds", [("k_decompress", 80 * KB), ("k_decompress_ahead", 80 * KB), ("k_decompress64", 80 * KB),
+                                      ("k_decompress_int", 80 * KB), ("k_batch_decompress", 80 * KB), ("k_decompress_split", 160 * KB)])
 def test_decompression(res, name, lds):
     for k, v in family(res, name).items():
         assert v["waves_per_simd"] >= 4 and v["vgprs"] <= 128, (k, v)
