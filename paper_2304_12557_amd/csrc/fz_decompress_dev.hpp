@@ -20,6 +20,7 @@
 
 #include "fz_device.hpp"
 #include "fz_format.hpp"
+#include "fz_kernels.hpp"
 
 namespace fz {
 
@@ -711,17 +712,94 @@ __device__ __forceinline__ int64_t in_place_chunk(const Geom& g, uint32_t b)
 // turned / (runs of 8): 64x1024x2048 114.7 / 108.3 / (110.3) us, 32x2048x2048 109.6
 // / 102.3 / (103.3), 2048x256x256 108.8 / 100.3 / (106.0), 512^3 101.0 / 100.5 /
 // (104.6); 2-D 64x2^20 70.7 / - / (58.7), 32x2^20 39.1 / - / (33.9), 1000x100000
-// 73.4 / - / (78.5).  With plain divisions: the turned order by multiply-high on
-// the scalar unit measured 111.8, 107.1, 104.0 and 104.3.
-template <int RANK, bool STREAM>
+// 73.4 / - / (78.5).  fp64 rows that are no whole lines share them as plain fp32
+// stores do, and short rows of chunks lose by turning: runs (fp64, turned / runs:
+// 32x1024x2048 104.6 / 118.7, 256x512x512 106.9 / 109.9, 1024x256x256 107.4 / 97.8).
+// With plain divisions: by multiply-high on the scalar unit the turned order
+// measured 111.8, 107.1, 104.0 and 104.3 in the four fp32 fields.
+template <int RANK, typename T, bool STREAM>
 __device__ __forceinline__ int64_t turned_chunk(const Geom& g, uint32_t b, int64_t n)
 {
-    if (!STREAM || (RANK == 2 && (g.n[1] & 8191) == 0)) return xcd_order(b, n);
+    const uint32_t row_bytes = (uint32_t)g.n[RANK - 1] * (uint32_t)sizeof(T);  // (2-D, 3-D: below 2^28)
+    if (!STREAM || (RANK == 2 && (row_bytes & 32767u) == 0)) return xcd_order(b, n);
+    if (sizeof(T) == 8 && RANK >= 2 && ((row_bytes & 127u) != 0 || (RANK == 3 && g.grid[2] < (int)kXcdRun)))
+        return xcd_order(b, n);
     if (RANK != 3) return b;
     const uint32_t nx = (uint32_t)g.grid[2], ny = (uint32_t)g.grid[1];
     const uint32_t row = b / nx, x = b - row * nx, z = row / ny, y = row - z * ny;
     const uint32_t by = (3 * y + 5 * z) % nx;
     return row * nx + (x + by < nx ? x + by : x + by - nx);
+}
+
+// The last layer of a field's chunks (2-D, 3-D), if the field reaches at most 8
+// of their 16 steps: as waves take two steps each, 1, 2 or 4 of them run such a
+// chunk, and a workgroup of 8 several chunks.  With all 8 on one chunk, those
+// without a step only hold wave slots and LDS (1x2048x2048: 19.8 us, now 11.0;
+// 4x2048x2048: 27.4, now 17.7; 33x2016x1984, a third of whose chunks have one
+// plane: 116.6, now 103.6).
+struct ThinLayer {
+    uint32_t full;  // chunks before it, one per block
+    int lg;         // log2 of the waves that run one of its chunks
+    uint32_t blocks(const Geom& g) const
+    {
+        const uint32_t per = 8u >> lg;
+        return full + ((uint32_t)g.n_chunks - full + per - 1) / per;
+    }
+};
+// at_once: the blocks at work at once.  Chunks that find room in the last round
+// of the blocks before them are better spread over the CUs it leaves idle
+// (100x500x500: 34.3 us shared, 30.0 not).
+inline ThinLayer thin_layer(const Geom& g, uint32_t at_once)
+{
+    const ThinLayer none{(uint32_t)g.n_chunks, 3};
+    if (g.rank == 1) return none;
+    const int64_t e = g.n[0] - (g.grid[0] - 1) * g.box[0], steps = g.rank == 3 ? e : (e + 1) / 2;
+    if (steps > 8) return none;
+    const ThinLayer t{(uint32_t)(g.n_chunks - g.grid[1] * g.grid[2]), steps > 4 ? 2 : steps > 2 ? 1 : 0};
+    const uint32_t last = t.full % at_once, room = t.full && !last ? 0u : at_once - last;
+    return none.full - t.full > room ? t : none;
+}
+
+// The per-field kernel (fp32, fp64) for fields of more chunks than are at work at
+// once (`ahead`): a workgroup reads ahead for the chunk that takes its place,
+// chunks are taken in turned_chunk's order, and a thin last layer shares
+// workgroups.  first: the launch's first block of the field (launch_chunks).
+// fp64, one wave a chunk / 8 waves / this, us: 32x1024x2048 104 / 118 / 105, cold
+// 107 / 128 / 115; 4096x8192 cold 58 / 61 / 56; 40x1000000 cold 75 / 80 / 72.
+template <int RANK, typename T, bool STREAM>
+__global__ __launch_bounds__(512, 4) void k_decompress_ahead(const uint8_t* __restrict__ s, uint64_t sb,
+                                                             T* __restrict__ y, Geom g, uint32_t* d_err, uint32_t first,
+                                                             uint32_t ahead, ThinLayer thin)
+{
+    __shared__ DecompressLds<8> S;
+    int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = 8, w0 = 0;
+    const uint32_t b = first + blockIdx.x;
+    int64_t c, next = -1;
+    if (b < thin.full) {
+        c = turned_chunk<RANK, T, STREAM>(g, b, thin.full);
+        if (b + ahead < thin.full) next = turned_chunk<RANK, T, STREAM>(g, b + ahead, thin.full);
+    } else {
+        const int lg = thin.lg, per = 8 >> lg;
+        c = (int64_t)thin.full + (int64_t)(b - thin.full) * per + (wave >> lg);
+        if (c >= g.n_chunks) return;
+        if (c + (int64_t)ahead * per < g.n_chunks) next = c + (int64_t)ahead * per;
+        waves = 1 << lg;
+        w0 = wave & ~(waves - 1);
+        wave -= w0;
+    }
+    decompress_chunk<RANK, T, 8, true>(s, sb, y, STREAM, g, d_err, c, wave, threadIdx.x & 63,
+                                           *reinterpret_cast<DecompressLds<8>*>(S.region[w0]), next, waves);
+}
+
+template <int RANK, typename T, bool STREAM>
+inline hipError_t launch_ahead(const uint8_t* s, uint64_t sb, T* y, const Geom& g, uint32_t* d_err, uint32_t at_once,
+                               hipStream_t st)
+{
+    const ThinLayer thin = thin_layer(g, at_once);
+    return launch_chunks(thin.blocks(g), [&](uint32_t first, dim3 blocks) {
+        hipLaunchKernelGGL((k_decompress_ahead<RANK, T, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first, at_once,
+                           thin);
+    });
 }
 
 }  // namespace fz

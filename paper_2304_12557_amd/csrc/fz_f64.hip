@@ -230,11 +230,11 @@ hipError_t launch_f64_front(const double* x, uint8_t* out, const Geom& g, const 
 // ------------------------------------------------------------ decompression
 template <int RANK, bool STREAM>
 __global__ __launch_bounds__(512, 4) void k_decompress64(const uint8_t* __restrict__ s, uint64_t sb, double* __restrict__ y,
-                                                         Geom g, uint32_t* d_err, uint32_t first)
+                                                         Geom g, uint32_t* d_err)
 {
     __shared__ DecompressLds<8> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    decompress_chunk<RANK, double, 8>(s, sb, y, STREAM, g, d_err, xcd_order(first + blockIdx.x, g.n_chunks), wave, threadIdx.x & 63, S);
+    decompress_chunk<RANK, double, 8>(s, sb, y, STREAM, g, d_err, xcd_order(blockIdx.x, g.n_chunks), wave, threadIdx.x & 63, S);
 }
 
 __global__ void k_clear_err(uint32_t* p)
@@ -245,9 +245,10 @@ __global__ void k_clear_err(uint32_t* p)
 template <int RANK, bool STREAM>
 static hipError_t launch_rank64(const uint8_t* s, uint64_t sb, double* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
-    return launch_chunks(g.n_chunks, [&](uint32_t first, dim3 blocks) {
-        hipLaunchKernelGGL((k_decompress64<RANK, STREAM>), blocks, dim3(512), 0, st, s, sb, y, g, d_err, first);
-    });
+    const uint32_t at_once = 2u * (uint32_t)cu_count();
+    if (g.n_chunks > at_once) return launch_ahead<RANK, double, STREAM>(s, sb, y, g, d_err, at_once, st);
+    hipLaunchKernelGGL((k_decompress64<RANK, STREAM>), dim3((unsigned)g.n_chunks), dim3(512), 0, st, s, sb, y, g, d_err);
+    return hipGetLastError();
 }
 
 hipError_t launch_decompress_f64(const uint8_t* s, uint64_t sb, double* y, const Geom& g, uint32_t* d_err,

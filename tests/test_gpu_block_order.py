@@ -35,3 +35,22 @@ def test_every_chunk_once(shape, bits):
     fz.decompress(torch.from_numpy(ref).cuda(), shape, out=y, err=err)
     assert int(err.item()) == 0
     assert np.array_equal(y.cpu().numpy(), x)
+
+
+@pytest.mark.parametrize("bits", [3, 14])
+@pytest.mark.parametrize("shape", SHAPES + [(33, 1030, 530), (2, 1030, 1060), (34, 290_001), (3, 560_000), (48, 544 * 1024)])
+def test_every_chunk_once_in_double(shape, bits):
+    """The same forms with double outputs: whole lines or not, and thin last layers."""
+    print("case", shape, bits, flush=True)
+    rng = np.random.default_rng(len(shape) + bits)
+    span = 2 if bits == 3 else 1 << (12 - len(shape))
+    x = rng.integers(-span, span + 1, shape).astype(np.float64)
+    x += np.arange(shape[0], dtype=np.float64).reshape(-1, *[1] * (len(shape) - 1)) % 97
+    x.reshape(-1)[::80_021] += 100_000  # escapes
+    ref, st = O.compress_f64(x, 0.5, O.EB_ABS, threads=16)
+    assert st == 0
+    y = torch.full(shape, -7777.0, dtype=torch.float64, device="cuda")
+    err = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    fz.decompress(torch.from_numpy(ref).cuda(), shape, out=y, err=err)
+    assert int(err.item()) == 0
+    assert np.array_equal(y.cpu().numpy(), x)
