@@ -49,7 +49,10 @@ def test_thin_fields(shape, escapes):
     assert bool((guard[:64] == -7).all()) and bool((guard[64 + x.size:] == -7).all())
 
 
-@pytest.mark.parametrize("shape", [(2, 1030, 530), (7, 1030, 530), (3, 300_001)])
+BAD = [(2, 1030, 530), (7, 1030, 530), (3, 300_001), (2, 1030, 1060), (4, 1030, 1060), (7, 1030, 1060), (3, 560_001), (15, 560_001)]
+
+
+@pytest.mark.parametrize("shape", BAD)
 def test_a_pair_that_does_not_match(shape):
     x = field(shape, True)
     ref, st = O.compress(x, 0.5, O.EB_ABS, threads=8)
@@ -71,4 +74,30 @@ def test_a_pair_that_does_not_match(shape):
     got = y.cpu().numpy()
     assert (got[first] == -7).all()  # the bad chunk is not written
     got[first] = x[first]
+    assert np.array_equal(got, x)
+
+
+@pytest.mark.parametrize("chunk", [0, 1, 6])
+@pytest.mark.parametrize("shape", BAD)
+def test_a_flag_past_the_field(shape, chunk):
+    """One chunk of a workgroup is refused before its first barrier, the others
+    go on."""
+    x = field(shape, True)
+    ref, st = O.compress(x, 0.5, O.EB_ABS, threads=8)
+    assert st == 0
+    n_chunks = fz.stream_info(ref[:128].tobytes())["n_chunks"]
+    flags = 128 + (8 * n_chunks + 15) // 16 * 16 + 512 * chunk
+    ref[flags + 511] ^= 0x80  # a brick of the last layer, which the field does not reach
+    y = torch.full(shape, -7.0, device="cuda")
+    err = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    print("case", shape, chunk, flush=True)
+    fz.decompress(torch.from_numpy(ref).cuda(), shape, out=y, err=err)
+    assert int(err.item()) == 6
+    box = (32, 64) if len(shape) == 3 else (1024,)
+    per_row = -(-shape[-1] // box[-1])
+    org = (32 * (chunk // per_row), 64 * (chunk % per_row)) if len(shape) == 3 else (1024 * chunk,)
+    bad = tuple([slice(None)] + [slice(o, o + b) for o, b in zip(org, box)])
+    got = y.cpu().numpy()
+    assert (got[bad] == -7).all()
+    got[bad] = x[bad]
     assert np.array_equal(got, x)
