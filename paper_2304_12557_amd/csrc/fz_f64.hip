@@ -245,7 +245,8 @@ __global__ void k_clear_err(uint32_t* p)
 template <int RANK, bool STREAM>
 static hipError_t launch_rank64(const uint8_t* s, uint64_t sb, double* y, const Geom& g, uint32_t* d_err, hipStream_t st)
 {
-    const uint32_t at_once = 2u * (uint32_t)cu_count();
+    // (a small field does not ask for the device's size)
+    const uint32_t at_once = g.n_chunks > 256 ? 2u * (uint32_t)cu_count() : 512u;
     if (g.n_chunks > at_once) return launch_ahead<RANK, double, STREAM>(s, sb, y, g, d_err, at_once, st);
     hipLaunchKernelGGL((k_decompress64<RANK, STREAM>), dim3((unsigned)g.n_chunks), dim3(512), 0, st, s, sb, y, g, d_err);
     return hipGetLastError();

@@ -54,3 +54,34 @@ def test_every_chunk_once_in_double(shape, bits):
     fz.decompress(torch.from_numpy(ref).cuda(), shape, out=y, err=err)
     assert int(err.item()) == 0
     assert np.array_equal(y.cpu().numpy(), x)
+
+
+@pytest.mark.parametrize("double", [False, True])
+@pytest.mark.parametrize("shape", [(33, 530, 1088), (34, 290_001), (18_000_001,)])
+def test_replays(shape, double):
+    """Captured and replayed with other work and a rejected stream in between."""
+    rng = np.random.default_rng(9)
+    x = rng.integers(-9, 10, shape).astype(np.float64 if double else np.float32)
+    ref, st = (O.compress_f64 if double else O.compress)(x, 0.5, O.EB_ABS, threads=16)
+    assert st == 0
+    s = torch.from_numpy(ref).cuda()
+    y = torch.empty(shape, dtype=torch.float64 if double else torch.float32, device="cuda")
+    err = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    fz.decompress(s, shape, out=y, err=err)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        fz.decompress(s, shape, out=y, err=err, stream=torch.cuda.current_stream())
+    keep = s[4].item()
+    for i in range(4):
+        print("replay", i, shape, double, flush=True)
+        y.fill_(-7.0)
+        s[4] = 9 if i == 2 else keep  # an unknown version
+        g.replay()
+        torch.cuda.synchronize()
+        assert int(err.item()) == (7 if i == 2 else 0)
+        if i == 2:
+            assert bool((y == -7).all())
+        else:
+            assert np.array_equal(y.cpu().numpy(), x)
